@@ -42,8 +42,10 @@ constexpr int kMaxBatched = 512;   // largest structure of the batched kernel
 constexpr int kLargeBlock = 256;
 constexpr int kNVFit = 8;          // partial sums per slot: E, W6, |F - F*|^2
 constexpr int kNVEval = 16;        // E, W6, |F-F*|^2, J3, unused
-constexpr int kNVGrad = 8;         // dZ/dx (6), unused (2)
-constexpr int kNVGradTF = 16;      // Tersoff form: dZ/dx (9), unused (7)
+// Sums behind dZ/dx (see GradSum in mt_kernels.h): seven, one unused; the
+// Tersoff form's nine, seven unused.
+constexpr int kNVGrad = 8;
+constexpr int kNVGradTF = 16;
 constexpr int kNParam = 26;        // per-candidate decoded parameter record (25 used)
 
 // Decoded parameter record (float or double), filled per work item in LDS.
@@ -153,130 +155,6 @@ __device__ __forceinline__ double exp2_acc(double y) {
     p = p * f + 0.6931471805599453;
     p = p * f + 1.0;
     return __builtin_amdgcn_ldexp(p, (int)k);
-}
-
-template <typename S>
-struct Consts;
-template <>
-struct Consts<float> {
-    static constexpr float ln2 = 0.693147180559945309f;
-};
-template <>
-struct Consts<double> {
-    static constexpr double ln2 = 0.693147180559945309;
-};
-
-// Forward-mode derivative with respect to K of the six parameters (which
-// ones is set where the parameter record is seeded).
-template <typename S, int K = 6>
-struct Dual {
-    S v;
-    S d[K];
-};
-
-template <typename T>
-struct DualOf { static constexpr int tangents = 0; };
-template <typename S, int K>
-struct DualOf<Dual<S, K>> { static constexpr int tangents = K; };
-
-template <typename S, int K>
-__device__ __forceinline__ Dual<S, K> dconst(S v) {
-    Dual<S, K> r;
-    r.v = v;
-#pragma unroll
-    for (int k = 0; k < K; ++k) r.d[k] = S(0);
-    return r;
-}
-
-template <typename S> __device__ __forceinline__ S val(S a) { return a; }
-template <typename S, int K> __device__ __forceinline__ S val(const Dual<S, K>& a) { return a.v; }
-
-template <typename S, int K>
-__device__ __forceinline__ Dual<S, K> operator+(const Dual<S, K>& a, const Dual<S, K>& b) {
-    Dual<S, K> r; r.v = a.v + b.v;
-#pragma unroll
-    for (int k = 0; k < K; ++k) r.d[k] = a.d[k] + b.d[k];
-    return r;
-}
-template <typename S, int K>
-__device__ __forceinline__ Dual<S, K> operator-(const Dual<S, K>& a, const Dual<S, K>& b) {
-    Dual<S, K> r; r.v = a.v - b.v;
-#pragma unroll
-    for (int k = 0; k < K; ++k) r.d[k] = a.d[k] - b.d[k];
-    return r;
-}
-template <typename S, int K>
-__device__ __forceinline__ Dual<S, K> operator-(const Dual<S, K>& a) {
-    Dual<S, K> r; r.v = -a.v;
-#pragma unroll
-    for (int k = 0; k < K; ++k) r.d[k] = -a.d[k];
-    return r;
-}
-template <typename S, int K>
-__device__ __forceinline__ Dual<S, K> operator*(const Dual<S, K>& a, const Dual<S, K>& b) {
-    Dual<S, K> r; r.v = a.v * b.v;
-#pragma unroll
-    for (int k = 0; k < K; ++k) r.d[k] = a.d[k] * b.v + a.v * b.d[k];
-    return r;
-}
-template <typename S, int K>
-__device__ __forceinline__ Dual<S, K> operator*(const Dual<S, K>& a, S b) {
-    Dual<S, K> r; r.v = a.v * b;
-#pragma unroll
-    for (int k = 0; k < K; ++k) r.d[k] = a.d[k] * b;
-    return r;
-}
-template <typename S, int K>
-__device__ __forceinline__ Dual<S, K> operator*(S b, const Dual<S, K>& a) { return a * b; }
-template <typename S, int K>
-__device__ __forceinline__ Dual<S, K> operator+(const Dual<S, K>& a, S b) {
-    Dual<S, K> r = a; r.v += b; return r;
-}
-template <typename S, int K>
-__device__ __forceinline__ Dual<S, K> operator+(S b, const Dual<S, K>& a) { return a + b; }
-template <typename S, int K>
-__device__ __forceinline__ Dual<S, K> operator-(const Dual<S, K>& a, S b) {
-    Dual<S, K> r = a; r.v -= b; return r;
-}
-template <typename S, int K>
-__device__ __forceinline__ Dual<S, K> operator-(S b, const Dual<S, K>& a) { return (-a) + b; }
-template <typename S, int K>
-__device__ __forceinline__ Dual<S, K> dexp2(const Dual<S, K>& a) {
-    Dual<S, K> r; r.v = dexp2(a.v);
-    const S g = r.v * Consts<S>::ln2;
-#pragma unroll
-    for (int k = 0; k < K; ++k) r.d[k] = g * a.d[k];
-    return r;
-}
-template <typename S, int K>
-__device__ __forceinline__ Dual<S, K> dlog2(const Dual<S, K>& a) {
-    Dual<S, K> r; r.v = dlog2(a.v);
-    const S g = drcp(a.v * Consts<S>::ln2);
-#pragma unroll
-    for (int k = 0; k < K; ++k) r.d[k] = g * a.d[k];
-    return r;
-}
-template <typename S, int K>
-__device__ __forceinline__ Dual<S, K> drcp(const Dual<S, K>& a) {
-    Dual<S, K> r; r.v = drcp(a.v);
-    const S g = -r.v * r.v;
-#pragma unroll
-    for (int k = 0; k < K; ++k) r.d[k] = g * a.d[k];
-    return r;
-}
-template <typename S, int K>
-__device__ __forceinline__ Dual<S, K> dselect(bool c, const Dual<S, K>& a, const Dual<S, K>& b) {
-    Dual<S, K> r; r.v = c ? a.v : b.v;
-#pragma unroll
-    for (int k = 0; k < K; ++k) r.d[k] = c ? a.d[k] : b.d[k];
-    return r;
-}
-template <typename S>
-__device__ __forceinline__ S dselect(bool c, S a, S b) { return c ? a : b; }
-
-template <typename V, typename S>
-__device__ __forceinline__ V vconst(S v) {
-    if constexpr (sizeof(V) == sizeof(S)) return v; else return dconst<S, DualOf<V>::tangents>(v);
 }
 
 // ---------------------------------------------------------------------------

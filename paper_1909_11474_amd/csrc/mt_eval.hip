@@ -307,28 +307,35 @@ __global__ __launch_bounds__(256) void k_grad_coef(FinArgs F) {
     }
 }
 
-// dZ/dx [P][nx], nx = 6 (minimal) or 9 (Tersoff form).
+// dZ/dx [P][nx], nx = 6 (minimal) or 9 (Tersoff form): the totals of the grad
+// sums over all slots, then the parameters' factors.
+template <bool Full>
 __global__ __launch_bounds__(256) void k_finalize_grad(FinArgs F, double* dZdx) {
-    __shared__ double sh[9][256];
+    constexpr int NL = GradSums<Full>::value, nx = Form<Full>::nx;
+    __shared__ double sh[NL][256];
     const int c = blockIdx.x;
     const SetDev& d = F.set;
-    const int nx = F.full ? 9 : 6;
-    double acc[9] = {0, 0, 0, 0, 0, 0, 0, 0, 0};
+    double acc[NL];
+    for (int k = 0; k < NL; ++k) acc[k] = 0.0;
     for (int sl = threadIdx.x; sl < d.nslots; sl += blockDim.x) {
         const double* p = F.partial + ((size_t)c * d.nslots + sl) * F.nv;
-        for (int k = 0; k < nx; ++k) acc[k] += p[k];
+        for (int k = 0; k < NL; ++k) acc[k] += p[k];
     }
-    for (int k = 0; k < 9; ++k) sh[k][threadIdx.x] = acc[k];
+    for (int k = 0; k < NL; ++k) sh[k][threadIdx.x] = acc[k];
     __syncthreads();
     for (int o = blockDim.x / 2; o > 0; o >>= 1) {
         if ((int)threadIdx.x < o)
-            for (int k = 0; k < 9; ++k) sh[k][threadIdx.x] += sh[k][threadIdx.x + o];
+            for (int k = 0; k < NL; ++k) sh[k][threadIdx.x] += sh[k][threadIdx.x + o];
         __syncthreads();
     }
     if (threadIdx.x == 0) {
-        const bool ok = cand_valid(F.x, c, F.full);
+        const double* x = F.x + (size_t)nx * c;
         const double nan = __longlong_as_double(0x7ff8000000000000ll);
-        for (int k = 0; k < nx; ++k) dZdx[(size_t)nx * c + k] = ok ? sh[k][0] : nan;
+        double T[NL], G[nx];
+        for (int k = 0; k < NL; ++k) T[k] = sh[k][0];
+        grad_from_sums<Full>(x, T, G);
+        const bool ok = params_valid<Full>(x);
+        for (int k = 0; k < nx; ++k) dZdx[(size_t)nx * c + k] = ok ? G[k] : nan;
     }
 }
 
@@ -449,16 +456,25 @@ bool family_adjoint(int fam) {
     return fam == FAM_ADJ32 || fam == FAM_ADJ64 || fam == FAM_ADJ32F || fam == FAM_ADJ64F;
 }
 
-// LDS of one item of nc candidates: parameter records, bond-gradient exchange
-// slots (4 values each) and, for the adjoint, the force-residual exchange.
+// The fitness family whose call writes an adjoint family's force residuals.
+int fit_family(int fam) {
+    switch (fam) {
+        case FAM_ADJ32: return FAM_FIT32;
+        case FAM_ADJ64: return FAM_FIT64;
+        case FAM_ADJ32F: return FAM_FIT32F;
+        default: return FAM_FIT64F;
+    }
+}
+
+// LDS of one item of nc candidates: parameter records and the bond-gradient
+// exchange slots (4 values each) or, for the adjoint, the force residuals.
 size_t item_lds(const mt_set* set, int s, int block, int fam, int nc) {
     const int npad = set->h_npad[s];
     const int R = block / npad;
     const size_t e = (size_t)family_elem(fam);
     const size_t par = ((size_t)nc * kNParam * e + 31) & ~(size_t)31;
-    const size_t xs = (size_t)R * set->h_xsize[s] * 4 * e;
-    const size_t ad = family_adjoint(fam) ? (size_t)R * npad * 4 * e : 0;
-    return par + xs + ad;
+    const size_t slots = family_adjoint(fam) ? (size_t)npad : (size_t)set->h_xsize[s];
+    return par + (size_t)R * slots * 4 * e;
 }
 
 hipError_t launch_family(int fam, int mc, dim3 g, dim3 b, size_t lds, hipStream_t st,
@@ -662,7 +678,9 @@ ItemPlan* get_plan(mt_set* set, int P, const LaunchCfg& cfg, int fam) {
             const int npad = set->h_npad[s];
             if (!plain && cfg.block < npad) return nullptr;
             const int block = block_for(set, s, cfg, P, fam, plain);
-            if (block == 0) {
+            // the adjoint reads the residuals of the structures that its
+            // fitness call batched
+            if (block == 0 || (family_adjoint(fam) && block_for(set, s, cfg, P, fit_family(fam), plain) == 0)) {
                 plan->twopass.push_back(s);
                 continue;
             }
@@ -1034,7 +1052,7 @@ static int launch_grad_coef(mt_set* set, int P, const double* w, const double* Z
 
 // Two-pass fitness gradient of the listed structures, one candidate chunk at a
 // time: bond gradients staged as for the two-pass fitness (no partial sums),
-// force residuals staged [chunk][3][Ns] in abuf, then the dual passes.
+// force residuals staged [chunk][3][Ns] in abuf, then the grad sums.
 template <typename S>
 static int launch_twopass_adjoint(mt_set* set, const std::vector<int>& structs, int P, int nv,
                                   hipStream_t st) {
@@ -1089,14 +1107,13 @@ static int adjoint_common(mt_set* set, const LaunchCfg& cfg, int P, int precisio
     BArgs<float> Af = make_args<float>(set, set->partial2.as<double>(), nv);
     BArgs<double> Ad = make_args<double>(set, set->partial2.as<double>(), nv);
     Af.coef = Ad.coef = set->zwork.as<double>();
-    // the fitness call before this one wrote the batched atoms' residuals (a
-    // structure the adjoint batches needs no more LDS in the fitness, so the
-    // fitness batched it too)
+    // the fitness call before this one wrote the batched atoms' residuals (the
+    // adjoint's work list batches no structure that the fitness did not)
     Af.resid = set->resid.as<float>();
     Ad.resid = set->resid.as<double>();
     TRY_RC(run_plan(set, plan, cfg, fam, Af, Ad, 1, st));
-    // structures over the batched limit, and those whose adjoint does not fit
-    // one block's LDS, take the two-pass adjoint
+    // structures over the batched limit, and those its work list leaves out,
+    // take the two-pass adjoint
     std::vector<int> structs;
     for (int s = 0; s < set->S; ++s)
         if (set->h_large[s]) structs.push_back(s);
@@ -1115,7 +1132,8 @@ int launch_adjoint(mt_set* set, const LaunchCfg& cfg, int P, int precision, cons
 int launch_finalize_grad(mt_set* set, int P, const double* Z, double* dZdx, hipStream_t st) {
     (void)Z;
     FinArgs F = make_fin(set, set->cur_form ? kNVGradTF : kNVGrad, set->partial2.as<double>());
-    hipLaunchKernelGGL(k_finalize_grad, dim3(P), dim3(256), 0, st, F, dZdx);
+    if (set->cur_form) hipLaunchKernelGGL(k_finalize_grad<true>, dim3(P), dim3(256), 0, st, F, dZdx);
+    else hipLaunchKernelGGL(k_finalize_grad<false>, dim3(P), dim3(256), 0, st, F, dZdx);
     HIPCHECK(hipGetLastError());
     return MT_OK;
 }

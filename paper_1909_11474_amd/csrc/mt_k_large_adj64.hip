@@ -1,5 +1,5 @@
 // Instantiates the double two-pass fitness-gradient kernels of mt_kernels.h
-// (force residuals, dual passes) for the minimal potential; the Tersoff
+// (force residuals, grad sums) for the minimal potential; the Tersoff
 // form's are in mt_k_tf_large_adj64.hip.
 #include "mt_kernels.h"
 

@@ -1,5 +1,5 @@
 // Instantiates the double two-pass fitness-gradient kernels of mt_kernels.h
-// (force residuals, dual passes) for the Tersoff form.
+// (force residuals, grad sums) for the Tersoff form.
 #include "mt_kernels.h"
 
 namespace mt {

@@ -230,8 +230,8 @@ __device__ __forceinline__ void store_group(double* v, const ItemCtx& x, bool gr
 }
 
 // LDS layout of a block while it works on an item: [it.nc x kNParam parameter
-// records][R x xsz exchange slots (Vec4)][adjoint: R x npad force residuals
-// (Vec4)].  The exchange follows the item's own records, so the LDS a launch
+// records][R x xsz exchange slots (Vec4); adjoint: R x npad force residuals
+// (Vec4) instead].  The exchange follows the item's own records, so the LDS a launch
 // gets for the largest (records + exchange) of its structures covers every
 // item, whatever the candidate tiles of the other structures in the launch.
 template <typename S>
@@ -249,7 +249,7 @@ __device__ __forceinline__ void run_batched(const BArgs<S>& A, const Item& it, c
     const int N = d.N;
     const S* __restrict__ pbuf = reinterpret_cast<const S*>(lds);
     Vec4<S>* __restrict__ xb = reinterpret_cast<Vec4<S>*>(lds + lds_param_bytes<S>(it.nc));
-    Geo<S, M> g;
+    Geo<S, M, Full> g;
     g.load(geom_of<S>(d), N, x.atom, x.active, d.gcs);
     constexpr int MM = M > 0 ? M : 1;
     int rv[MM];
@@ -273,7 +273,7 @@ __device__ __forceinline__ void run_batched(const BArgs<S>& A, const Item& it, c
         const bool cok = x.active && group_ok;
         const int clv = group_ok ? cl : 0;
         const int c = it.c0 + clv;
-        Cand<S, S, Full> p;
+        Cand<S, Full> p;
         load_cand(pbuf + kNParam * clv, p);
         // Each bond gradient G_j goes to its exchange slot as soon as the site
         // routine emits it and is folded into this atom's own force sum and
@@ -283,7 +283,7 @@ __device__ __forceinline__ void run_batched(const BArgs<S>& A, const Item& it, c
         S w6[6];
 #pragma unroll
         for (int k = 0; k < 6; ++k) w6[k] = S(0);
-        site_eval_sink<S, S, M, true, (M > kPairwiseMax), false, Full>(
+        site_eval_sink<S, M, true, (M > kPairwiseMax), Full>(
             g, p, U, [&](int m, S gx, S gy, S gz) {
                 S* slot = &xb[x.own + m * x.g].x;     // the fourth component is never read
                 slot[0] = gx;
@@ -448,75 +448,290 @@ void k_plain(BArgs<S> A) {
 //   dZ/dx|_s = sum_i [ k_e U_i' - sum_j G_ij' . delta_ij ],
 //   delta_ij = k_f (a_j - a_i) + C_s r_ij,   a = F - F*,
 // where ' is the derivative with respect to the parameters (six, or nine for
-// the Tersoff form; forward-mode dual numbers), k_e = w_e (e_s - e*_s)/(N_s Z_e Q_e), k_f = w_f/(Z_f Q_f) and
+// the Tersoff form), k_e = w_e (e_s - e*_s)/(N_s Z_e Q_e), k_f = w_f/(Z_f Q_f) and
 // C_s = w_v/(N_s Z_v Q_v) times the symmetric matrix of virial residuals (off
 // diagonals halved).  These follow from dF_i/dx = -d/dx dE/dr_i and
 // dW/dx = -sum r_ij (x) dG_ij/dx.
 //
-// Per candidate: a plain pass gives the force residuals a_i, shared through
-// LDS; then dual passes over K of the parameters at a time contract each
-// G_ij' with delta_ij as soon as the site routine emits it, so no bond
-// gradient derivative is held across the exchange.
+// sum_j G_ij . delta_ij is the derivative D of U_i when every bond vector moves
+// along its delta_ij, so the contraction is L[U_i'] with the linear map
+// L[f] = k_e f - D f.  U_i' is a closed form in each bond's r, f_C and angular
+// sums, so one derivative along delta of those few quantities serves all the
+// parameters: no bond gradient is formed, and the parameter count does not
+// multiply the pair loop.  Against forward-mode duals over three to six
+// parameters at a time through the whole gradient (256 registers, 2 KB of
+// scratch a lane at M = 12, bound by VALU issue and spills): a fitness_grad call
+// on 300 structures of 8-512 atoms x 64 candidates 1415 -> 450 us (float32), on
+// 18 structures x 5 Tersoff-form candidates 1004 -> 288 us (float64).
 // ---------------------------------------------------------------------------
 
-// Tangents per dual pass: six for small coordination (one pass for the six
-// minimal parameters; six and three for the nine of the Tersoff form), three
-// where six would not fit in registers.
-template <typename S, int M>
-struct AdjointTangents {
-    static constexpr int value = (M <= 4 && sizeof(S) == 4) ? 6 : 3;
+// The sums over an atom's bonds that dZ/dx is made of, each under L; the
+// parameters' own factors (D0, mu, ...) are the same for every atom and are
+// applied once per candidate in float64 (k_finalize_grad).  With
+// e_R = e^{-lambda (r - r0)}, e_A = e^{-mu (r - r0)}, Y = -1/2 f_C e_A db/dzeta:
+//   R, A     f_C e_R,  f_C b e_A
+//   DR, DA   the same times r - r0
+//   N        -1/2 f_C e_A db/dn
+//   minimal: Z2 = Y sum_k f_C t^2, Z1 = Y sum_k f_C t        (t = cos - h)
+//   Tersoff: S0 = Y sum_k f_C, SQ = Y sum_k f_C q, SQR = Y sum_k f_C q rho,
+//            SP = Y sum_k f_C t rho^2   (rho = 1/(d^2 + t^2), q = t^2 rho)
+enum GradSum {
+    GS_R = 0, GS_A, GS_DR, GS_DA, GS_N,
+    GS_Z2, GS_Z1,
+    GS_S0 = 5, GS_SQ, GS_SQR, GS_SP
+};
+template <bool Full>
+struct GradSums {
+    static constexpr int value = Full ? 9 : 7;
 };
 
-// pass(Base, K') for consecutive blocks of at most K of the NX parameters.
-template <int Base, int NX, int K, typename F>
-__device__ __forceinline__ void for_passes(F&& pass) {
-    if constexpr (Base < NX) {
-        constexpr int KK = (NX - Base) < K ? (NX - Base) : K;
-        pass(std::integral_constant<int, Base>{}, std::integral_constant<int, KK>{});
-        for_passes<Base + KK, NX, K>(pass);
-    }
-}
+// Largest coordination whose angular sums of the Tersoff form take every
+// unordered pair once, with the sums of all bonds live; above it they are
+// formed bond by bond.
+template <typename S>
+constexpr int kAdjointPairs = sizeof(S) == 8 ? 4 : 12;
 
-// The parameter derivatives of one atom's site terms contracted with its
-// residual directions: phi[p] = k_e dU_i/dx_p - sum_j dG_ij/dx_p . delta_ij,
-// delta_ij = k_f (a_j - a_i) + C_s r_ij, by dual passes over KK parameters at a
-// time.  rec: the candidate's decoded record, xrow its parameters (Tersoff
-// form), (ax, ay, az) this atom's force residual, aj(m) the residual of the
-// atom at the far end of bond m, cf the coefficients k_e, k_f, C_s (xx yy zz yz
-// zx xy, off-diagonals halved) of the (candidate, structure).
+// One atom's grad sums.  rec: the candidate's decoded record, (ax, ay, az) this
+// atom's force residual, aj(m) the residual of the atom at the far end of bond
+// m, cf the coefficients k_e, k_f, C_s (xx yy zz yz zx xy, off-diagonals halved)
+// of the (candidate, structure).
 template <typename S, int M, bool Full, typename Aj>
-__device__ __forceinline__ void adjoint_phi(Geo<S, M>& g, const S* __restrict__ rec,
-                                            const double* __restrict__ xrow, S ax, S ay, S az,
-                                            Aj&& aj, const double* __restrict__ cf,
-                                            S (&phi)[Form<Full>::nx]) {
-    constexpr int K = AdjointTangents<S, M>::value;
-    constexpr int NX = Form<Full>::nx;
+__device__ __forceinline__ void adjoint_sums(Geo<S, M, Full>& g, const S* __restrict__ rec, S ax, S ay, S az,
+                                             Aj&& aj, const double* __restrict__ cf,
+                                             S (&L)[GradSums<Full>::value]) {
+    constexpr int MM = M > 0 ? M : 1;
     const S ke = (S)cf[0], kf = (S)cf[1];
     const S cxx = (S)cf[2], cyy = (S)cf[3], czz = (S)cf[4];
     const S cyz = (S)cf[5], czx = (S)cf[6], cxy = (S)cf[7];
-    auto pass = [&](auto base_c, auto k_c) {
-        constexpr int Base = decltype(base_c)::value;
-        constexpr int KK = decltype(k_c)::value;
-        Cand<Dual<S, KK>, S, Full> p;
-        if constexpr (Full) load_cand<Base>(rec, xrow, p);
-        else load_cand<Base>(rec, p);
-        Dual<S, KK> U;
-        site_eval_sink<Dual<S, KK>, S, M, false, true, true>(
-            g, p, U, [&](int m, const Dual<S, KK>& gx, const Dual<S, KK>& gy, const Dual<S, KK>& gz) {
-                const Vec4<S> a = aj(m);
-                const S dx = g.rhi[m] * g.ux[m], dy = g.rhi[m] * g.uy[m], dz = g.rhi[m] * g.uz[m];
-                const S ex = kf * (a.x - ax) + cxx * dx + cxy * dy + czx * dz;
-                const S ey = kf * (a.y - ay) + cxy * dx + cyy * dy + cyz * dz;
-                const S ez = kf * (a.z - az) + czx * dx + cyz * dy + czz * dz;
-#pragma unroll
-                for (int t = 0; t < KK; ++t) phi[Base + t] -= gx.d[t] * ex + gy.d[t] * ey + gz.d[t] * ez;
-            });
-#pragma unroll
-        for (int t = 0; t < KK; ++t) phi[Base + t] += ke * U.d[t];
+    Cand<S, Full> p;
+    load_cand(rec, p);
+    if constexpr (!Geo<S, M, Full>::kCache && M > 1) {
+        // keep the uncached cos(theta) out of registers across candidates
+        opaque(g.ux);
+        opaque(g.uy);
+        opaque(g.uz);
+    }
+    // D of bond m's length, f_C and unit vector
+    struct BondD {
+        S dr, dfc, wx, wy, wz;
     };
+    auto bond_d = [&](int m) {
+        const Vec4<S> a = aj(m);
+        const S dx = g.rhi[m] * g.ux[m], dy = g.rhi[m] * g.uy[m], dz = g.rhi[m] * g.uz[m];
+        const S ex = kf * (a.x - ax) + cxx * dx + cxy * dy + czx * dz;
+        const S ey = kf * (a.y - ay) + cxy * dx + cyy * dy + cyz * dz;
+        const S ez = kf * (a.z - az) + czx * dx + cyz * dy + czz * dz;
+        BondD d;
+        d.dr = ex * g.ux[m] + ey * g.uy[m] + ez * g.uz[m];
+        d.dfc = (S(2) * g.hfcp[m]) * d.dr;
+        d.wx = (ex - d.dr * g.ux[m]) * g.rinv[m];
+        d.wy = (ey - d.dr * g.uy[m]) * g.rinv[m];
+        d.wz = (ez - d.dr * g.uz[m]) * g.rinv[m];
+        return d;
+    };
+    // Angular sums over the other bonds and their D.  Minimal: s[0] = sum f_C t^2,
+    // s[1] = sum f_C t.  Tersoff: sums of f_C, f_C q, f_C q rho, f_C t rho^2.
+    constexpr int NS = Full ? 4 : 2;
+    auto terms = [&](S t, S dt, S (&f)[NS], S (&df)[NS]) {
+        if constexpr (Full) {
+            const S t2 = t * t;
+            const S rho = drcp(p.d2 + t2);
+            const S q = t2 * rho, pr = t * rho * rho;
+            f[0] = S(1); f[1] = q; f[2] = q * rho; f[3] = pr;
+            const S e = S(2) * pr * dt;           // -D rho
+            df[0] = S(0); df[1] = p.d2 * e; df[2] = (p.d2 * rho - q) * e;
+            df[3] = (rho * rho) * (S(1) - S(4) * q) * dt;
+        } else {
+            f[0] = t * t; f[1] = t;
+            df[0] = (S(2) * t) * dt; df[1] = dt;
+        }
+    };
+    const S mu = S(2) * p.hmu, lam = S(2) * p.hlambda;
+    const S c1 = S(2) * p.ninv2n * p.ninv2n;              // 1 / (2 n^2)
+    const S ln2 = S(0.6931471805599453);
 #pragma unroll
-    for (int k = 0; k < NX; ++k) phi[k] = S(0);
-    for_passes<0, NX, K>(pass);
+    for (int k = 0; k < GradSums<Full>::value; ++k) L[k] = S(0);
+    auto bond = [&](int j, S drj, S dfcj, const S (&s)[NS], const S (&ds)[NS]) {
+        S z, dz;
+        if constexpr (Full) {
+            z = p.gam * s[0] + p.K * s[1];
+            dz = p.gam * ds[0] + p.K * ds[1];
+        } else {
+            z = p.zs * s[0];
+            dz = p.zs * ds[0];
+        }
+        // zeta = 0: b = 1 and every derivative of b is dropped (zn = 0)
+        const bool pos = z > S(0);
+        const S zsafe = pos ? z : S(1);
+        const S delta = (g.rhi[j] - p.r0hi) + (g.rlo[j] - p.r0lo);
+        const S eA = dexp2(-(p.aA * delta));
+        S eR;
+        if constexpr (Full) eR = dexp2(-(p.aR * delta));
+        else eR = eA * eA;
+        const S l2z = dlog2(zsafe);
+        const S zn = pos ? dexp2(p.n * l2z) : S(0);
+        const S onep = S(1) + zn;
+        const S v = drcp(onep), w = zn * v, iz = drcp(zsafe);
+        const S l2p = dlog2(onep);
+        const S b = dexp2(p.ninv2n * l2p);
+        // db/dzeta, db/dn (over b: kn) and their D, with e = D zeta / zeta:
+        // D w = n w v e, D(db/dn) = Db (kn + v ln zeta)
+        const S e = dz * iz;
+        const S db = S(-0.5) * (b * w) * e;
+        const S bz = S(-0.5) * (b * w) * iz;
+        const S dbz = (bz * e) * (p.n * v - S(0.5) * w - S(1));
+        const S kn = ln2 * (c1 * l2p + p.ninv2n * (w * l2z));
+        const S bn = b * kn;
+        const S dbn = db * (kn + (v * ln2) * l2z);
+        const S R = g.fc[j] * eR, dR = dfcj * eR - (lam * drj) * R;
+        const S q = g.fc[j] * eA, dq = dfcj * eA - (mu * drj) * q;
+        const S A = b * q, dA = b * dq + db * q;
+        const S LR = ke * R - dR, LA = ke * A - dA;
+        L[GS_R] += LR;
+        L[GS_A] += LA;
+        L[GS_DR] += delta * LR - drj * R;
+        L[GS_DA] += delta * LA - drj * A;
+        L[GS_N] -= S(0.5) * (ke * (q * bn) - (dq * bn + q * dbn));
+        const S Y = S(-0.5) * (q * bz), dY = S(-0.5) * (dq * bz + q * dbz);
+        const S LY = ke * Y - dY;
+#pragma unroll
+        for (int c = 0; c < NS; ++c) L[5 + c] += LY * s[c] - Y * ds[c];
+        __builtin_amdgcn_sched_barrier(0);
+    };
+    if constexpr (Geo<S, M, Full>::kMoments) {
+        // Minimal form, larger coordination: the pair sums from the moments
+        // sum f_C, sum f_C u, sum f_C u u^T and their D, so the work grows with
+        // the bonds, not the bond pairs, and nothing is held per bond.
+        S txx = S(0), tyy = txx, tzz = txx, tyz = txx, tzx = txx, txy = txx, mx = txx, my = txx, mz = txx;
+        S exx = S(0), eyy = exx, ezz = exx, eyz = exx, ezx = exx, exy = exx, nx = exx, ny = exx, nz = exx;
+        S dS = S(0);
+#pragma unroll
+        for (int m = 0; m < M; ++m) {
+            const BondD d = bond_d(m);
+            const S ux = g.ux[m], uy = g.uy[m], uz = g.uz[m], f = g.fc[m];
+            const S fx = f * ux, fy = f * uy, fz = f * uz;
+            mx += fx; my += fy; mz += fz;
+            txx += fx * ux; tyy += fy * uy; tzz += fz * uz;
+            tyz += fy * uz; tzx += fz * ux; txy += fx * uy;
+            // D(f u u^T) = v u^T + u v^T with v = f w + dfc u / 2
+            const S gx = f * d.wx, gy = f * d.wy, gz = f * d.wz, hf = S(0.5) * d.dfc;
+            const S vx = gx + hf * ux, vy = gy + hf * uy, vz = gz + hf * uz;
+            nx += gx + d.dfc * ux; ny += gy + d.dfc * uy; nz += gz + d.dfc * uz;
+            exx += (S(2) * vx) * ux; eyy += (S(2) * vy) * uy; ezz += (S(2) * vz) * uz;
+            eyz += vy * uz + vz * uy; ezx += vz * ux + vx * uz; exy += vx * uy + vy * ux;
+            dS += d.dfc;
+            __builtin_amdgcn_sched_barrier(0);
+        }
+#pragma unroll
+        for (int j = 0; j < M; ++j) {
+            const BondD d = bond_d(j);
+            const S ux = g.ux[j], uy = g.uy[j], uz = g.uz[j];
+            const S yx = txx * ux + txy * uy + tzx * uz, yy = txy * ux + tyy * uy + tyz * uz,
+                    yz = tzx * ux + tyz * uy + tzz * uz;
+            const S zx = exx * ux + exy * uy + ezx * uz, zy = exy * ux + eyy * uy + eyz * uz,
+                    zz = ezx * ux + eyz * uy + ezz * uz;
+            // D of sum_k f_C c and sum_k f_C c^2 over the other bonds (c = 1 for
+            // the bond itself)
+            const S p1 = (d.wx * mx + d.wy * my + d.wz * mz) + (ux * nx + uy * ny + uz * nz) - d.dfc;
+            const S p2 = S(2) * (d.wx * yx + d.wy * yy + d.wz * yz) + (ux * zx + uy * zy + uz * zz) - d.dfc;
+            const S ds0 = dS - d.dfc;
+            const S t = (g.sh[j] - p.h) - p.hlo;
+            const S s1 = g.ss[j] * t;
+            const S s[NS] = {g.sv[j] + s1 * t, s1};
+            const S ds[NS] = {p2 - p.h * (S(2) * p1 - p.h * ds0), p1 - p.h * ds0};
+            bond(j, d.dr, d.dfc, s, ds);
+        }
+    } else if constexpr (!Full || M <= kAdjointPairs<S>) {
+        // every unordered bond pair once
+        BondD d[MM];
+#pragma unroll
+        for (int m = 0; m < M; ++m) d[m] = bond_d(m);
+        S s[MM][NS], ds[MM][NS];
+#pragma unroll
+        for (int m = 0; m < M; ++m)
+#pragma unroll
+            for (int k = 0; k < NS; ++k) s[m][k] = ds[m][k] = S(0);
+        int pidx = 0;
+#pragma unroll
+        for (int j = 0; j < M; ++j) {
+#pragma unroll
+            for (int k = j + 1; k < M; ++k) {
+                const S t = (g.cosjk(j, k, pidx++) - p.h) - p.hlo;
+                const S dt = (d[j].wx * g.ux[k] + d[j].wy * g.uy[k] + d[j].wz * g.uz[k]) +
+                             (d[k].wx * g.ux[j] + d[k].wy * g.uy[j] + d[k].wz * g.uz[j]);
+                S f[NS], df[NS];
+                terms(t, dt, f, df);
+#pragma unroll
+                for (int c = 0; c < NS; ++c) {
+                    s[j][c] += g.fc[k] * f[c];
+                    s[k][c] += g.fc[j] * f[c];
+                    ds[j][c] += d[k].dfc * f[c] + g.fc[k] * df[c];
+                    ds[k][c] += d[j].dfc * f[c] + g.fc[j] * df[c];
+                }
+            }
+        }
+#pragma unroll
+        for (int j = 0; j < M; ++j) bond(j, d[j].dr, d[j].dfc, s[j], ds[j]);
+    } else {
+        // one bond at a time, every pair from both ends: twice the pair
+        // arithmetic, but the sums of one bond only are live
+        BondD d[MM];
+#pragma unroll
+        for (int m = 0; m < M; ++m) d[m] = bond_d(m);
+#pragma unroll
+        for (int j = 0; j < M; ++j) {
+            S s[NS], ds[NS];
+#pragma unroll
+            for (int c = 0; c < NS; ++c) s[c] = ds[c] = S(0);
+#pragma unroll
+            for (int k = 0; k < M; ++k) {
+                if (k == j) continue;
+                const S t = ((g.ux[j] * g.ux[k] + g.uy[j] * g.uy[k] + g.uz[j] * g.uz[k]) - p.h) - p.hlo;
+                const S dt = (d[j].wx * g.ux[k] + d[j].wy * g.uy[k] + d[j].wz * g.uz[k]) +
+                             (d[k].wx * g.ux[j] + d[k].wy * g.uy[j] + d[k].wz * g.uz[j]);
+                S f[NS], df[NS];
+                terms(t, dt, f, df);
+#pragma unroll
+                for (int c = 0; c < NS; ++c) {
+                    s[c] += g.fc[k] * f[c];
+                    ds[c] += d[k].dfc * f[c] + g.fc[k] * df[c];
+                }
+            }
+            bond(j, d[j].dr, d[j].dfc, s, ds);
+        }
+    }
+}
+
+// dZ/dx from the totals T of the grad sums: the parameters' factors.
+template <bool Full>
+__device__ __forceinline__ void grad_from_sums(const double* __restrict__ x, const double* __restrict__ T,
+                                               double* __restrict__ G) {
+    const double D0 = x[0], al = x[1];
+    if constexpr (Full) {
+        // DR = D0/(S-1), DA = S DR, mu = alpha sqrt(2/S), lambda = alpha sqrt(2S)
+        const double Sl = x[3], gam = x[4], c = x[6], d = x[7];
+        const double sm1 = Sl - 1.0, DR = D0 / sm1, DA = Sl * DR;
+        const double rs = sqrt(2.0 / Sl), rl = sqrt(2.0 * Sl), mu = al * rs, lam = al * rl;
+        const double K = gam * c * c / (d * d);
+        G[0] = 0.5 * (T[GS_R] - Sl * T[GS_A]) / sm1;
+        G[1] = 0.5 * (rs * DA * T[GS_DA] - rl * DR * T[GS_DR]);
+        G[2] = 0.5 * (lam * DR * T[GS_R] - mu * DA * T[GS_A]);
+        G[3] = 0.5 * ((DA / (Sl * sm1)) * T[GS_A] - (DR / sm1) * T[GS_R] -
+                      (0.5 / Sl) * (lam * DR * T[GS_DR] + mu * DA * T[GS_DA]));
+        G[4] = DA * (T[GS_S0] + (c * c / (d * d)) * T[GS_SQ]);
+        G[5] = DA * T[GS_N];
+        G[6] = DA * (2.0 * gam * c / (d * d)) * T[GS_SQ];
+        G[7] = DA * (-2.0 * K) * (T[GS_SQ] / d + d * T[GS_SQR]);
+        G[8] = DA * (-2.0 * K * d * d) * T[GS_SP];
+    } else {
+        // S = 2: DR = D0, DA = 2 D0, mu = alpha, lambda = 2 alpha
+        G[0] = 0.5 * T[GS_R] - T[GS_A];
+        G[1] = D0 * (T[GS_DA] - T[GS_DR]);
+        G[2] = al * D0 * (T[GS_R] - T[GS_A]);
+        G[3] = 2.0 * D0 * T[GS_Z2];
+        G[4] = 2.0 * D0 * T[GS_N];
+        G[5] = -4.0 * D0 * x[3] * T[GS_Z1];
+    }
 }
 
 template <typename S, int M, bool Full = false>
@@ -525,12 +740,12 @@ __device__ __forceinline__ void run_adjoint(const BArgs<S>& A, const Item& it, c
     const SetDev& d = A.set;
     const int N = d.N;
     const S* __restrict__ pbuf = reinterpret_cast<const S*>(lds);
-    Vec4<S>* __restrict__ xb = reinterpret_cast<Vec4<S>*>(lds + lds_param_bytes<S>(it.nc));
-    Vec4<S>* __restrict__ ab = xb + (size_t)x.R * x.xsz + (size_t)x.q * x.npad;
-    Geo<S, M> g;
-    g.load(geom_of<S>(d), N, x.atom, x.active);
+    Vec4<S>* __restrict__ ab =
+        reinterpret_cast<Vec4<S>*>(lds + lds_param_bytes<S>(it.nc)) + (size_t)x.q * x.npad;
+    Geo<S, M, Full> g;
+    g.load(geom_of<S>(d), N, x.atom, x.active, d.gcs);
     constexpr int MM = M > 0 ? M : 1;
-    constexpr int NX = Form<Full>::nx;
+    constexpr int NL = GradSums<Full>::value;
     int jl[MM];
 #pragma unroll
     for (int m = 0; m < M; ++m) jl[m] = x.active ? d.jl[(size_t)m * N + x.atom] : x.la;
@@ -550,24 +765,24 @@ __device__ __forceinline__ void run_adjoint(const BArgs<S>& A, const Item& it, c
         }
         ab[x.la] = Vec4<S>{ax, ay, az, S(0)};
         exchange_sync(x.block_sync);
-        S phi[NX];
-        adjoint_phi<S, M, Full>(
-            g, prec, A.x + (size_t)NX * c, ax, ay, az,
+        S L[NL];
+        adjoint_sums<S, M, Full>(
+            g, prec, ax, ay, az,
             [&](int m) {
-                // a fresh read in every pass (a reused one would stay live across passes)
+                // read afresh on every use (a reused value would stay live)
                 int jm = jl[m];
                 asm volatile("" : "+v"(jm));
                 return ab[jm];
             },
-            A.coef + ((size_t)c * d.S + x.s) * 8, phi);
+            A.coef + ((size_t)c * d.S + x.s) * 8, L);
         exchange_sync(x.block_sync);
         double v[8];
 #pragma unroll
-        for (int k = 0; k < 8; ++k) v[k] = k < NX ? (double)phi[k < NX ? k : 0] : 0.0;
-        store_group(v, x, group_ok, A.partial, d.nslots, A.nv, c, 0, Full ? 0xff : 0x3f);
+        for (int k = 0; k < 8; ++k) v[k] = k < NL ? (double)L[k < NL ? k : 0] : 0.0;
+        store_group(v, x, group_ok, A.partial, d.nslots, A.nv, c, 0, Full ? 0xff : 0x7f);
         if constexpr (Full) {
             double u[8];
-            u[0] = (double)phi[8];
+            u[0] = (double)L[8];
 #pragma unroll
             for (int k = 1; k < 8; ++k) u[k] = 0.0;
             store_group(u, x, group_ok, A.partial, d.nslots, A.nv, c, 8, 0x01);
@@ -666,7 +881,7 @@ __device__ __forceinline__ void run_large_site(const BArgs<S>& A, const LArgs& L
                                                bool active, double& sum, int& vidx, int rows = M) {
     const SetDev& d = A.set;
     const int N = d.N;
-    Geo<S, M> g;
+    Geo<S, M, Full> g;
     g.load(geom_of<S>(d), N, atom, active, d.gcs, rows);
     constexpr int MM = M > 0 ? M : 1;
     const int c = L.c0 + blockIdx.y;
@@ -675,13 +890,13 @@ __device__ __forceinline__ void run_large_site(const BArgs<S>& A, const LArgs& L
     const int lb = active ? d.lbo[atom] : 0;
     S rec[kNParam];
     decode_record<S, Full>(A.x + Form<Full>::nx * (size_t)c, rec);
-    Cand<S, S, Full> p;
+    Cand<S, Full> p;
     load_cand(rec, p);
     double U;
     S Gx[MM], Gy[MM], Gz[MM];
     // about one wavefront per SIMD for a large structure: the bonds' float64
     // energy chains interleave
-    site_eval<S, S, M, E64, Full, false>(g, p, U, Gx, Gy, Gz);
+    site_eval<S, M, E64, Full, false>(g, p, U, Gx, Gy, Gz);
     using V4 = typename Stage4<S>::T;
     V4* gb = reinterpret_cast<V4*>(L.gbuf) + (size_t)blockIdx.y * nbs;
     if (active) {
@@ -820,7 +1035,7 @@ __global__ __launch_bounds__(256) void k_large_gather(BArgs<S> A, LArgs L) {
 // Fitness gradient of the two-pass structures.  k_large_site stages the bond
 // gradients of a candidate chunk (as for the fitness), k_large_residual turns
 // them into the force residuals a_i = F_i - F*_i, staged [chunk][3][Ns], and
-// k_large_adjoint runs the dual passes of every atom (adjoint_phi) with the
+// k_large_adjoint forms every atom's grad sums (adjoint_sums) with the
 // residuals of its bond partners read from there; its partial sums go to the
 // structure's per-wavefront slots as in the batched adjoint.
 // ---------------------------------------------------------------------------
@@ -858,34 +1073,34 @@ __device__ __forceinline__ void run_large_adjoint(const BArgs<S>& A, const LArgs
     const SetDev& d = A.set;
     const int N = d.N;
     constexpr int MM = M > 0 ? M : 1;
-    constexpr int NX = Form<Full>::nx;
-    Geo<S, M> g;
-    g.load(geom_of<S>(d), N, atom, active, nullptr, d.kcap);
+    constexpr int NL = GradSums<Full>::value;
+    Geo<S, M, Full> g;
+    g.load(geom_of<S>(d), N, atom, active, d.gcs, d.kcap);
     int jl[MM];
 #pragma unroll
     for (int m = 0; m < M; ++m) jl[m] = (active && m < d.kcap) ? d.jl[(size_t)m * N + atom] : 0;
     const int c = L.c0 + blockIdx.y;
     S rec[kNParam];
-    decode_record<S, Full>(A.x + (size_t)NX * c, rec);
+    decode_record<S, Full>(A.x + Form<Full>::nx * (size_t)c, rec);
     const S* a = abuf + (size_t)blockIdx.y * 3 * Ns;
     const S ax = active ? a[la] : S(0), ay = active ? a[Ns + la] : S(0), az = active ? a[2 * Ns + la] : S(0);
-    S phi[NX];
-    // lanes past the structure have zero geometry: phi = 0
-    adjoint_phi<S, M, Full>(
-        g, rec, A.x + (size_t)NX * c, ax, ay, az,
+    S sums[NL];
+    // lanes past the structure have zero geometry: every sum is zero
+    adjoint_sums<S, M, Full>(
+        g, rec, ax, ay, az,
         [&](int m) {
             int jm = jl[m];
             asm volatile("" : "+v"(jm));
             return Vec4<S>{a[jm], a[Ns + jm], a[2 * Ns + jm], S(0)};
         },
-        A.coef + ((size_t)c * d.S + L.s) * 8, phi);
+        A.coef + ((size_t)c * d.S + L.s) * 8, sums);
     double v[8];
 #pragma unroll
-    for (int k = 0; k < 8; ++k) v[k] = k < NX ? (double)phi[k < NX ? k : 0] : 0.0;
+    for (int k = 0; k < 8; ++k) v[k] = k < NL ? (double)sums[k < NL ? k : 0] : 0.0;
     sum = group_reduce8(v, 64, &vidx);
     if constexpr (Full) {
         double u[8];
-        u[0] = (double)phi[8];
+        u[0] = (double)sums[8];
 #pragma unroll
         for (int k = 1; k < 8; ++k) u[k] = 0.0;
         sum2 = group_reduce8(u, 64, &vidx2);
@@ -911,15 +1126,13 @@ __global__ __launch_bounds__(256) void k_large_adjoint(BArgs<S> A, LArgs L, cons
         if constexpr (MC <= 4) {
             dispatch_m<0, MC>(Mw, run);
         } else {
-            // two variants only: the dual passes of a wide variant take minutes to
-            // compile, and rows past the wave's coordination are padding bonds
+            // two variants: rows past the wave's coordination are padding bonds
             if (Mw <= 8) run(std::integral_constant<int, 8>{});
             else run(std::integral_constant<int, MC>{});
         }
     }
-    constexpr int NX = Form<Full>::nx;
     const int c = L.c0 + blockIdx.y;
-    large_store(d, L, A.partial, A.nv, c, la, Mw >= 0, sum, vidx, (1u << (NX < 8 ? NX : 8)) - 1, 0, sh);
+    large_store(d, L, A.partial, A.nv, c, la, Mw >= 0, sum, vidx, Full ? 0xffu : 0x7fu, 0, sh);
     if constexpr (Full) large_store(d, L, A.partial, A.nv, c, la, Mw >= 0, sum2, vidx2, 0x01, 8, sh);
 }
 
@@ -972,12 +1185,12 @@ hipError_t launch_large64(int mc, int mode, int full, dim3 g, dim3 b, hipStream_
                           const BArgs<double>& A, const LArgs& L);
 // Two-pass fitness gradient of one structure and candidate chunk: force
 // residuals into abuf from the bond gradients staged by launch_large* in
-// MODE_STAGE, then the dual passes.
+// MODE_STAGE, then the grad sums.
 hipError_t launch_large_adj32(int mc, int full, dim3 g, dim3 b, hipStream_t st, const BArgs<float>& Afit,
                               const BArgs<float>& Aadj, const LArgs& L, float* abuf);
 hipError_t launch_large_adj64(int mc, int full, dim3 g, dim3 b, hipStream_t st, const BArgs<double>& Afit,
                               const BArgs<double>& Aadj, const LArgs& L, double* abuf);
-// The Tersoff form's residual and dual-pass kernels of the two-pass gradient.
+// The Tersoff form's residual and grad-sum kernels of the two-pass gradient.
 hipError_t launch_large_adj32f(int mc, dim3 g, dim3 b, hipStream_t st, const BArgs<float>& A,
                                const LArgs& L, float* abuf);
 hipError_t launch_large_adj64f(int mc, dim3 g, dim3 b, hipStream_t st, const BArgs<double>& A,

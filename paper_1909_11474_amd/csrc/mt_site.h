@@ -26,8 +26,7 @@
 // and takes f_R, f_A with their own exponents lambda = alpha sqrt(2S),
 // mu = alpha sqrt(2/S); then D_j = 1/2 [f_C' (f_R - b f_A) + f_C (mu b f_A - lambda f_R)].
 //
-// V is the value type (float, double, or Dual<> for parameter derivatives);
-// S is the geometry type.  The code is written once for all of them.
+// S is the arithmetic type (float or double); the code is written once for both.
 #pragma once
 
 #include <type_traits>
@@ -36,14 +35,49 @@
 
 namespace mt {
 
-template <typename S, int M>
+// Largest coordination whose angular sums run over bond pairs in the minimal
+// form; above it they come from moments (see Geo::angular_moments).
+constexpr int kPairMax = 6;
+
+template <typename S, int M, bool Full = false>
 struct Geo {
     static constexpr int NP = M * (M - 1) / 2;
     static constexpr bool kCache = NP <= 15;       // keep cos(theta) in registers for M <= 6
+    static constexpr bool kMoments = !Full && M > kPairMax;
     S ux[M > 0 ? M : 1], uy[M > 0 ? M : 1], uz[M > 0 ? M : 1];
     S rhi[M > 0 ? M : 1], rlo[M > 0 ? M : 1], rinv[M > 0 ? M : 1];
     S fc[M > 0 ? M : 1], hfcp[M > 0 ? M : 1];     // f_C and f_C'/2
     S cs[kCache && NP > 0 ? NP : 1];
+    S ss[kMoments ? M : 1], sh[kMoments ? M : 1], sv[kMoments ? M : 1];
+
+    // The minimal form's angular function is (cos - h)^2, so bond j's sum over
+    // the other bonds is a quadratic in h that no parameter enters:
+    //   sum_k f_C (cos_jk - h)^2 = V + S (H - h)^2,
+    // S = sum f_C, H = sum f_C cos / S, V = sum f_C (cos - H)^2.  Formed once per
+    // atom, not per candidate; every term is positive, so nothing cancels.
+    __device__ __forceinline__ void angular_moments() {
+        if constexpr (kMoments) {
+#pragma unroll
+            for (int j = 0; j < M; ++j) {
+                S f = S(0), c1 = S(0), v = S(0);
+#pragma unroll
+                for (int k = 0; k < M; ++k) {
+                    if (k == j) continue;
+                    f += fc[k];
+                    c1 += fc[k] * (ux[j] * ux[k] + uy[j] * uy[k] + uz[j] * uz[k]);
+                }
+                const S h = f > S(0) ? c1 / f : S(0);
+#pragma unroll
+                for (int k = 0; k < M; ++k) {
+                    if (k == j) continue;
+                    const S t = (ux[j] * ux[k] + uy[j] * uy[k] + uz[j] * uz[k]) - h;
+                    v += (fc[k] * t) * t;
+                }
+                ss[j] = f; sh[j] = h; sv[j] = v;
+                __builtin_amdgcn_sched_barrier(0);
+            }
+        }
+    }
 
     __device__ __forceinline__ S cosjk(int j, int k, int pidx) const {
         if constexpr (kCache && NP > 0) {
@@ -86,6 +120,7 @@ struct Geo {
                     }
                 }
                 cache_cos();
+                angular_moments();
                 return;
             }
         }
@@ -103,6 +138,7 @@ struct Geo {
             hfcp[m] = ok ? G.hfcp[o] : S(0);
         }
         cache_cos();
+        angular_moments();
     }
 
     __device__ __forceinline__ void cache_cos() {
@@ -119,27 +155,27 @@ struct Geo {
 // Decoded parameters of one candidate.  Full selects the Tersoff angular
 // function g^T and independent pair exponents (the nine-parameter form); the
 // minimal potential has g = (cos - h)^2 and lambda = 2 mu.
-template <typename V, typename S, bool Full = false>
+template <typename S, bool Full = false>
 struct Cand {
     static constexpr bool kFull = Full;
-    V aA, aR, r0hi, r0lo, DR, DA, hmu, hlambda, zs, ccs, n, ninv2n, h;
-    V gam, K, d2, Kd2;               // g^T = gam + K t^2 / (d2 + t^2)
+    S aA, aR, r0hi, r0lo, DR, DA, hmu, hlambda, zs, ccs, n, ninv2n, h;
+    S gam, K, d2, Kd2;               // g^T = gam + K t^2 / (d2 + t^2)
     S valid;
     S aAlo, aRlo, DRlo, DAlo, nlo, ninv2nlo;   // low parts for the float64 energy terms
     S hlo;                                      // h - float(h): zeta of the float path
 };
 
 // Type of the site energy: float64 for the float path (its energy terms are
-// evaluated in float64), the value type otherwise.
-template <typename V>
-struct EnergyOf { using type = V; };
+// evaluated in float64), the arithmetic type otherwise.
+template <typename S>
+struct EnergyOf { using type = S; };
 template <>
 struct EnergyOf<float> { using type = double; };
 
 // The minimal record leaves the Tersoff-form slots unwritten; its candidate
 // takes lambda = 2 mu and does not read them.
 template <typename S, bool Full>
-__device__ __forceinline__ void load_cand(const S* __restrict__ p, Cand<S, S, Full>& c) {
+__device__ __forceinline__ void load_cand(const S* __restrict__ p, Cand<S, Full>& c) {
     c.aA = p[P_AA]; c.r0hi = p[P_R0HI]; c.r0lo = p[P_R0LO];
     c.DR = p[P_DR]; c.DA = p[P_DA]; c.hmu = p[P_HMU];
     c.zs = p[P_ZS]; c.ccs = p[P_CCS]; c.n = p[P_N]; c.ninv2n = p[P_NINV2N]; c.h = p[P_H];
@@ -155,116 +191,21 @@ __device__ __forceinline__ void load_cand(const S* __restrict__ p, Cand<S, S, Fu
     }
 }
 
-// Seeds K parameter directions, parameters Base .. Base + K - 1 of the
-// minimal potential's (D0, alpha, r0, beta, n, h).
-template <int Base, typename S, int K>
-__device__ __forceinline__ void load_cand(const S* __restrict__ p, Cand<Dual<S, K>, S, false>& c) {
-    const S log2e = S(1.4426950408889634);
-    c.aA = dconst<S, K>(p[P_AA]);
-    c.aR = dconst<S, K>(S(2) * p[P_AA]);
-    c.r0hi = dconst<S, K>(p[P_R0HI]);
-    c.r0lo = dconst<S, K>(p[P_R0LO]);
-    c.DR = dconst<S, K>(p[P_DR]);
-    c.DA = dconst<S, K>(p[P_DA]);
-    c.hmu = dconst<S, K>(p[P_HMU]);
-    c.hlambda = dconst<S, K>(S(2) * p[P_HMU]);
-    c.zs = dconst<S, K>(p[P_ZS]);
-    c.ccs = dconst<S, K>(p[P_CCS]);
-    c.n = dconst<S, K>(p[P_N]);
-    c.ninv2n = dconst<S, K>(p[P_NINV2N]);
-    c.h = dconst<S, K>(p[P_H]);
-#pragma unroll
-    for (int t = 0; t < K; ++t) {
-        switch (Base + t) {
-            // S = 2: DR = D0, DA = 2 D0, mu = alpha, lambda = 2 alpha
-            case 0: c.DR.d[t] = S(1); c.DA.d[t] = S(2); break;
-            case 1:
-                c.aA.d[t] = log2e; c.hmu.d[t] = S(0.5);
-                c.aR.d[t] = S(2) * log2e; c.hlambda.d[t] = S(1);
-                break;
-            case 2: c.r0hi.d[t] = S(1); break;
-            case 3: c.zs.d[t] = S(1); c.ccs.d[t] = S(0.5); break;
-            // d/dn (-1/(2n)) = 1/(2n^2)
-            case 4: c.n.d[t] = S(1); c.ninv2n.d[t] = S(2) * p[P_NINV2N] * p[P_NINV2N]; break;
-            case 5: c.h.d[t] = S(1); break;
-        }
-    }
-    c.valid = p[P_VALID];
-    c.hlo = S(0);
-}
-
-// Seeds K parameter directions, parameters Base .. Base + K - 1 of the
-// Tersoff form's (D0, alpha, r0, S, gamma, n, c, d, h): values from the record
-// p, tangents of the record's fields from the candidate's x (float64):
-//   DR = D0/(S-1), DA = S D0/(S-1), mu = alpha sqrt(2/S), lambda = alpha sqrt(2S),
-//   K = gamma c^2/d^2, d^2, K d^2 = gamma c^2, -1/(2n).
-template <int Base, typename S, int K>
-__device__ __forceinline__ void load_cand(const S* __restrict__ p, const double* __restrict__ x,
-                                          Cand<Dual<S, K>, S, true>& c) {
-    const double log2e = 1.4426950408889634;
-    c.aA = dconst<S, K>(p[P_AA]);
-    c.aR = dconst<S, K>(p[P_AR]);
-    c.r0hi = dconst<S, K>(p[P_R0HI]);
-    c.r0lo = dconst<S, K>(p[P_R0LO]);
-    c.DR = dconst<S, K>(p[P_DR]);
-    c.DA = dconst<S, K>(p[P_DA]);
-    c.hmu = dconst<S, K>(p[P_HMU]);
-    c.hlambda = dconst<S, K>(p[P_HLAMBDA]);
-    c.zs = dconst<S, K>(p[P_ZS]);
-    c.ccs = dconst<S, K>(p[P_CCS]);
-    c.n = dconst<S, K>(p[P_N]);
-    c.ninv2n = dconst<S, K>(p[P_NINV2N]);
-    c.h = dconst<S, K>(p[P_H]);
-    c.gam = dconst<S, K>(p[P_GAM]);
-    c.K = dconst<S, K>(p[P_K]);
-    c.d2 = dconst<S, K>(p[P_D2]);
-    c.Kd2 = dconst<S, K>(p[P_KD2]);
-    const double D0 = x[0], al = x[1], Sl = x[3], gam = x[4], n = x[5], cc = x[6], d = x[7];
-    const double rs = sqrt(2.0 / Sl), rl = sqrt(2.0 * Sl), sm1 = Sl - 1.0;
-#pragma unroll
-    for (int t = 0; t < K; ++t) {
-        switch (Base + t) {
-            case 0: c.DR.d[t] = (S)(1.0 / sm1); c.DA.d[t] = (S)(Sl / sm1); break;
-            case 1:
-                c.aA.d[t] = (S)(rs * log2e); c.aR.d[t] = (S)(rl * log2e);
-                c.hmu.d[t] = (S)(0.5 * rs); c.hlambda.d[t] = (S)(0.5 * rl);
-                break;
-            case 2: c.r0hi.d[t] = S(1); break;
-            case 3: {
-                // d sqrt(2/S)/dS = -sqrt(2/S)/(2S), d sqrt(2S)/dS = sqrt(2S)/(2S)
-                const double dD = -D0 / (sm1 * sm1), ts = 0.5 / Sl;
-                c.DR.d[t] = (S)dD; c.DA.d[t] = (S)dD;
-                c.aA.d[t] = (S)(-al * rs * log2e * ts); c.aR.d[t] = (S)(al * rl * log2e * ts);
-                c.hmu.d[t] = (S)(-0.5 * al * rs * ts); c.hlambda.d[t] = (S)(0.5 * al * rl * ts);
-                break;
-            }
-            case 4: c.gam.d[t] = S(1); c.K.d[t] = (S)(cc * cc / (d * d)); c.Kd2.d[t] = (S)(cc * cc); break;
-            // d/dn (-1/(2n)) = 1/(2n^2)
-            case 5: c.n.d[t] = S(1); c.ninv2n.d[t] = (S)(0.5 / (n * n)); break;
-            case 6: c.K.d[t] = (S)(2.0 * gam * cc / (d * d)); c.Kd2.d[t] = (S)(2.0 * gam * cc); break;
-            case 7: c.K.d[t] = (S)(-2.0 * gam * cc * cc / (d * d * d)); c.d2.d[t] = (S)(2.0 * d); break;
-            case 8: c.h.d[t] = S(1); break;
-        }
-    }
-    c.valid = p[P_VALID];
-    c.hlo = S(0);
-}
-
 // Angular function and half its derivative for t = cos(theta) - h:
 // minimal g = t^2, g'/2 = t; Tersoff g^T = gam + K t^2 / (d^2 + t^2),
 // g'/2 = K d^2 t / (d^2 + t^2)^2 (Sec. II.A Eq. 8, written without the
 // cancellation of 1 + c^2/d^2 - c^2/(d^2 + t^2)).
-template <bool Full, typename V, typename P>
-__device__ __forceinline__ V ang_g(const P& p, const V& t) {
-    const V t2 = t * t;
+template <bool Full, typename S, typename P>
+__device__ __forceinline__ S ang_g(const P& p, S t) {
+    const S t2 = t * t;
     if constexpr (Full) return p.gam + (p.K * t2) * drcp(p.d2 + t2);
     else return t2;
 }
-template <bool Full, typename V, typename P>
-__device__ __forceinline__ void ang_g_dg(const P& p, const V& t, V& gv, V& hg) {
-    const V t2 = t * t;
+template <bool Full, typename S, typename P>
+__device__ __forceinline__ void ang_g_dg(const P& p, S t, S& gv, S& hg) {
+    const S t2 = t * t;
     if constexpr (Full) {
-        const V r = drcp(p.d2 + t2);
+        const S r = drcp(p.d2 + t2);
         gv = p.gam + (p.K * t2) * r;
         hg = ((p.Kd2 * t) * r) * r;
     } else {
@@ -285,28 +226,18 @@ __device__ __forceinline__ void opaque(S (&a)[N]) {
 constexpr int kPairwiseMax = 8;
 
 // The site routine.  It hands each bond gradient G_j to sink(j, Gx, Gy, Gz);
-// PerBond selects the one-bond-at-a-time backward sweep (for large M, or for
-// dual numbers, whose per-bond state is K + 1 times larger), which emits G_j
-// as soon as it is complete.
-// Fresh: treat the geometry as new, so that nothing computed from it by an
-// earlier call in the same loop iteration is kept alive for reuse (repeated
-// dual passes over the same site would otherwise hold every shared primal
-// value across passes).  The barriers act on the caller's geometry in place
-// (they change no value), so no second copy of it becomes live.
+// PerBond selects the one-bond-at-a-time backward sweep (for large M), which
+// emits G_j as soon as it is complete.
 // SerialE64: keep the float64 energy chains of the bonds one after another
 // (fewer live registers; a kernel with other wavefronts to switch to loses
 // nothing), or let them interleave (a kernel that runs about one wavefront per
 // SIMD needs the instruction-level parallelism).
-template <typename V, typename S, int M, bool Energy64, bool PerBond, bool Fresh = false,
-          bool Full = false, bool SerialE64 = true, typename Sink>
-__device__ __forceinline__ void site_eval_sink(Geo<S, M>& g, const Cand<V, S, Full>& p,
-                                               typename EnergyOf<V>::type& U, Sink&& sink) {
+template <typename S, int M, bool Energy64, bool PerBond, bool Full = false, bool SerialE64 = true,
+          typename Sink>
+__device__ __forceinline__ void site_eval_sink(Geo<S, M, Full>& g, const Cand<S, Full>& p,
+                                               typename EnergyOf<S>::type& U, Sink&& sink) {
     constexpr int MM = M > 0 ? M : 1;
-    if constexpr (Fresh && M > 0) {
-        opaque(g.rhi); opaque(g.rlo); opaque(g.rinv); opaque(g.fc); opaque(g.hfcp);
-        if constexpr (Geo<S, M>::kCache && Geo<S, M>::NP > 0) opaque(g.cs);
-    }
-    if constexpr ((Fresh || !Geo<S, M>::kCache) && M > 1) {
+    if constexpr (!Geo<S, M, Full>::kCache && M > 1) {
         // cos(theta) is not cached for larger M: keep the compiler from
         // hoisting the M (M - 1) / 2 values out of the candidate loop (they
         // would not fit in registers and go to scratch)
@@ -318,10 +249,10 @@ __device__ __forceinline__ void site_eval_sink(Geo<S, M>& g, const Cand<V, S, Fu
     // are evaluated with float64 exponentials (below), and zeta takes h as a
     // float hi/lo pair, so that a float rounding of h does not shift every
     // (cos - h)^2 of a candidate the same way.
-    constexpr bool kE64 = Energy64 && std::is_same<V, float>::value;
-    V zeta[MM];
+    constexpr bool kE64 = Energy64 && std::is_same<S, float>::value;
+    S zeta[MM];
 #pragma unroll
-    for (int j = 0; j < M; ++j) zeta[j] = vconst<V, S>(S(0));
+    for (int j = 0; j < M; ++j) zeta[j] = S(0);
     {
         int pidx = 0;
 #pragma unroll
@@ -329,10 +260,10 @@ __device__ __forceinline__ void site_eval_sink(Geo<S, M>& g, const Cand<V, S, Fu
 #pragma unroll
             for (int k = j + 1; k < M; ++k) {
                 const S c = g.cosjk(j, k, pidx++);
-                V t;
+                S t;
                 if constexpr (kE64) t = (c - p.h) - p.hlo;
                 else t = c - p.h;
-                const V gv = ang_g<Full>(p, t);
+                const S gv = ang_g<Full>(p, t);
                 zeta[j] = zeta[j] + g.fc[k] * gv;
                 zeta[k] = zeta[k] + g.fc[j] * gv;
             }
@@ -346,18 +277,18 @@ __device__ __forceinline__ void site_eval_sink(Geo<S, M>& g, const Cand<V, S, Fu
     // 1 + zeta^n, whose error enters b damped by zeta^n / (1 + zeta^n) / 2n),
     // and the pair energy is formed in float64.  Their float32 roundings feed
     // the gradient.
-    V cc[MM], D[MM];
-    V usum = vconst<V, S>(S(0));
+    S cc[MM], D[MM];
+    S usum = S(0);
     double usum64 = 0.0;
 #pragma unroll
     for (int j = 0; j < M; ++j) {
-        const V z = zeta[j] * p.zs;
+        const S z = zeta[j] * p.zs;
         // zeta = 0 (no other neighbour inside the cutoff, or all at g = 0):
         // zeta^n = 0 exactly, so b = 1 and db/dzeta * zeta^n-terms vanish
-        const bool pos = val(z) > S(0);
-        const V zsafe = dselect(pos, z, vconst<V, S>(S(1)));
-        V eA, zn, b;
-        [[maybe_unused]] V eR;
+        const bool pos = z > S(0);
+        const S zsafe = pos ? z : S(1);
+        S eA, zn, b;
+        [[maybe_unused]] S eR;
         if constexpr (kE64) {
             // float64 copies of the bond's geometry are made here, per candidate:
             // hoisted out of the candidate loop they would hold 6 M registers
@@ -382,19 +313,19 @@ __device__ __forceinline__ void site_eval_sink(Geo<S, M>& g, const Cand<V, S, Fu
             zn = zn32;
             b = (float)b64;
         } else {
-            const V delta = (g.rhi[j] - p.r0hi) + (g.rlo[j] - p.r0lo);
+            const S delta = (g.rhi[j] - p.r0hi) + (g.rlo[j] - p.r0lo);
             eA = dexp2(-(p.aA * delta));
             if constexpr (Full) eR = dexp2(-(p.aR * delta));
-            zn = dselect(pos, dexp2(p.n * dlog2(zsafe)), vconst<V, S>(S(0)));
+            zn = pos ? dexp2(p.n * dlog2(zsafe)) : S(0);
             b = dexp2(p.ninv2n * dlog2(S(1) + zn));
         }
-        const V onep = S(1) + zn;
-        V fR;
+        const S onep = S(1) + zn;
+        S fR;
         if constexpr (Full) fR = p.DR * eR;
         else fR = p.DR * (eA * eA);               // e_R = e_A^2
-        const V fA = p.DA * eA;
-        const V diff = fR - b * fA;           // one rounding (fused multiply-add)
-        const V bfA = b * fA;
+        const S fA = p.DA * eA;
+        const S diff = fR - b * fA;           // one rounding (fused multiply-add)
+        const S bfA = b * fA;
         if constexpr (!kE64) usum = usum + g.fc[j] * diff;
         // D = 1/2 [f_C' (f_R - b f_A) + f_C (mu b f_A - lambda f_R)]
         if constexpr (Full) D[j] = g.hfcp[j] * diff + g.fc[j] * (p.hmu * bfA - p.hlambda * fR);
@@ -418,31 +349,31 @@ __device__ __forceinline__ void site_eval_sink(Geo<S, M>& g, const Cand<V, S, Fu
         opaque(g.uz);
 #pragma unroll
         for (int j = 0; j < M; ++j) {
-            V vx = vconst<V, S>(S(0)), vy = vx, vz = vx, pp = vx;
+            S vx = S(0), vy = vx, vz = vx, pp = vx;
 #pragma unroll
             for (int k = 0; k < M; ++k) {
                 if (k == j) continue;
                 const S c = g.ux[j] * g.ux[k] + g.uy[j] * g.uy[k] + g.uz[j] * g.uz[k];
-                const V t = c - p.h;
-                V gv, hg;
+                const S t = c - p.h;
+                S gv, hg;
                 ang_g_dg<Full>(p, t, gv, hg);
-                const V q = (cc[j] * g.fc[k] + cc[k] * g.fc[j]) * hg;
+                const S q = (cc[j] * g.fc[k] + cc[k] * g.fc[j]) * hg;
                 vx = vx + q * g.ux[k]; vy = vy + q * g.uy[k]; vz = vz + q * g.uz[k];
                 if constexpr (Full) pp = pp + cc[k] * gv;
                 else pp = pp + (cc[k] * t) * t;
             }
-            const V uv = g.ux[j] * vx + g.uy[j] * vy + g.uz[j] * vz;
-            const V rad = D[j] + g.hfcp[j] * pp - uv * g.rinv[j];
+            const S uv = g.ux[j] * vx + g.uy[j] * vy + g.uz[j] * vz;
+            const S rad = D[j] + g.hfcp[j] * pp - uv * g.rinv[j];
             sink(j, rad * g.ux[j] + vx * g.rinv[j], rad * g.uy[j] + vy * g.rinv[j],
                  rad * g.uz[j] + vz * g.rinv[j]);
             __builtin_amdgcn_sched_barrier(0);
         }
         return;
     }
-    V Vx[MM], Vy[MM], Vz[MM], Pp[MM];
+    S Vx[MM], Vy[MM], Vz[MM], Pp[MM];
 #pragma unroll
     for (int j = 0; j < M; ++j) {
-        Vx[j] = Vy[j] = Vz[j] = Pp[j] = vconst<V, S>(S(0));
+        Vx[j] = Vy[j] = Vz[j] = Pp[j] = S(0);
     }
     {
         int pidx = 0;
@@ -451,10 +382,10 @@ __device__ __forceinline__ void site_eval_sink(Geo<S, M>& g, const Cand<V, S, Fu
 #pragma unroll
             for (int k = j + 1; k < M; ++k) {
                 const S c = g.cosjk(j, k, pidx++);
-                const V t = c - p.h;
-                V gv, hg;
+                const S t = c - p.h;
+                S gv, hg;
                 ang_g_dg<Full>(p, t, gv, hg);
-                const V q = (cc[j] * g.fc[k] + cc[k] * g.fc[j]) * hg;
+                const S q = (cc[j] * g.fc[k] + cc[k] * g.fc[j]) * hg;
                 Vx[j] = Vx[j] + q * g.ux[k]; Vy[j] = Vy[j] + q * g.uy[k]; Vz[j] = Vz[j] + q * g.uz[k];
                 Vx[k] = Vx[k] + q * g.ux[j]; Vy[k] = Vy[k] + q * g.uy[j]; Vz[k] = Vz[k] + q * g.uz[j];
                 Pp[j] = Pp[j] + cc[k] * gv;
@@ -465,21 +396,21 @@ __device__ __forceinline__ void site_eval_sink(Geo<S, M>& g, const Cand<V, S, Fu
     // sum_k q_jk cos_jk = u_j . V_j, so the radial part needs no per-pair term
 #pragma unroll
     for (int j = 0; j < M; ++j) {
-        const V uv = g.ux[j] * Vx[j] + g.uy[j] * Vy[j] + g.uz[j] * Vz[j];
-        const V rad = D[j] + g.hfcp[j] * Pp[j] - uv * g.rinv[j];
+        const S uv = g.ux[j] * Vx[j] + g.uy[j] * Vy[j] + g.uz[j] * Vz[j];
+        const S rad = D[j] + g.hfcp[j] * Pp[j] - uv * g.rinv[j];
         sink(j, rad * g.ux[j] + Vx[j] * g.rinv[j], rad * g.uy[j] + Vy[j] * g.rinv[j],
              rad * g.uz[j] + Vz[j] * g.rinv[j]);
     }
 }
 
 // The site routine with the bond gradients returned in arrays.
-template <typename V, typename S, int M, bool Energy64 = false, bool Full = false, bool SerialE64 = true>
-__device__ __forceinline__ void site_eval(Geo<S, M>& g, const Cand<V, S, Full>& p,
-                                          typename EnergyOf<V>::type& U,
-                                          V* __restrict__ Gx, V* __restrict__ Gy,
-                                          V* __restrict__ Gz) {
-    site_eval_sink<V, S, M, Energy64, (M > kPairwiseMax), false, Full, SerialE64>(
-        g, p, U, [&](int j, const V& x, const V& y, const V& z) {
+template <typename S, int M, bool Energy64 = false, bool Full = false, bool SerialE64 = true>
+__device__ __forceinline__ void site_eval(Geo<S, M, Full>& g, const Cand<S, Full>& p,
+                                          typename EnergyOf<S>::type& U,
+                                          S* __restrict__ Gx, S* __restrict__ Gy,
+                                          S* __restrict__ Gz) {
+    site_eval_sink<S, M, Energy64, (M > kPairwiseMax), Full, SerialE64>(
+        g, p, U, [&](int j, S x, S y, S z) {
             Gx[j] = x;
             Gy[j] = y;
             Gz[j] = z;
