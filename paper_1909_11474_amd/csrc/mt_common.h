@@ -118,8 +118,17 @@ struct SetDev {
     // [15][N] cos(theta_jk) of the bond pairs j < k < 6, pair k (k - 1) / 2 + j:
     // float64 unit-vector products rounded once (zero for padding bonds)
     const float* gcs;
+    // angular moments (S, H, V) of every bond over the atom's other bonds, for
+    // sets with more than kPairMax neighbours somewhere (null otherwise):
+    // [kcap][N] float4 (fourth unused)
+    const float4* gam;
     const float* fref32;  const double* fref64; // [3][N] sorted order
 };
+
+// Largest coordination whose angular sums run over bond pairs in the float
+// minimal form; above it they come from moments.  About 52 operations a bond by moments
+// against 13 a pair (20 uncached, M > 6): equal between 6 and 7 neighbours.
+constexpr int kPairMax = 6;
 
 // Pairs of bonds whose cos(theta) the pair table holds (bonds 0-5).
 constexpr int kCosPairs = 15;

@@ -348,6 +348,42 @@ __global__ void k_pair_cos(int N, int kcap, const double* __restrict__ gd, float
             gcs[(size_t)(k * (k - 1) / 2 + j) * N + a] = (float)(vx[j] * vx[k] + vy[j] * vy[k] + vz[j] * vz[k]);
 }
 
+// Angular moments of every bond over the atom's other bonds (float64 sums):
+//   S = sum f_C, H = sum f_C cos / S, V = sum f_C (cos - H)^2,
+// zero for padding bonds and where no other bond is inside the cutoff (then
+// zeta is exactly zero).  One thread per bond; V in a second pass, so it does
+// not come from a difference of sums.
+__global__ void k_ang_moments(int N, int kcap, const int* __restrict__ nnb, const double* __restrict__ gd,
+                              float4* __restrict__ gam) {
+    const int idx = blockIdx.x * blockDim.x + threadIdx.x;
+    if (idx >= N * kcap) return;
+    const int a = idx % N, j = idx / N;
+    const size_t KN = (size_t)kcap * N;
+    const int M = nnb[a];
+    double s = 0.0, h = 0.0, v = 0.0;
+    if (j < M) {
+        const double ux = gd[idx], uy = gd[KN + idx], uz = gd[2 * KN + idx];
+        double c1 = 0.0;
+        for (int k = 0; k < M; ++k) {
+            if (k == j) continue;
+            const size_t o = (size_t)k * N + a;
+            const double f = gd[5 * KN + o];
+            s += f;
+            c1 += f * (ux * gd[o] + uy * gd[KN + o] + uz * gd[2 * KN + o]);
+        }
+        if (s > 0.0) {
+            h = c1 / s;
+            for (int k = 0; k < M; ++k) {
+                if (k == j) continue;
+                const size_t o = (size_t)k * N + a;
+                const double t = (ux * gd[o] + uy * gd[KN + o] + uz * gd[2 * KN + o]) - h;
+                v += gd[5 * KN + o] * t * t;
+            }
+        }
+    }
+    gam[idx] = make_float4((float)s, (float)h, (float)v, 0.f);
+}
+
 // Bond geometry for every (sorted atom, slot).  Padded slots (m >= coordination)
 // get f_C = f_C' = 0 and a zero unit vector, so they add nothing anywhere.
 __global__ void k_geometry(int N, int S, int kcap, double R1, double R2,
@@ -498,6 +534,20 @@ int grid_of(long long n, int block) { return (int)((n + block - 1) / block); }
         hipError_t _e = (call);                          \
         if (_e != hipSuccess) return hip_fail(_e, #call); \
     } while (0)
+
+// The tables of angles that follow the bond geometry: pair cosines, and the
+// angular moments of sets with more than kPairMax neighbours somewhere.
+static int launch_angle_tables(mt_set* set, hipStream_t st) {
+    const int N = set->N, kcap = set->kcap;
+    k_pair_cos<<<grid_of(N, 256), 256, 0, st>>>(N, kcap, set->gd.as<double>(), set->gcs.as<float>());
+    HIPCHECK(hipGetLastError());
+    if (set->kmax > kPairMax) {
+        k_ang_moments<<<grid_of((long long)kcap * N, 256), 256, 0, st>>>(
+            N, kcap, set->nnb.as<int>(), set->gd.as<double>(), set->gam.as<float4>());
+        HIPCHECK(hipGetLastError());
+    }
+    return MT_OK;
+}
 
 int build_set(mt_set* set, const int64_t* atom_offset, const double* pos, const double* cell,
               hipStream_t st) {
@@ -665,6 +715,7 @@ int build_set(mt_set* set, const int64_t* atom_offset, const double* pos, const 
     HIPCHECK(set->gpk.reserve(sizeof(float4) * 2 * KN));
     HIPCHECK(set->gd.reserve(sizeof(double) * 7 * KN));
     HIPCHECK(set->gcs.reserve(sizeof(float) * kCosPairs * (size_t)N));
+    if (set->kmax > kPairMax) HIPCHECK(set->gam.reserve(sizeof(float4) * KN));
     HIPCHECK(set->rev.reserve(sizeof(int) * KN));
     HIPCHECK(set->revc.reserve(sizeof(int) * KN));
     HIPCHECK(set->jl.reserve(sizeof(int) * KN));
@@ -679,8 +730,8 @@ int build_set(mt_set* set, const int64_t* atom_offset, const double* pos, const 
         set->gd.as<double>(), set->rev.as<int>(), set->revc.as<int>(), set->jl.as<int>(), set->nbr_j.as<int>(),
         set->nbr_sh.as<int>(), flags.as<int>());
     HIPCHECK(hipGetLastError());
-    k_pair_cos<<<grid_of(N, 256), 256, 0, st>>>(N, kcap, set->gd.as<double>(), set->gcs.as<float>());
-    HIPCHECK(hipGetLastError());
+    const int rc = launch_angle_tables(set, st);
+    if (rc != MT_OK) return rc;
     HIPCHECK(hipMemcpyAsync(&hflags, flags.p, sizeof(int), hipMemcpyDeviceToHost, st));
     HIPCHECK(hipStreamSynchronize(st));
     if (hflags & 8) {
@@ -704,8 +755,8 @@ int update_geometry(mt_set* set, const double* pos, hipStream_t st) {
         set->gd.as<double>(), set->rev.as<int>(), set->revc.as<int>(), set->jl.as<int>(), set->nbr_j.as<int>(),
         set->nbr_sh.as<int>(), B.flags.as<int>());
     HIPCHECK(hipGetLastError());
-    k_pair_cos<<<grid_of(N, 256), 256, 0, st>>>(N, kcap, set->gd.as<double>(), set->gcs.as<float>());
-    HIPCHECK(hipGetLastError());
+    const int rc = launch_angle_tables(set, st);
+    if (rc != MT_OK) return rc;
     return MT_OK;
 }
 

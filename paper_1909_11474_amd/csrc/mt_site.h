@@ -19,7 +19,8 @@
 //   D_j = 1/2 [ f_C'_j (f_R - b f_A) + f_C,j alpha (b f_A - 2 f_R) ]
 // (the radial term uses sum_k q_jk cos_jk = r^_j . V_j).  Every unordered bond
 // pair (j, k) is visited once in each of the forward (zeta) and backward
-// (gradient) sweeps.
+// (gradient) sweeps; the float minimal potential above kPairMax neighbours takes
+// both from moments over the bonds instead.
 //
 // The Tersoff form (Sec. II.A Eqs. 2-8 with Eqs. 11-14 for general S) replaces
 // beta (cos - h)^2 by g^T(theta), t^2 by g^T in the P sums, t by g^T'/2 in q_jk,
@@ -35,46 +36,39 @@
 
 namespace mt {
 
-// Largest coordination whose angular sums run over bond pairs in the minimal
-// form; above it they come from moments (see Geo::angular_moments).
-constexpr int kPairMax = 6;
-
 template <typename S, int M, bool Full = false>
 struct Geo {
     static constexpr int NP = M * (M - 1) / 2;
     static constexpr bool kCache = NP <= 15;       // keep cos(theta) in registers for M <= 6
-    static constexpr bool kMoments = !Full && M > kPairMax;
+    static constexpr bool kMoments = !Full && sizeof(S) == 4 && M > kPairMax;
     S ux[M > 0 ? M : 1], uy[M > 0 ? M : 1], uz[M > 0 ? M : 1];
     S rhi[M > 0 ? M : 1], rlo[M > 0 ? M : 1], rinv[M > 0 ? M : 1];
     S fc[M > 0 ? M : 1], hfcp[M > 0 ? M : 1];     // f_C and f_C'/2
     S cs[kCache && NP > 0 ? NP : 1];
-    S ss[kMoments ? M : 1], sh[kMoments ? M : 1], sv[kMoments ? M : 1];
-
     // The minimal form's angular function is (cos - h)^2, so bond j's sum over
     // the other bonds is a quadratic in h that no parameter enters:
     //   sum_k f_C (cos_jk - h)^2 = V + S (H - h)^2,
-    // S = sum f_C, H = sum f_C cos / S, V = sum f_C (cos - H)^2.  Formed once per
-    // atom, not per candidate; every term is positive, so nothing cancels.
-    __device__ __forceinline__ void angular_moments() {
+    // S = sum f_C, H = sum f_C cos / S, V = sum f_C (cos - H)^2, from the set's
+    // table (float64 sums rounded once).  Both terms are positive, so nothing
+    // cancels.
+    S ss[kMoments ? M : 1], sh[kMoments ? M : 1], sv[kMoments ? M : 1];
+    // sum f_C u u^T and sum f_C u over the bonds
+    S txx, tyy, tzz, tyz, tzx, txy, mx, my, mz;
+
+    __device__ __forceinline__ void load_moments(const SetDev& d, int atom, bool active, int rows) {
         if constexpr (kMoments) {
 #pragma unroll
-            for (int j = 0; j < M; ++j) {
-                S f = S(0), c1 = S(0), v = S(0);
+            for (int m = 0; m < M; ++m) {
+                const float4 a = active && m < rows ? d.gam[(size_t)m * d.N + atom] : make_float4(0.f, 0.f, 0.f, 0.f);
+                ss[m] = a.x; sh[m] = a.y; sv[m] = a.z;
+            }
+            txx = tyy = tzz = tyz = tzx = txy = mx = my = mz = S(0);
 #pragma unroll
-                for (int k = 0; k < M; ++k) {
-                    if (k == j) continue;
-                    f += fc[k];
-                    c1 += fc[k] * (ux[j] * ux[k] + uy[j] * uy[k] + uz[j] * uz[k]);
-                }
-                const S h = f > S(0) ? c1 / f : S(0);
-#pragma unroll
-                for (int k = 0; k < M; ++k) {
-                    if (k == j) continue;
-                    const S t = (ux[j] * ux[k] + uy[j] * uy[k] + uz[j] * uz[k]) - h;
-                    v += (fc[k] * t) * t;
-                }
-                ss[j] = f; sh[j] = h; sv[j] = v;
-                __builtin_amdgcn_sched_barrier(0);
+            for (int m = 0; m < M; ++m) {
+                const S fx = fc[m] * ux[m], fy = fc[m] * uy[m], fz = fc[m] * uz[m];
+                mx += fx; my += fy; mz += fz;
+                txx += fx * ux[m]; tyy += fy * uy[m]; tzz += fz * uz[m];
+                tyz += fy * uz[m]; tzx += fz * ux[m]; txy += fx * uy[m];
             }
         }
     }
@@ -88,57 +82,51 @@ struct Geo {
         }
     }
 
-    // Gcs (float geometry only): the set's pair table of cos(theta) values,
-    // formed from the float64 unit vectors and rounded once; from float unit
-    // vectors they carry up to ~2e-7 absolute error, which zeta passes on to
-    // the energy through (cos - h)^2.
+    // The cached angle cosines of the float geometry come from the set's pair
+    // table, formed from the float64 unit vectors and rounded once; from float
+    // unit vectors they carry up to ~2e-7 absolute error, which zeta passes on
+    // to the energy through (cos - h)^2.
     // rows: neighbour rows the arrays hold (a variant wider than the set's
     // capacity reads the rows past it as padding bonds)
-    __device__ __forceinline__ void load(const GeomArrays<S>& G, int N, int atom, bool active,
-                                         const float* Gcs = nullptr, int rows = M) {
+    __device__ __forceinline__ void load(const SetDev& d, int atom, bool active, int rows = M) {
+        const int N = d.N;
         if constexpr (sizeof(S) == 4) {
-            if (G.pk0) {
 #pragma unroll
-                for (int m = 0; m < M; ++m) {
-                    const size_t o = (size_t)m * N + atom;
-                    const bool ok = active && m < rows;
-                    const float4 a = ok ? G.pk0[o] : make_float4(0.f, 0.f, 0.f, 3.f);
-                    const float4 b = ok ? G.pk1[o] : make_float4(0.f, 0.f, 0.f, 0.f);
-                    ux[m] = a.x; uy[m] = a.y; uz[m] = a.z; rhi[m] = a.w;
-                    rlo[m] = b.x; rinv[m] = b.y; fc[m] = b.z; hfcp[m] = b.w;
-                }
-                if constexpr (kCache && NP > 0) {
-                    static_assert(M <= 6, "the pair table holds bonds 0-5");
-                    if (Gcs && active) {
-                        int p = 0;
-#pragma unroll
-                        for (int j = 0; j < M; ++j)
-#pragma unroll
-                            for (int k = j + 1; k < M; ++k)
-                                cs[p++] = k < rows ? Gcs[(size_t)(k * (k - 1) / 2 + j) * N + atom] : S(0);
-                        return;
-                    }
-                }
-                cache_cos();
-                angular_moments();
-                return;
+            for (int m = 0; m < M; ++m) {
+                const size_t o = (size_t)m * N + atom;
+                const bool ok = active && m < rows;
+                const float4 a = ok ? d.gf.pk0[o] : make_float4(0.f, 0.f, 0.f, 3.f);
+                const float4 b = ok ? d.gf.pk1[o] : make_float4(0.f, 0.f, 0.f, 0.f);
+                ux[m] = a.x; uy[m] = a.y; uz[m] = a.z; rhi[m] = a.w;
+                rlo[m] = b.x; rinv[m] = b.y; fc[m] = b.z; hfcp[m] = b.w;
             }
-        }
+            if constexpr (kCache && NP > 0) {
+                static_assert(M <= 6, "the pair table holds bonds 0-5");
+                int p = 0;
 #pragma unroll
-        for (int m = 0; m < M; ++m) {
-            const size_t o = (size_t)m * N + atom;
-            const bool ok = active && m < rows;
-            ux[m] = ok ? G.ux[o] : S(0);
-            uy[m] = ok ? G.uy[o] : S(0);
-            uz[m] = ok ? G.uz[o] : S(0);
-            rhi[m] = ok ? G.rhi[o] : S(3);
-            rlo[m] = (ok && G.rlo) ? G.rlo[o] : S(0);
-            rinv[m] = ok ? G.rinv[o] : S(0);
-            fc[m] = ok ? G.fc[o] : S(0);
-            hfcp[m] = ok ? G.hfcp[o] : S(0);
+                for (int j = 0; j < M; ++j)
+#pragma unroll
+                    for (int k = j + 1; k < M; ++k)
+                        cs[p++] = active && k < rows ? d.gcs[(size_t)(k * (k - 1) / 2 + j) * N + atom] : S(0);
+            }
+        } else {
+            const GeomArrays<double>& G = d.gd;
+#pragma unroll
+            for (int m = 0; m < M; ++m) {
+                const size_t o = (size_t)m * N + atom;
+                const bool ok = active && m < rows;
+                ux[m] = ok ? G.ux[o] : S(0);
+                uy[m] = ok ? G.uy[o] : S(0);
+                uz[m] = ok ? G.uz[o] : S(0);
+                rhi[m] = ok ? G.rhi[o] : S(3);
+                rlo[m] = S(0);
+                rinv[m] = ok ? G.rinv[o] : S(0);
+                fc[m] = ok ? G.fc[o] : S(0);
+                hfcp[m] = ok ? G.hfcp[o] : S(0);
+            }
+            cache_cos();
         }
-        cache_cos();
-        angular_moments();
+        load_moments(d, atom, active, rows);
     }
 
     __device__ __forceinline__ void cache_cos() {
@@ -226,16 +214,25 @@ __device__ __forceinline__ void opaque(S (&a)[N]) {
 constexpr int kPairwiseMax = 8;
 
 // The site routine.  It hands each bond gradient G_j to sink(j, Gx, Gy, Gz);
-// PerBond selects the one-bond-at-a-time backward sweep (for large M), which
-// emits G_j as soon as it is complete.
+// PerBond selects the one-bond-at-a-time backward sweep (for large M without
+// moments), which emits G_j as soon as it is complete.
 // SerialE64: keep the float64 energy chains of the bonds one after another
 // (fewer live registers; a kernel with other wavefronts to switch to loses
 // nothing), or let them interleave (a kernel that runs about one wavefront per
 // SIMD needs the instruction-level parallelism).
+// park: where the moment path leaves two values per bond between its sweeps
+// (registers, or the bond's exchange slot).
+template <typename S, int M>
+struct ParkRegs {
+    S a[M > 0 ? M : 1], b[M > 0 ? M : 1];
+    __device__ __forceinline__ void put(int j, S x, S y) { a[j] = x; b[j] = y; }
+    __device__ __forceinline__ void get(int j, S& x, S& y) const { x = a[j]; y = b[j]; }
+};
+
 template <typename S, int M, bool Energy64, bool PerBond, bool Full = false, bool SerialE64 = true,
-          typename Sink>
+          typename Sink, typename Park>
 __device__ __forceinline__ void site_eval_sink(Geo<S, M, Full>& g, const Cand<S, Full>& p,
-                                               typename EnergyOf<S>::type& U, Sink&& sink) {
+                                               typename EnergyOf<S>::type& U, Sink&& sink, Park&& park) {
     constexpr int MM = M > 0 ? M : 1;
     if constexpr (!Geo<S, M, Full>::kCache && M > 1) {
         // cos(theta) is not cached for larger M: keep the compiler from
@@ -250,25 +247,6 @@ __device__ __forceinline__ void site_eval_sink(Geo<S, M, Full>& g, const Cand<S,
     // float hi/lo pair, so that a float rounding of h does not shift every
     // (cos - h)^2 of a candidate the same way.
     constexpr bool kE64 = Energy64 && std::is_same<S, float>::value;
-    S zeta[MM];
-#pragma unroll
-    for (int j = 0; j < M; ++j) zeta[j] = S(0);
-    {
-        int pidx = 0;
-#pragma unroll
-        for (int j = 0; j < M; ++j) {
-#pragma unroll
-            for (int k = j + 1; k < M; ++k) {
-                const S c = g.cosjk(j, k, pidx++);
-                S t;
-                if constexpr (kE64) t = (c - p.h) - p.hlo;
-                else t = c - p.h;
-                const S gv = ang_g<Full>(p, t);
-                zeta[j] = zeta[j] + g.fc[k] * gv;
-                zeta[k] = zeta[k] + g.fc[j] * gv;
-            }
-        }
-    }
     // Energy64: in float32 the rounding of f_R and b f_A (up to ~15 eV each
     // for parameters inside the fitting box) and the one-ulp errors of the
     // hardware exponentials reach 1e-6 eV per bond.  The exponentials whose
@@ -277,12 +255,11 @@ __device__ __forceinline__ void site_eval_sink(Geo<S, M, Full>& g, const Cand<S,
     // 1 + zeta^n, whose error enters b damped by zeta^n / (1 + zeta^n) / 2n),
     // and the pair energy is formed in float64.  Their float32 roundings feed
     // the gradient.
-    S cc[MM], D[MM];
     S usum = S(0);
     double usum64 = 0.0;
-#pragma unroll
-    for (int j = 0; j < M; ++j) {
-        const S z = zeta[j] * p.zs;
+    // bond j's energy terms from its angular sum: c~_j and D_j of its gradient
+    auto bond = [&](int j, S zeta, S& ccj, S& Dj) __attribute__((always_inline)) {
+        const S z = zeta * p.zs;
         // zeta = 0 (no other neighbour inside the cutoff, or all at g = 0):
         // zeta^n = 0 exactly, so b = 1 and db/dzeta * zeta^n-terms vanish
         const bool pos = z > S(0);
@@ -316,7 +293,9 @@ __device__ __forceinline__ void site_eval_sink(Geo<S, M, Full>& g, const Cand<S,
             const S delta = (g.rhi[j] - p.r0hi) + (g.rlo[j] - p.r0lo);
             eA = dexp2(-(p.aA * delta));
             if constexpr (Full) eR = dexp2(-(p.aR * delta));
-            zn = pos ? dexp2(p.n * dlog2(zsafe)) : S(0);
+            // formed before the selection: a branch around it splits the chain
+            const S zne = dexp2(p.n * dlog2(zsafe));
+            zn = pos ? zne : S(0);
             b = dexp2(p.ninv2n * dlog2(S(1) + zn));
         }
         const S onep = S(1) + zn;
@@ -328,14 +307,85 @@ __device__ __forceinline__ void site_eval_sink(Geo<S, M, Full>& g, const Cand<S,
         const S bfA = b * fA;
         if constexpr (!kE64) usum = usum + g.fc[j] * diff;
         // D = 1/2 [f_C' (f_R - b f_A) + f_C (mu b f_A - lambda f_R)]
-        if constexpr (Full) D[j] = g.hfcp[j] * diff + g.fc[j] * (p.hmu * bfA - p.hlambda * fR);
-        else D[j] = g.hfcp[j] * diff + (p.hmu * g.fc[j]) * (bfA - S(2) * fR);
+        if constexpr (Full) Dj = g.hfcp[j] * diff + g.fc[j] * (p.hmu * bfA - p.hlambda * fR);
+        else Dj = g.hfcp[j] * diff + (p.hmu * g.fc[j]) * (bfA - S(2) * fR);
         // c~ = -ZS f_C f_A db/dzeta with db/dzeta = -b zeta^n / (2 zeta (1 + zeta^n))
-        cc[j] = (p.ccs * g.fc[j]) * (bfA * zn) * drcp(zsafe * onep);
-        // per-bond sweep: keep the scheduler from interleaving all M bonds' chains
-        // (about ten live values each; float64 ones in the energy mode)
-        if constexpr (PerBond || (kE64 && SerialE64)) __builtin_amdgcn_sched_barrier(0);
+        ccj = (p.ccs * g.fc[j]) * (bfA * zn) * drcp(zsafe * onep);
+        // keep the scheduler from interleaving all M bonds' chains (about ten
+        // live values each; float64 ones in the energy mode)
+        if constexpr (PerBond || Geo<S, M, Full>::kMoments || (kE64 && SerialE64)) __builtin_amdgcn_sched_barrier(0);
+    };
+    if constexpr (Geo<S, M, Full>::kMoments) {
+        // The pair sums of every bond from the moments over all bonds:
+        //   sum_k (c~_j f_C,k + c~_k f_C,j) t_jk u_k = c~_j (T u_j - h m) + f_C,j (T~ u_j - h m~),
+        //   sum_k c~_k t_jk^2 = u_j . T~ u_j - 2 h u_j . m~ + h^2 s~,
+        // T = sum f_C u u^T, m = sum f_C u (no parameter in them) and T~, m~, s~
+        // the same with c~ for f_C.  The bond's own term is radial in the first
+        // (removed with the rest of V's radial part) and c~_j (1 - h)^2 in the
+        // second.  About 55 operations per bond, where a sweep over ordered pairs
+        // takes 12 per pair: bound by VALU issue either way (1,870 instructions a
+        // step at M = 12), the M <= 12 launch of 500 candidates x 101 packings
+        // takes 784 us against 969 us.
+        S txx = S(0), tyy = txx, tzz = txx, tyz = txx, tzx = txx, txy = txx, mx = txx, my = txx, mz = txx,
+          sc = txx;
+#pragma unroll
+        for (int j = 0; j < M; ++j) {
+            S t, c, Dj;
+            if constexpr (kE64) t = (g.sh[j] - p.h) - p.hlo;
+            else t = g.sh[j] - p.h;
+            bond(j, g.sv[j] + (g.ss[j] * t) * t, c, Dj);
+            park.put(j, c, Dj);
+            const S cx = c * g.ux[j], cy = c * g.uy[j], cz = c * g.uz[j];
+            sc += c;
+            mx += cx; my += cy; mz += cz;
+            txx += cx * g.ux[j]; tyy += cy * g.uy[j]; tzz += cz * g.uz[j];
+            tyz += cy * g.uz[j]; tzx += cz * g.ux[j]; txy += cx * g.uy[j];
+        }
+        if constexpr (kE64) U = 0.5 * usum64; else U = S(0.5) * usum;
+        mx *= p.h; my *= p.h; mz *= p.h;
+        const S hx = p.h * g.mx, hy = p.h * g.my, hz = p.h * g.mz;
+        const S h2s = (p.h * p.h) * sc, omh2 = (S(1) - p.h) * (S(1) - p.h);
+#pragma unroll
+        for (int j = 0; j < M; ++j) {
+            S c, Dj;
+            park.get(j, c, Dj);
+            const S ux = g.ux[j], uy = g.uy[j], uz = g.uz[j], f = g.fc[j];
+            const S yx = (txx * ux + txy * uy + tzx * uz) - mx;
+            const S yy = (txy * ux + tyy * uy + tyz * uz) - my;
+            const S yz = (tzx * ux + tyz * uy + tzz * uz) - mz;
+            const S wx = (g.txx * ux + g.txy * uy + g.tzx * uz) - hx;
+            const S wy = (g.txy * ux + g.tyy * uy + g.tyz * uz) - hy;
+            const S wz = (g.tzx * ux + g.tyz * uy + g.tzz * uz) - hz;
+            const S vx = f * yx + c * wx, vy = f * yy + c * wy, vz = f * yz + c * wz;
+            const S pp = ((ux * yx + uy * yy + uz * yz) - (ux * mx + uy * my + uz * mz)) + (h2s - c * omh2);
+            const S uv = ux * vx + uy * vy + uz * vz;
+            const S rad = Dj + g.hfcp[j] * pp - uv * g.rinv[j];
+            sink(j, rad * ux + vx * g.rinv[j], rad * uy + vy * g.rinv[j], rad * uz + vz * g.rinv[j]);
+            __builtin_amdgcn_sched_barrier(0);
+        }
+        return;
     }
+    S zeta[MM], cc[MM], D[MM];
+#pragma unroll
+    for (int j = 0; j < M; ++j) zeta[j] = S(0);
+    {
+        int pidx = 0;
+#pragma unroll
+        for (int j = 0; j < M; ++j) {
+#pragma unroll
+            for (int k = j + 1; k < M; ++k) {
+                const S c = g.cosjk(j, k, pidx++);
+                S t;
+                if constexpr (kE64) t = (c - p.h) - p.hlo;
+                else t = c - p.h;
+                const S gv = ang_g<Full>(p, t);
+                zeta[j] = zeta[j] + g.fc[k] * gv;
+                zeta[k] = zeta[k] + g.fc[j] * gv;
+            }
+        }
+    }
+#pragma unroll
+    for (int j = 0; j < M; ++j) bond(j, zeta[j], cc[j], D[j]);
     if constexpr (kE64) U = 0.5 * usum64; else U = S(0.5) * usum;
     if constexpr (PerBond) {
         // One bond at a time, visiting each pair from both ends.
@@ -414,7 +464,8 @@ __device__ __forceinline__ void site_eval(Geo<S, M, Full>& g, const Cand<S, Full
             Gx[j] = x;
             Gy[j] = y;
             Gz[j] = z;
-        });
+        },
+        ParkRegs<S, M>{});
 }
 
 // Cross-lane exchanges of a double, 32 bits at a time.
