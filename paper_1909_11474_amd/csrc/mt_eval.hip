@@ -9,6 +9,7 @@
 #include <cmath>
 #include <numeric>
 #include <queue>
+#include <set>
 #include <string>
 #include <vector>
 
@@ -534,6 +535,7 @@ int class_of(int fam, int kmax) {
 }
 
 LaunchCfg default_cfg(const mt_set* set, int P, int precision) {
+    (void)P;
     (void)precision;
     LaunchCfg c;
     int maxpad = 8;
@@ -541,11 +543,7 @@ LaunchCfg default_cfg(const mt_set* set, int P, int precision) {
         if (!set->h_large[s]) maxpad = std::max(maxpad, set->h_npad[s]);
     c.block = std::max(64, ((maxpad + 63) / 64) * 64);
     if (c.block < 256 && maxpad <= 64) c.block = 256;
-    // aim for about 4 work items per compute unit
-    long long pairs = (long long)P * std::max(1, set->n_batched);
-    long long tile = std::max<long long>(1, pairs / 1024);
-    tile = std::min<long long>(tile, P);
-    c.tile = (int)std::max<long long>(1, tile);
+    c.tile = 0;
     c.persistent = 0;
     return c;
 }
@@ -563,27 +561,54 @@ static bool upload_class(ClassPlan& cp, const std::vector<Item>& ordered, const 
     return hipMemcpy(cp.bin_off.p, bin_off.data(), sizeof(int) * bin_off.size(), hipMemcpyHostToDevice) == hipSuccess;
 }
 
-// Candidate tile of structure s at R replicas per block (whole steps of the replicas).
-static int tile_for(const LaunchCfg& cfg, int P, int R, bool plain) {
+// Candidate tile of structure s at R replicas per block (whole steps of the
+// replicas): cfg.tile candidates, or steps per replica where cfg.tile is 0,
+// held to 128 candidates (at least one step) so that the parameter records
+// take at most 13 KB (float) of the LDS that the exchange needs.
+static int tile_for(const LaunchCfg& cfg, int P, int R, bool plain, int steps) {
     int tile = plain ? 1 : std::max(cfg.tile, 1);
+    if (!plain && cfg.tile == 0) tile = std::max(R, std::min(steps * R, 128));
     if (!plain) tile = ((tile + R - 1) / R) * R;
     return std::min(tile, ((P + R - 1) / R) * R);
 }
 
-// Block size for structure s: the requested one when its LDS fits the device
-// (replicas that do not fill the block leave whole wavefronts idle), else the
-// largest smaller multiple of 64 threads, at least the padded size, that fits;
-// 0 when a single replica does not fit.  Keeping the requested size keeps
-// every structure of a class in one launch.
+// Block size for structure s: the requested one when its LDS fits the device at
+// the smallest tile (replicas that do not fill the block leave whole wavefronts
+// idle), else the largest smaller multiple of 64 threads, at least the padded
+// size, that fits; 0 when a single replica does not fit.  Keeping the requested
+// size keeps every structure of a class in one launch.
 static int block_for(const mt_set* set, int s, const LaunchCfg& cfg, int P, int fam, bool plain) {
     const int npad = set->h_npad[s];
     const int least = std::max(64, npad);
-    for (int block = plain ? least : cfg.block; block >= least; block -= 64) {
-        const int R = block / npad;
-        if (item_lds(set, s, block, fam, std::min(tile_for(cfg, P, R, plain), P)) <= set->lds_max)
+    for (int block = plain ? least : cfg.block; block >= least; block -= 64)
+        if (item_lds(set, s, block, fam, std::min(tile_for(cfg, P, block / npad, plain, 1), P)) <= set->lds_max)
             return block;
-    }
     return 0;
+}
+
+// Relative time of a block's step with R replicas of structure s: the busiest
+// SIMD's bonds per lane (at least the costliest wavefront's, at least a quarter
+// of all wavefronts'), three bonds' worth added per wavefront for the exchange
+// and the group sums.
+static double step_cost(const mt_set* set, int s, int R) {
+    const int npad = set->h_npad[s];
+    const double waves = (double)R * npad / 64.0;
+    return std::max(set->h_kmax[s] + 3.0, (R * set->h_xsize[s] / 64.0 + 3.0 * waves) / 4.0);
+}
+
+// Time of a launch's work items where the launch shape leaves the tile open, in
+// units of step_cost.  total: the launch's block steps, mean: of one of them;
+// round: their share per block the device holds at once.  Up to a few steps one
+// item per block slot is best; beyond that an item costs about two steps more
+// than its own (records, bond geometry) and the launch ends about half an item
+// after the blocks run out: least at sqrt(4 mean round).  Against items of P S / 1024
+// candidates: 500 candidates x 300 structures 1.15 -> 0.91 ms, 200 x 60
+// (Tersoff form) 0.24 -> 0.20 ms; the best of a sweep of fixed tiles takes 0.88
+// and 0.19 ms.
+static double auto_item(double total, double mean, int block, int mc, int fam, int ncu) {
+    const int waves = mc <= 4 && fam == FAM_FIT32 ? 16 : 8;          // per compute unit (registers)
+    const double round = total / ((double)ncu * std::max(1, waves * 64 / block));
+    return std::min(round, std::sqrt(4.0 * mean * round));
 }
 
 // The blocks of a launch go to the XCDs round robin (block b to XCD b mod 8),
@@ -636,10 +661,18 @@ ItemPlan* get_plan(mt_set* set, int P, const LaunchCfg& cfg, int fam) {
         std::vector<Item> items;
         size_t lds = 16;
     };
+    // the adjoint reads the residuals of the structures that its fitness call
+    // batched: those it left out go to the two-pass path here too
+    std::set<int> not_batched;
+    if (family_adjoint(fam)) {
+        const ItemPlan* fit = get_plan(set, P, cfg, fit_family(fam));
+        if (!fit) return nullptr;
+        not_batched.insert(fit->twopass.begin(), fit->twopass.end());
+    }
     // Launch class of each structure.  A class above 4 whose work items would
-    // fill fewer blocks than the device has compute units joins the next
-    // larger class that has work: on its own its launch leaves most of the
-    // device idle, and the larger class's kernel runs the same compiled
+    // fill fewer blocks than the device has compute units (with an open tile:
+    // under 16 steps for each) joins the next larger class that has work: on its
+    // own its launch leaves most of the device idle, and the larger class's kernel runs the same compiled
     // variants (chosen per wavefront by the largest coordination, never
     // below 3) on the same exchange-slot layout, so results are unchanged.
     const std::vector<int>& classes = family_classes(fam);
@@ -653,51 +686,92 @@ ItemPlan* get_plan(mt_set* set, int P, const LaunchCfg& cfg, int fam) {
             continue;
         }
         cls[s] = class_of(fam, set->h_kmax[s]);
-        if (!plain) {
-            const int tile = tile_for(cfg, P, std::max(1, cfg.block / set->h_npad[s]), plain);
-            nitems[cls[s]] += (P + tile - 1) / tile;
-        }
     }
+    // block steps of structure s and their time
+    auto block_steps = [&](int s, int block) {
+        const int R = std::max(1, block / set->h_npad[s]);
+        return (P + R - 1) / R;
+    };
+    auto add_work = [&](int s, int block, std::pair<double, double>& w) {
+        const double n = block_steps(s, block);
+        w.first += n;
+        w.second += n * step_cost(set, s, std::max(1, block / set->h_npad[s]));
+    };
+    // steps per item of structure s in a launch of work w (steps, time)
+    auto open_steps = [&](int s, int block, int mc, const std::pair<double, double>& w) {
+        const double item = auto_item(w.second, w.second / w.first, block, mc, fam, ncu);
+        return std::max(1, (int)std::lround(item / step_cost(set, s, std::max(1, block / set->h_npad[s]))));
+    };
+    // work and work items per class
+    std::map<int, std::pair<double, double>> work_of;
+    auto count = [&]() {
+        work_of.clear();
+        nitems.clear();
+        for (int s = 0; s < set->S; ++s)
+            if (cls[s]) add_work(s, cfg.block, work_of[cls[s]]);
+        for (int s = 0; s < set->S; ++s)
+            if (cls[s]) {
+                const int steps = open_steps(s, std::max(64, cfg.block), cls[s], work_of[cls[s]]);
+                const int tile = tile_for(cfg, P, std::max(1, cfg.block / set->h_npad[s]), plain, steps);
+                nitems[cls[s]] += (P + tile - 1) / tile;
+            }
+    };
+    if (!plain) count();
     for (size_t i = 0; !plain && i < classes.size(); ++i) {
         const int mc = classes[i];
-        if (mc <= 4 || nitems[mc] == 0 || nitems[mc] >= ncu) continue;
+        if (mc <= 4 || nitems[mc] == 0) continue;
+        if (cfg.tile == 0 ? work_of[mc].first >= 16.0 * ncu : nitems[mc] >= ncu) continue;
         for (size_t j = i + 1; j < classes.size(); ++j) {
             const int to = classes[j];
             if (nitems[to] == 0) continue;
             for (int s = 0; s < set->S; ++s)
                 if (!set->h_large[s] && cls[s] == mc) cls[s] = to;
-            nitems[to] += nitems[mc];
-            nitems[mc] = 0;
+            count();
             break;
         }
     }
     for (int mc : classes) {
-        std::map<int, Group> groups;          // launch block size -> work items
+        std::map<int, std::vector<int>> members;   // launch block size -> structures
+        std::map<int, std::pair<double, double>> work;      // and their block steps and time
         for (int s = 0; s < set->S; ++s) {
             if (set->h_large[s] || cls[s] != mc) continue;
-            const int npad = set->h_npad[s];
-            if (!plain && cfg.block < npad) return nullptr;
+            if (!plain && cfg.block < set->h_npad[s]) return nullptr;
             const int block = block_for(set, s, cfg, P, fam, plain);
-            // the adjoint reads the residuals of the structures that its
-            // fitness call batched
-            if (block == 0 || (family_adjoint(fam) && block_for(set, s, cfg, P, fit_family(fam), plain) == 0)) {
+            if (block == 0 || not_batched.count(s)) {
                 plan->twopass.push_back(s);
                 continue;
             }
-            const int R = block / npad;
-            const int tile = tile_for(cfg, P, R, plain);
+            members[block].push_back(s);
+            add_work(s, block, work[block]);
+        }
+        std::map<int, Group> groups;               // launch block size -> work items
+        for (auto& [block, structs] : members) {
             Group& g = groups[block];
-            g.lds = std::max(g.lds, item_lds(set, s, block, fam, std::min(tile, P)));
-            const int ns = set->h_off[s + 1] - set->h_off[s];
-            for (int c0 = 0; c0 < P; c0 += tile) {
-                Item it;
-                it.s = s;
-                it.c0 = c0;
-                it.nc = std::min(tile, P - c0);
-                const long long steps = (it.nc + R - 1) / R;
-                const long long per = set->h_trip[s] + 8ll * ns + 64;
-                it.cost = (int)std::min<long long>(steps * per / std::max(1, R) + 1, 1ll << 30);
-                g.items.push_back(it);
+            for (int s : structs) {
+                const int R = block / set->h_npad[s];
+                int steps = open_steps(s, block, mc, work[block]);
+                int tile = tile_for(cfg, P, R, plain, steps);
+                // an open tile is halved until its records fit beside the exchange
+                while (steps > 1 && cfg.tile == 0 && item_lds(set, s, block, fam, std::min(tile, P)) > set->lds_max)
+                    tile = tile_for(cfg, P, R, plain, steps /= 2);
+                g.lds = std::max(g.lds, item_lds(set, s, block, fam, std::min(tile, P)));
+                for (int c0 = 0; c0 < P;) {
+                    Item it;
+                    it.s = s;
+                    it.c0 = c0;
+                    it.nc = std::min(tile, P - c0);
+                    if (!plain && cfg.tile == 0) {
+                        // an open tile shrinks to half of what is left (at
+                        // least a quarter of it), so that the launch ends on
+                        // short items
+                        const int left = (P - c0 + 2 * R - 1) / (2 * R), least = std::max(1, steps / 4);
+                        it.nc = std::min(it.nc, std::max(left, least) * R);
+                    }
+                    c0 += it.nc;
+                    const int n = (it.nc + R - 1) / R;
+                    it.cost = (int)std::min(16.0 * n * step_cost(set, s, R) + 1.0, 1e9);
+                    g.items.push_back(it);
+                }
             }
         }
         for (auto it = groups.rbegin(); it != groups.rend(); ++it) {

@@ -1,0 +1,65 @@
+"""Launch shapes the other tests do not reach: every block size in whole
+wavefronts (rows of one to four wavefronts in the last place of a block, which
+take the costly and cheap chunks of 64 atoms in turn), and the work lists of an
+open tile at small, odd and large populations.
+
+Z in float64 is bit-identical to the plain schedule (one item per launch); in
+float32 it is bit-identical across shapes.
+"""
+import numpy as np
+import pytest
+
+import workloads as W
+
+pytestmark = pytest.mark.gpu
+
+
+def rng(seed):
+    return np.random.Generator(np.random.PCG64(seed))
+
+
+@pytest.fixture(scope="module")
+def tset():
+    import torch
+    if not torch.cuda.is_available():
+        pytest.skip("no GPU")
+    from paper_1909_11474_amd import api
+    dia, cell = W.diamond(2, 2, 2)
+    s = W.make_set([W.random_packing(rng(n), n) for n in (9, 33, 100, 129, 190)] +
+                   [(W.displace(rng(1), dia, 0.1), cell)])
+    ts = api.from_structures(s)
+    ref = ts.tersoff_eval(W.draw_params(rng(2), 1), precision="fp64")
+    n = torch.as_tensor(s.sizes(), dtype=torch.float64, device="cuda")
+    ts.attach_reference(ref["E"][0] / n, ref["W"][0] / n[:, None], ref["F"][0])
+    yield ts
+    ts.close()
+
+
+@pytest.mark.parametrize("block", [192, 256, 320, 384, 448, 512])
+def test_every_block_size(tset, block, tmp_path):
+    X = W.draw_params(rng(3), 11)
+    plain = tset.fitness(X, precision="fp64", schedule="plain").cpu().numpy()
+    f32 = tset.fitness(X, precision="fp32").cpu().numpy()
+    s = tset.stats()
+    for prec, code, want in (("fp64", 0, plain), ("fp32", 1, f32)):
+        p = tmp_path / prec
+        p.write_text("N=%d S=%d nb=%d trip=%d P=%d prec=%d | block=%d tile=3 persistent=0 graph=0 ms=1\n" % (
+            s["n_atoms"], s["n_struct"], s["n_bonds"], s["n_triplets"], len(X), code, block))
+        tset.autotune(len(X), prec, str(p))
+        got = tset.fitness(X, precision=prec).cpu().numpy()
+        assert p.read_text().count("\n") == 1           # the shape was taken, not timed
+        assert np.array_equal(got, want), prec
+
+
+@pytest.mark.parametrize("P", [1, 2, 7, 65, 500])
+def test_open_tile(tset, P):
+    X = W.draw_params(rng(4), 1000)[:P]
+    got = tset.fitness(X, precision="fp64").cpu().numpy()
+    plain = tset.fitness(X, precision="fp64", schedule="plain").cpu().numpy()
+    assert np.array_equal(got, plain)
+    # each candidate's value does not depend on how many others there are
+    one = tset.fitness(X[-1:], precision="fp64").cpu().numpy()
+    assert np.array_equal(got[-1:], one)
+    _, G = tset.fitness_grad(X, precision="fp64")
+    _, g = tset.fitness_grad(X[-1:], precision="fp64")
+    assert np.array_equal(G[-1:].cpu().numpy(), g.cpu().numpy())
