@@ -53,7 +53,7 @@ mt::SetDev mt_set::dev() const {
     SetDev d{};
     d.S = S; d.N = N; d.kcap = kcap; d.nb = nb; d.nslots = nslots;
     d.st_off = st_off.as<int>(); d.st_boff = st_boff.as<int>(); d.st_npad = st_npad.as<int>();
-    d.st_kmax = st_kmax.as<int>(); d.st_slot = st_slot.as<int>(); d.st_xsize = st_xsize.as<int>();
+    d.st_kmax = st_kmax; d.st_slot = st_slot.as<int>(); d.st_xsize = st_xsize;
     d.perm = perm.as<int>(); d.nnb = nnb.as<int>(); d.lbo = lbo.as<int>(); d.xbase = xbase.as<int>();
     d.rev = rev.as<int>(); d.revc = revc.as<int>(); d.jl = jl.as<int>();
     const size_t KN = (size_t)kcap * N;
@@ -336,6 +336,7 @@ static int fitness_graph(mt_set* set, const double* x, int form, int P, const do
         ItemPlan* plan = get_plan(set, P, cfg, family_for(precision, MODE_FIT, form));
         if (!plan) return fail(MT_EINVAL, "could not build the work list");
         TRY(reserve_twopass(set, plan, P, precision));     // allocate before capture
+        if (precision != MT_FP64) TRY(float_tables(set, st));
         if (!set->capture_stream) HIPCHECK(hipStreamCreateWithFlags(&set->capture_stream, hipStreamNonBlocking));
         GraphEntry ge;
         ge.key = key;
@@ -569,6 +570,12 @@ int mt_autotune(mt_set* set, int P, int precision, const char* cache_path) {
     if (P <= 0) return fail(MT_EINVAL, "P must be positive");
     if (precision != MT_FP64 && precision != MT_FP32_ACC64)
         return fail(MT_EINVAL, "precision must be MT_FP64 or MT_FP32_ACC64");
+    if (precision != MT_FP64 && !set->f32_ready) {
+        // the calls that follow may be on any stream
+        HIPCHECK(hipDeviceSynchronize());
+        TRY(float_tables(set, nullptr));
+        HIPCHECK(hipDeviceSynchronize());
+    }
     const int fam = precision == MT_FP64 ? FAM_FIT64 : FAM_FIT32;
     char key[200];
     snprintf(key, sizeof key, "N=%d S=%d nb=%d trip=%lld P=%d prec=%d", set->N, set->S, set->nb,

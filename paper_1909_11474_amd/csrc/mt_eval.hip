@@ -861,6 +861,7 @@ static int launch_twopass(mt_set* set, const std::vector<int>& structs, int P, i
 
 int launch_batched(mt_set* set, const LaunchCfg& cfg, int P, int precision, int mode,
                    const double* vel, double* force, double* atom_virial, hipStream_t st) {
+    if (precision != MT_FP64) TRY_RC(float_tables(set, st));
     const int fam = family_for(precision, mode, set->cur_form);
     ItemPlan* plan = get_plan(set, P, cfg, fam);
     if (!plan) {
@@ -885,6 +886,7 @@ int launch_batched(mt_set* set, const LaunchCfg& cfg, int P, int precision, int 
 
 int launch_plan_fit(mt_set* set, ItemPlan* plan, const LaunchCfg& cfg, int precision, double* partial,
                     hipStream_t st) {
+    if (precision != MT_FP64) TRY_RC(float_tables(set, st));
     const int fam = family_for(precision, MODE_FIT, set->cur_form);
     BArgs<float> Af = make_args<float>(set, partial, kNVFit);
     BArgs<double> Ad = make_args<double>(set, partial, kNVFit);
@@ -902,6 +904,7 @@ int launch_plain(mt_set* set, int P, int precision, int mode, const double* vel,
 // the per-pass average in ms and the launches per pass.  Synchronises st.
 int time_batched_kernels(mt_set* set, const LaunchCfg& cfg, int P, int precision, int reps,
                          hipStream_t st, double* ms, int64_t* launches) {
+    if (precision != MT_FP64) TRY_RC(float_tables(set, st));
     const int fam = family_for(precision, MODE_FIT, set->cur_form);
     ItemPlan* plan = get_plan(set, P, cfg, fam);
     if (!plan) {
@@ -938,6 +941,7 @@ int time_batched_kernels(mt_set* set, const LaunchCfg& cfg, int P, int precision
 int time_class_launches(mt_set* set, const LaunchCfg& cfg, int P, int precision, int reps,
                         hipStream_t st, int max_launches, double* ms, int* mc, int* struct_launch,
                         int* n_launches) {
+    if (precision != MT_FP64) TRY_RC(float_tables(set, st));
     const int fam = family_for(precision, MODE_FIT, set->cur_form);
     ItemPlan* plan = get_plan(set, P, cfg, fam);
     if (!plan) {
@@ -1061,6 +1065,7 @@ static int launch_twopass(mt_set* set, const std::vector<int>& structs, int P, i
 
 int launch_large(mt_set* set, int P, int precision, int mode, const double* vel, double* force,
                  double* atom_virial, hipStream_t st) {
+    if (precision != MT_FP64) TRY_RC(float_tables(set, st));
     if (set->n_large == 0) return MT_OK;
     std::vector<int> structs;
     for (int s = 0; s < set->S; ++s)
@@ -1168,6 +1173,7 @@ static int launch_twopass_adjoint(mt_set* set, const std::vector<int>& structs, 
 
 static int adjoint_common(mt_set* set, const LaunchCfg& cfg, int P, int precision, const double* w,
                           const double* Z, hipStream_t st) {
+    if (precision != MT_FP64) TRY_RC(float_tables(set, st));
     TRY_RC(launch_grad_coef(set, P, w, Z, st));
     const int nv = set->cur_form ? kNVGradTF : kNVGrad;
     HIPCHECK(set->partial2.reserve(sizeof(double) * nv * (size_t)P * set->nslots));

@@ -89,8 +89,12 @@ struct GraphKey {             // what a captured fitness graph depends on
 // Temporaries of the neighbour search and table build, kept with the set so
 // that position updates (molecular dynamics) reuse them instead of allocating.
 struct BuildScratch {
-    DevBuf meta, atom_bin, atom_wrap, bin_count, bin_start, bin_fill, bin_atoms, cnt, ent_j, ent_sh,
-        inv, flags, st_nb, st_trip;
+    DevBuf meta, atom_bin, atom_wrap, bin_count, bin_start, bin_fill, bin_atoms, cnt, ent_j, ent_sh, inv;
+    DevBuf summary;                   // per-structure sums and flags the host reads back
+    std::vector<char> h_summary;
+    int* flags = nullptr;             // in summary
+    long long nbins = 0;              // cell-list bins (0: none yet) at the list radius
+    double rlist = 0;
 };
 
 struct GraphEntry {
@@ -116,7 +120,8 @@ struct mt_set {
 
     // device data (see mt_common.h for the layout)
     mt::DevBuf pos, cell;
-    mt::DevBuf st_off, st_boff, st_npad, st_kmax, st_slot, st_xsize;
+    mt::DevBuf st_off, st_boff, st_npad, st_slot;
+    int *st_kmax = nullptr, *st_xsize = nullptr;   // in build.summary
     mt::DevBuf perm, nnb, lbo, xbase, rev, revc, jl;
     mt::DevBuf nbr_j, nbr_sh;                // caller-numbering neighbour entries, [kcap][N]
     mt::DevBuf gf, gd;                       // float / double geometry, 8 resp. 7 arrays of [kcap][N]
@@ -124,6 +129,10 @@ struct mt_set {
     mt::DevBuf gpk;                          // float geometry packed as 2 x float4, [2][kcap][N]
     mt::DevBuf gam;                          // angular moments per bond (sets above kPairMax neighbours)
     mt::DevBuf gcs;                          // cos(theta) of bond pairs j < k < 6, [15][N] float
+
+    // angle tables of the float kernels: built for the present geometry, and
+    // whether any float call has been made (see float_tables)
+    bool f32_ready = false, f32_used = false;
 
     // references (sorted order)
     bool has_ref = false;
@@ -177,6 +186,9 @@ int build_set(mt_set* set, const int64_t* atom_offset, const double* pos, const 
 int attach_reference(mt_set* set, const double* e_ref, const double* w_ref, const double* f_ref,
                      hipStream_t stream);
 int export_neighbors(const mt_set* set, int32_t* i, int32_t* j, int32_t* shift, hipStream_t stream);
+// The angle tables of the float kernels, built in stream order if the present
+// geometry has none yet (before any float launch).
+int float_tables(mt_set* set, hipStream_t stream);
 // New positions with the neighbour lists of the last build (no host sync).
 int update_geometry(mt_set* set, const double* pos, hipStream_t stream);
 
