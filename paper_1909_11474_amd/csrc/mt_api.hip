@@ -52,8 +52,7 @@ static int fail(int code, const std::string& msg) {
 mt::SetDev mt_set::dev() const {
     SetDev d{};
     d.S = S; d.N = N; d.kcap = kcap; d.nb = nb; d.nslots = nslots;
-    d.st_off = st_off.as<int>(); d.st_boff = st_boff.as<int>(); d.st_npad = st_npad.as<int>();
-    d.st_kmax = st_kmax; d.st_slot = st_slot.as<int>(); d.st_xsize = st_xsize;
+    d.st_off = st_off.as<int>(); d.st_boff = st_boff.as<int>(); d.st_slot = st_slot.as<int>();
     d.perm = perm.as<int>(); d.nnb = nnb.as<int>(); d.lbo = lbo.as<int>(); d.xbase = xbase.as<int>();
     d.rev = rev.as<int>(); d.revc = revc.as<int>(); d.jl = jl.as<int>();
     const size_t KN = (size_t)kcap * N;

@@ -86,11 +86,18 @@ enum ParamIndex {
     P_HLO = 24      // h - float(h) (float records; zero in double records)
 };
 
-struct Item {       // one (structure, candidate range) work item of the batched kernel
+// One (structure, candidate range) work item of the batched kernels, with the
+// structure's own numbers: a block learns all of them in one load.
+struct Item {
     int s;
     int c0;
     int nc;
     int cost;       // relative cost used for scheduling
+    int a0, ns;     // the structure's first atom and atom count
+    int npad;
+    int slot;       // its first partial-sum slot
+    int xsz;        // exchange slots of one replica
+    int unused[3];  // 48 bytes
 };
 
 template <typename S>
@@ -105,9 +112,8 @@ struct GeomArrays {
 
 struct SetDev {
     int S, N, kcap, nb, nslots;
-    const int* st_off; const int* st_boff; const int* st_npad; const int* st_kmax;
+    const int* st_off; const int* st_boff;
     const int* st_slot;
-    const int* st_xsize;                        // exchange slots of one replica
     const int* perm; const int* nnb; const int* lbo;
     const int* xbase;                           // [N] first exchange slot of the atom
     const int* rev;                             // [kcap][N] exchange slot of the reverse bond

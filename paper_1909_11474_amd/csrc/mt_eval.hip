@@ -7,7 +7,6 @@
 
 #include <algorithm>
 #include <cmath>
-#include <numeric>
 #include <queue>
 #include <set>
 #include <string>
@@ -548,15 +547,17 @@ LaunchCfg default_cfg(const mt_set* set, int P, int precision) {
     return c;
 }
 
+// bin_off empty: one item per block.
 static bool upload_class(ClassPlan& cp, const std::vector<Item>& ordered, const std::vector<int>& bin_off) {
     cp.h_items = ordered;
     cp.n_items = (int)ordered.size();
-    cp.n_bins = (int)bin_off.size() - 1;
+    cp.n_bins = bin_off.empty() ? cp.n_items : (int)bin_off.size() - 1;
     if (cp.n_items > 0) {
         if (cp.items.reserve(sizeof(Item) * ordered.size()) != hipSuccess) return false;
         if (hipMemcpy(cp.items.p, ordered.data(), sizeof(Item) * ordered.size(), hipMemcpyHostToDevice) != hipSuccess)
             return false;
     }
+    if (bin_off.empty()) return true;
     if (cp.bin_off.reserve(sizeof(int) * bin_off.size()) != hipSuccess) return false;
     return hipMemcpy(cp.bin_off.p, bin_off.data(), sizeof(int) * bin_off.size(), hipMemcpyHostToDevice) == hipSuccess;
 }
@@ -756,8 +757,13 @@ ItemPlan* get_plan(mt_set* set, int P, const LaunchCfg& cfg, int fam) {
                     tile = tile_for(cfg, P, R, plain, steps /= 2);
                 g.lds = std::max(g.lds, item_lds(set, s, block, fam, std::min(tile, P)));
                 for (int c0 = 0; c0 < P;) {
-                    Item it;
+                    Item it{};
                     it.s = s;
+                    it.a0 = set->h_off[s];
+                    it.ns = set->h_off[s + 1] - set->h_off[s];
+                    it.npad = set->h_npad[s];
+                    it.slot = set->h_slot[s];
+                    it.xsz = set->h_xsize[s];
                     it.c0 = c0;
                     it.nc = std::min(tile, P - c0);
                     if (!plain && cfg.tile == 0) {
@@ -784,7 +790,6 @@ ItemPlan* get_plan(mt_set* set, int P, const LaunchCfg& cfg, int fam) {
             std::vector<Item> ordered;
             if (plain) {
                 ordered = items;
-                bin_off = {0, 1};
             } else {
                 // longest first; equal costs grouped by XCD (bins, one per block,
                 // take the items in this order)
@@ -793,8 +798,6 @@ ItemPlan* get_plan(mt_set* set, int P, const LaunchCfg& cfg, int fam) {
                 items = xcd_grouped(items);
                 if (!cfg.persistent) {
                     ordered = items;
-                    bin_off.resize(items.size() + 1);
-                    std::iota(bin_off.begin(), bin_off.end(), 0);
                 } else {
                     const int per_cu = std::max(1, 1024 / cp->block);
                     const int nbins = (int)std::min<size_t>(items.size(), (size_t)ncu * per_cu);

@@ -135,7 +135,7 @@ template <typename S>
 struct BArgs {
     SetDev set;
     const Item* items;
-    const int* bin_off;
+    const int* bin_off;       // null: one item per block
     const double* x;          // [P][6] (minimal) or [P][9] (Tersoff form) parameter sets
     double* partial;          // [P][nslots][nv]
     int nv;
@@ -164,7 +164,7 @@ template <>
 __device__ __forceinline__ const double* fref_of<double>(const SetDev& d) { return d.fref64; }
 
 struct ItemCtx {
-    int s, a0, Ns, npad, R, q, la, atom, steps, slot, g, xsz, own;
+    int s, a0, Ns, npad, R, q, la, atom, steps, slot, g, xsz, own, Mw;
     bool active, block_sync;
 };
 
@@ -173,9 +173,9 @@ __device__ __forceinline__ ItemCtx item_ctx(const SetDev& d, const Item& it) {
     // multiple of 64, so lane -> (replica, atom) needs no vector division.
     ItemCtx x;
     x.s = it.s;
-    x.a0 = d.st_off[x.s];
-    x.Ns = d.st_off[x.s + 1] - x.a0;
-    x.npad = d.st_npad[x.s];
+    x.a0 = it.a0;
+    x.Ns = it.ns;
+    x.npad = it.npad;
     const int tid = threadIdx.x;
     if (x.npad <= 64) {
         const int sh = 31 - __clz(x.npad);
@@ -204,12 +204,16 @@ __device__ __forceinline__ ItemCtx item_ctx(const SetDev& d, const Item& it) {
     x.active = (x.q < x.R) && (x.la < x.Ns);
     x.atom = x.a0 + (x.active ? x.la : 0);
     x.steps = (it.nc + x.R - 1) / x.R;
-    x.slot = d.st_slot[x.s] + (x.npad > 64 ? (x.la >> 6) : 0);
-    x.xsz = d.st_xsize[x.s];
+    x.slot = it.slot + (x.npad > 64 ? (x.la >> 6) : 0);
+    x.xsz = it.xsz;
     x.block_sync = x.npad > 64;
-    // own exchange slot base: the chunk's first atom is always a real atom
-    const int first = x.la & ~(x.g - 1);
-    x.own = (x.q < x.R) ? (d.xbase[x.a0 + first] + (x.la - first) + x.q * x.xsz) : 0;
+    // own exchange slot base: the first chunk's slots start at 0, and a chunk's
+    // first atom is always a real atom
+    const int chunk0 = x.npad > 64 ? __builtin_amdgcn_readfirstlane(x.la & ~63) : 0;
+    x.own = x.q < x.R ? (chunk0 ? d.xbase[x.a0 + chunk0] : 0) + (x.la - chunk0) + x.q * x.xsz : 0;
+    // the wavefront's largest coordination is that of its first atom (sorted);
+    // -1: no replica here (whole wavefronts past the last replica)
+    x.Mw = x.npad > 64 && __builtin_amdgcn_readfirstlane(x.q) >= x.R ? -1 : d.nnb[x.a0 + chunk0];
     return x;
 }
 
@@ -291,6 +295,7 @@ __device__ __forceinline__ void run_batched(const BArgs<S>& A, const Item& it, c
     if (MODE == MODE_EVAL && A.vel && x.active) {
         vx = (S)A.vel[orig]; vy = (S)A.vel[(size_t)N + orig]; vz = (S)A.vel[(size_t)2 * N + orig];
     }
+    __syncthreads();                                   // the records
 
     for (int step = 0; step < x.steps; ++step) {
         const int cl = x.q + step * x.R;
@@ -382,6 +387,7 @@ __device__ __forceinline__ void run_batched(const BArgs<S>& A, const Item& it, c
 }
 
 __device__ __forceinline__ void run_idle(int steps, int barriers) {
+    __syncthreads();                                   // the records
     for (int step = 0; step < steps; ++step)
         for (int b = 0; b < barriers; ++b) __syncthreads();
 }
@@ -405,20 +411,20 @@ struct ClassLo {
 };
 
 // Decode the item's parameter sets into the LDS records (all threads take part).
+// The block synchronises after its wavefronts have issued their geometry loads
+// (run_batched, run_adjoint, run_idle), so one memory round trip covers both.
 template <typename S, bool Full = false>
 __device__ __forceinline__ void decode_item(const BArgs<S>& A, const Item& it, unsigned char* lds) {
     S* pbuf = reinterpret_cast<S*>(lds);
     for (int t = threadIdx.x; t < it.nc; t += blockDim.x)
         decode_record<S, Full>(A.x + Form<Full>::nx * (size_t)(it.c0 + t), pbuf + kNParam * t);
-    __syncthreads();
 }
 
 template <typename S, int MODE, int MC, bool Full, bool Resid = false>
 __device__ __forceinline__ void batched_item(const BArgs<S>& A, const Item& it, unsigned char* lds) {
-    decode_item<S, Full>(A, it, lds);
     const ItemCtx x = item_ctx(A.set, it);
-    const int Mi = x.active ? A.set.nnb[x.atom] : -1;
-    const int Mw = wave_max_int(Mi);
+    decode_item<S, Full>(A, it, lds);
+    const int Mw = x.Mw;
     if (Mw < 0) {
         // whole wavefront outside every replica: only larger replicas have such
         // wavefronts, and they synchronise the block twice per step
@@ -451,7 +457,9 @@ template <typename S, int MODE, int MC, bool Full = false, bool Resid = false>
 __global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(WavesPerEU<S, MODE, MC>::value)))
 void k_batched(BArgs<S> A) {
     extern __shared__ __align__(32) unsigned char lds_raw[];
-    const int b0 = A.bin_off[blockIdx.x], b1 = A.bin_off[blockIdx.x + 1];
+    // without bins, block b has item b
+    const int b0 = A.bin_off ? A.bin_off[blockIdx.x] : (int)blockIdx.x;
+    const int b1 = A.bin_off ? A.bin_off[blockIdx.x + 1] : b0 + 1;
     for (int i = b0; i < b1; ++i) {
         const Item it = A.items[i];
         batched_item<S, MODE, MC, Full, Resid>(A, it, lds_raw);
@@ -771,6 +779,7 @@ __device__ __forceinline__ void run_adjoint(const BArgs<S>& A, const Item& it, c
     int jl[MM];
 #pragma unroll
     for (int m = 0; m < M; ++m) jl[m] = x.active ? d.jl[(size_t)m * N + x.atom] : x.la;
+    __syncthreads();                                   // the records
 
     for (int step = 0; step < x.steps; ++step) {
         const int cl = x.q + step * x.R;
@@ -814,10 +823,9 @@ __device__ __forceinline__ void run_adjoint(const BArgs<S>& A, const Item& it, c
 
 template <typename S, int MC, bool Full>
 __device__ __forceinline__ void adjoint_item(const BArgs<S>& A, const Item& it, unsigned char* lds) {
-    decode_item<S, Full>(A, it, lds);
     const ItemCtx x = item_ctx(A.set, it);
-    const int Mi = x.active ? A.set.nnb[x.atom] : -1;
-    const int Mw = wave_max_int(Mi);
+    decode_item<S, Full>(A, it, lds);
+    const int Mw = x.Mw;
     if (Mw < 0) {
         run_idle(x.steps, 2);
         return;
@@ -830,7 +838,9 @@ __device__ __forceinline__ void adjoint_item(const BArgs<S>& A, const Item& it, 
 template <typename S, int MC, bool Full = false>
 __global__ __launch_bounds__(512) void k_adjoint(BArgs<S> A) {
     extern __shared__ __align__(32) unsigned char lds_raw[];
-    const int b0 = A.bin_off[blockIdx.x], b1 = A.bin_off[blockIdx.x + 1];
+    // without bins, block b has item b
+    const int b0 = A.bin_off ? A.bin_off[blockIdx.x] : (int)blockIdx.x;
+    const int b1 = A.bin_off ? A.bin_off[blockIdx.x + 1] : b0 + 1;
     for (int i = b0; i < b1; ++i) {
         const Item it = A.items[i];
         adjoint_item<S, MC, Full>(A, it, lds_raw);
@@ -962,8 +972,9 @@ __global__ __launch_bounds__(256) void k_large_site(BArgs<S> A, LArgs L) {
         wave_in = (la & ~63) < Ns;
         if (wave_in) run_large_site<S, MC, E64, Full>(A, L, la, atom, active, sum, vidx, L.kmax);
     } else {
-        const int Mi = active ? d.nnb[atom] : -1;
-        const int Mw = wave_max_int(Mi);
+        // the wavefront's first atom has its largest coordination (sorted)
+        const int first = __builtin_amdgcn_readfirstlane(la & ~63);
+        const int Mw = first < Ns ? d.nnb[a0 + first] : -1;
         wave_in = Mw >= 0;
         if (wave_in)
             dispatch_m<ClassLo<MC>::value, MC>(Mw, [&](auto mv) {
@@ -1136,8 +1147,8 @@ __global__ __launch_bounds__(256) void k_large_adjoint(BArgs<S> A, LArgs L, cons
     const int la = blockIdx.x * blockDim.x + threadIdx.x;
     const bool active = la < Ns;
     const int atom = a0 + (active ? la : 0);
-    const int Mi = active ? d.nnb[atom] : -1;
-    const int Mw = wave_max_int(Mi);
+    const int first = __builtin_amdgcn_readfirstlane(la & ~63);
+    const int Mw = first < Ns ? d.nnb[a0 + first] : -1;
     __shared__ double sh[kLargeBlock / 64][8];
     double sum = 0.0, sum2 = 0.0;
     int vidx = (threadIdx.x & 63) >> 3, vidx2 = vidx;

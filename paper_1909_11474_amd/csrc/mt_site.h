@@ -550,13 +550,4 @@ __device__ __forceinline__ double group_reduce8(double* v, int g, int* vidx) {
     }
 }
 
-__device__ __forceinline__ int wave_max_int(int v) {
-#pragma unroll
-    for (int o = 32; o > 0; o >>= 1) {
-        const int y = __shfl_xor(v, o, 64);
-        v = v > y ? v : y;
-    }
-    return v;
-}
-
 }  // namespace mt
