@@ -264,12 +264,17 @@ static int eval_impl(mt_set* set, const double* x, int form, int P, int precisio
     set->fit_P = 0;
     set->cur_x = x;
     set->cur_form = form;
+    EvalOut out;
+    out.vel = vel; out.force = force; out.atom_virial = atom_virial;
+    out.energy = energy; out.virial = virial; out.heat = heat_current;
+    bool direct = false;
     if (schedule == MT_BATCHED) {
         const LaunchCfg cfg = cfg_for(set, P, precision);
-        TRY(launch_batched(set, cfg, P, precision, MODE_EVAL, vel, force, atom_virial, st));
+        TRY(launch_batched(set, cfg, P, precision, MODE_EVAL, out, st, &direct));
     } else {
-        TRY(launch_plain(set, P, precision, MODE_EVAL, vel, force, atom_virial, st));
+        TRY(launch_plain(set, P, precision, MODE_EVAL, out, st, &direct));
     }
+    if (direct) return MT_OK;
     TRY(launch_large(set, P, precision, MODE_EVAL, vel, force, atom_virial, st));
     return launch_finalize_eval(set, P, energy, virial, heat_current, st);
 }
@@ -280,9 +285,9 @@ static int fitness_sequence(mt_set* set, const double* x, int form, int P, const
     set->cur_form = form;
     if (schedule == MT_BATCHED) {
         const LaunchCfg cfg = cfg_for(set, P, precision);
-        TRY(launch_batched(set, cfg, P, precision, MODE_FIT, nullptr, nullptr, nullptr, st));
+        TRY(launch_batched(set, cfg, P, precision, MODE_FIT, EvalOut{}, st));
     } else {
-        TRY(launch_plain(set, P, precision, MODE_FIT, nullptr, nullptr, nullptr, st));
+        TRY(launch_plain(set, P, precision, MODE_FIT, EvalOut{}, st));
     }
     TRY(launch_large(set, P, precision, MODE_FIT, nullptr, nullptr, nullptr, st));
     return launch_finalize_fit(set, P, w, Z, st);
@@ -660,7 +665,7 @@ int mt_autotune(mt_set* set, int P, int precision, const char* cache_path) {
         auto gen = [&]() -> int {
             if (have_ref)
                 return fitness_sequence(set, xb.as<double>(), 0, P, wt, precision, MT_BATCHED, zb.as<double>(), st);
-            return launch_batched(set, c, P, precision, MODE_FIT, nullptr, nullptr, nullptr, st);
+            return launch_batched(set, c, P, precision, MODE_FIT, EvalOut{}, st);
         };
         if (gen() != MT_OK) continue;
         float tmin = 1e30f;

@@ -37,6 +37,9 @@ namespace mt {
 
 constexpr int kMaxNbr = 16;        // template limit on coordination
 constexpr int kMaxBatched = 512;   // largest structure of the batched kernel
+// LDS in front of a batched block's records: the sums of up to eight wavefronts,
+// sixteen values each.
+constexpr int kRedBytes = 8 * 16 * 8;
 // Threads per block of the two-pass kernels; a structure over the batching
 // limit has one partial-sum slot per such block.
 constexpr int kLargeBlock = 256;

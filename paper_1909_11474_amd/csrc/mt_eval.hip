@@ -474,7 +474,7 @@ size_t item_lds(const mt_set* set, int s, int block, int fam, int nc) {
     const size_t e = (size_t)family_elem(fam);
     const size_t par = ((size_t)nc * kNParam * e + 31) & ~(size_t)31;
     const size_t slots = family_adjoint(fam) ? (size_t)npad : (size_t)set->h_xsize[s];
-    return par + (size_t)R * slots * 4 * e;
+    return kRedBytes + par + (size_t)R * slots * 4 * e;
 }
 
 hipError_t launch_family(int fam, int mc, dim3 g, dim3 b, size_t lds, hipStream_t st,
@@ -862,8 +862,8 @@ static int launch_twopass(mt_set* set, const std::vector<int>& structs, int P, i
                           int mode, const double* vel, double* force, double* atom_virial,
                           hipStream_t st);
 
-int launch_batched(mt_set* set, const LaunchCfg& cfg, int P, int precision, int mode,
-                   const double* vel, double* force, double* atom_virial, hipStream_t st) {
+int launch_batched(mt_set* set, const LaunchCfg& cfg, int P, int precision, int mode, const EvalOut& out,
+                   hipStream_t st, bool* direct) {
     if (precision != MT_FP64) TRY_RC(float_tables(set, st));
     const int fam = family_for(precision, mode, set->cur_form);
     ItemPlan* plan = get_plan(set, P, cfg, fam);
@@ -874,17 +874,26 @@ int launch_batched(mt_set* set, const LaunchCfg& cfg, int P, int precision, int 
     const int nv = mode == MODE_FIT ? kNVFit : kNVEval;
     BArgs<float> Af = make_args<float>(set, set->partial.as<double>(), nv);
     BArgs<double> Ad = make_args<double>(set, set->partial.as<double>(), nv);
-    Af.vel = Ad.vel = vel;
-    Af.force = Ad.force = force;
-    Af.atom_virial = Ad.atom_virial = atom_virial;
+    Af.vel = Ad.vel = out.vel;
+    Af.force = Ad.force = out.force;
+    Af.atom_virial = Ad.atom_virial = out.atom_virial;
     if (mode == MODE_FIT && set->grad_resid) {
         Af.resid = static_cast<float*>(set->grad_resid);
         Ad.resid = static_cast<double*>(set->grad_resid);
     }
+    // a block holds whole structures, so their energies and virials are final (the
+    // finalize kernel is another 4 us of a 12 us call);
+    // only the heat current adds up structures, and the two-pass path blocks
+    if (mode == MODE_EVAL && direct && !out.heat && set->n_large == 0 && plan->twopass.empty()) {
+        *direct = true;
+        Af.direct = Ad.direct = 1;
+        Af.energy = Ad.energy = out.energy;
+        Af.virial = Ad.virial = out.virial;
+    }
     TRY_RC(run_plan(set, plan, cfg, fam, Af, Ad, 0, st));
     if (plan->twopass.empty()) return MT_OK;
     TRY_RC(reserve_twopass(set, plan, P, precision));     // no-op once reserved
-    return launch_twopass(set, plan->twopass, P, precision, mode, vel, force, atom_virial, st);
+    return launch_twopass(set, plan->twopass, P, precision, mode, out.vel, out.force, out.atom_virial, st);
 }
 
 int launch_plan_fit(mt_set* set, ItemPlan* plan, const LaunchCfg& cfg, int precision, double* partial,
@@ -896,10 +905,9 @@ int launch_plan_fit(mt_set* set, ItemPlan* plan, const LaunchCfg& cfg, int preci
     return run_plan(set, plan, cfg, fam, Af, Ad, -1, st);
 }
 
-int launch_plain(mt_set* set, int P, int precision, int mode, const double* vel, double* force,
-                 double* atom_virial, hipStream_t st) {
+int launch_plain(mt_set* set, int P, int precision, int mode, const EvalOut& out, hipStream_t st, bool* direct) {
     LaunchCfg plain;      // block = 0
-    return launch_batched(set, plain, P, precision, mode, vel, force, atom_virial, st);
+    return launch_batched(set, plain, P, precision, mode, out, st, direct);
 }
 
 // reps back-to-back passes of the batched fitness kernels (the launches of
@@ -1014,11 +1022,41 @@ int reserve_twopass(mt_set* set, const ItemPlan* plan, int P, int precision) {
         if (set->h_large[s]) add(s);
     if (plan)
         for (int s : plan->twopass) add(s);
-    // a captured fitness graph holds the buffer's address in its two-pass
-    // launches: growing the buffer frees that memory, so those graphs go too
-    const void* before = set->gbuf.p;
+    // a captured fitness graph holds the buffers' addresses in its two-pass
+    // launches: growing a buffer frees that memory, so those graphs go too
+    const void *before = set->gbuf.p, *before_part = set->tpart.p;
     if (need) HIPCHECK(set->gbuf.reserve(need));
-    if (set->gbuf.p != before) clear_graphs(set);
+    if (plan && !plan->twopass.empty())
+        HIPCHECK(set->tpart.reserve(sizeof(double) * (size_t)P * (kMaxBatched / kLargeBlock) * kNVEval));
+    if (set->gbuf.p != before || set->tpart.p != before_part) clear_graphs(set);
+    return MT_OK;
+}
+
+// Sums of a batched structure's two-pass blocks, in block order, into its slot:
+// values 0 .. nval - 1 of each candidate.
+__global__ __launch_bounds__(256) void k_sum_blocks(const double* __restrict__ part, int nblk, int nv, int nval,
+                                                    int P, double* __restrict__ out, int nslots, int slot) {
+    const int idx = blockIdx.x * blockDim.x + threadIdx.x;
+    const int c = idx / nv, k = idx % nv;
+    if (c >= P || k >= nval) return;
+    double t = 0.0;
+    for (int b = 0; b < nblk; ++b) t += part[((size_t)c * nblk + b) * nv + k];
+    out[((size_t)c * nslots + slot) * nv + k] = t;
+}
+
+// Where the partial sums of structure s's two-pass blocks go.
+static void place_sums(mt_set* set, int s, double* partial, LArgs& L) {
+    const int ns = set->h_off[s + 1] - set->h_off[s];
+    L.part = set->h_large[s] ? partial : set->tpart.as<double>();
+    L.pslots = set->h_large[s] ? set->nslots : grid_of(ns, kLargeBlock);
+    L.slot0 = set->h_large[s] ? set->h_slot[s] : 0;
+}
+static int finish_sums(mt_set* set, int s, int P, double* partial, int nv, int nval, hipStream_t st) {
+    if (set->h_large[s]) return MT_OK;
+    const int nblk = grid_of(set->h_off[s + 1] - set->h_off[s], kLargeBlock);
+    hipLaunchKernelGGL(k_sum_blocks, dim3(grid_of((long long)P * nv, 256)), dim3(256), 0, st, set->tpart.as<double>(),
+                       nblk, nv, nval, P, partial, set->nslots, set->h_slot[s]);
+    HIPCHECK(hipGetLastError());
     return MT_OK;
 }
 
@@ -1042,8 +1080,9 @@ static int launch_twopass_t(mt_set* set, const std::vector<int>& structs, int P,
         }
         for (int c0 = 0; c0 < P; c0 += chunk) {
             const int nc = std::min(chunk, P - c0);
-            LArgs L{s, c0, set->gbuf.p, set->h_large[s] ? 1 : 0, set->h_off[s], set->h_off[s + 1] - set->h_off[s],
-                    set->h_boff[s + 1] - set->h_boff[s], set->h_slot[s], set->h_kmax[s]};
+            LArgs L{s, c0, set->gbuf.p, nullptr, 0, set->h_off[s], ns, set->h_boff[s + 1] - set->h_boff[s], 0,
+                    set->h_kmax[s]};
+            place_sums(set, s, set->partial.as<double>(), L);
             dim3 grid(grid_of(ns, kLargeBlock), nc);
             hipError_t e;
             if constexpr (std::is_same<S, double>::value)
@@ -1052,6 +1091,7 @@ static int launch_twopass_t(mt_set* set, const std::vector<int>& structs, int P,
                 e = launch_large32(mc, mode, set->cur_form, grid, dim3(kLargeBlock), st, A, L);
             HIPCHECK(e);
         }
+        TRY_RC(finish_sums(set, s, P, set->partial.as<double>(), nv, mode == MODE_FIT ? 8 : 11, st));
     }
     return MT_OK;
 }
@@ -1158,8 +1198,9 @@ static int launch_twopass_adjoint(mt_set* set, const std::vector<int>& structs, 
         }
         for (int c0 = 0; c0 < P; c0 += chunk) {
             const int nc = std::min(chunk, P - c0);
-            LArgs L{s, c0, set->gbuf.p, set->h_large[s] ? 1 : 0, set->h_off[s], set->h_off[s + 1] - set->h_off[s],
-                    set->h_boff[s + 1] - set->h_boff[s], set->h_slot[s], set->h_kmax[s]};
+            LArgs L{s, c0, set->gbuf.p, nullptr, 0, set->h_off[s], ns, set->h_boff[s + 1] - set->h_boff[s], 0,
+                    set->h_kmax[s]};
+            place_sums(set, s, set->partial2.as<double>(), L);
             dim3 grid(grid_of(ns, kLargeBlock), nc);
             hipError_t e;
             if constexpr (std::is_same<S, double>::value)
@@ -1170,6 +1211,8 @@ static int launch_twopass_adjoint(mt_set* set, const std::vector<int>& structs, 
                                        set->abuf.as<float>());
             HIPCHECK(e);
         }
+        TRY_RC(finish_sums(set, s, P, set->partial2.as<double>(), nv,
+                           set->cur_form ? GradSums<true>::value : GradSums<false>::value, st));
     }
     return MT_OK;
 }

@@ -161,6 +161,7 @@ struct mt_set {
     void* grad_resid = nullptr;
     mt::DevBuf zwork;                        // [P][4] scratch for fitness_grad
     mt::DevBuf gbuf;                         // large path bond gradients
+    mt::DevBuf tpart;                        // block sums of batched structures on the two-pass path
     mt::DevBuf scalars;                      // small device scratch
     mt::BuildScratch build;                  // neighbour-search temporaries
 
@@ -197,10 +198,17 @@ int update_geometry(mt_set* set, const double* pos, hipStream_t stream);
 void clear_graphs(mt_set* set);
 
 // mt_eval.hip
-int launch_batched(mt_set* set, const LaunchCfg& cfg, int P, int precision, int mode,
-                   const double* vel, double* force, double* atom_virial, hipStream_t stream);
-int launch_plain(mt_set* set, int P, int precision, int mode, const double* vel, double* force,
-                 double* atom_virial, hipStream_t stream);
+// Outputs of an evaluation (MODE_EVAL), each null where not wanted.
+struct EvalOut {
+    const double* vel = nullptr;
+    double *force = nullptr, *atom_virial = nullptr, *energy = nullptr, *virial = nullptr, *heat = nullptr;
+};
+// direct (evaluations): set when the kernels wrote energy and virial themselves
+// and no finalize is needed.
+int launch_batched(mt_set* set, const LaunchCfg& cfg, int P, int precision, int mode, const EvalOut& out,
+                   hipStream_t stream, bool* direct = nullptr);
+int launch_plain(mt_set* set, int P, int precision, int mode, const EvalOut& out, hipStream_t stream,
+                 bool* direct = nullptr);
 // Average time of reps back-to-back passes of the batched fitness kernels.
 int time_batched_kernels(mt_set* set, const LaunchCfg& cfg, int P, int precision, int reps,
                          hipStream_t stream, double* ms, int64_t* launches);

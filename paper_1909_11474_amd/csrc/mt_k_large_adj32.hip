@@ -15,7 +15,9 @@ static hipError_t large_adj(dim3 g, dim3 b, hipStream_t st, const BArgs<float>& 
 
 hipError_t launch_large_adj32(int mc, int full, dim3 g, dim3 b, hipStream_t st, const BArgs<float>& Afit,
                               const BArgs<float>& Aadj, const LArgs& L, float* abuf) {
-    const hipError_t e = launch_large32(mc, MODE_STAGE, full, g, b, st, Afit, L);
+    LArgs stage = L;
+    stage.part = nullptr;          // staged bond gradients only
+    const hipError_t e = launch_large32(mc, MODE_STAGE, full, g, b, st, Afit, stage);
     if (e != hipSuccess) return e;
     if (full) return launch_large_adj32f(mc, g, b, st, Aadj, L, abuf);
     if (mc == 4) return large_adj<4>(g, b, st, Aadj, L, abuf);

@@ -143,6 +143,11 @@ struct BArgs {
     double* force;            // [P][3][N]
     double* atom_virial;      // [P][9][N]
     const double* vel;        // [3][N]
+    // MODE_EVAL without a finalize kernel: the totals go straight to energy
+    // [P][S] and virial [P][S][6] (either may be null)
+    int direct;
+    double* energy;
+    double* virial;
     // adjoint inputs
     const double* coef;       // [P][S][8]
     // force residuals F - F* of the batched atoms, [P][3][N] (sorted atom
@@ -164,7 +169,7 @@ template <>
 __device__ __forceinline__ const double* fref_of<double>(const SetDev& d) { return d.fref64; }
 
 struct ItemCtx {
-    int s, a0, Ns, npad, R, q, la, atom, steps, slot, g, xsz, own, Mw;
+    int s, a0, Ns, npad, R, q, la, atom, steps, slot, g, xsz, own, Mw, unit, wpr;
     bool active, block_sync;
 };
 
@@ -183,6 +188,8 @@ __device__ __forceinline__ ItemCtx item_ctx(const SetDev& d, const Item& it) {
         x.q = tid >> sh;
         x.la = tid & (x.npad - 1);
         x.g = x.npad;
+        x.unit = 0;
+        x.wpr = 1;
     } else {
         const int wpr = x.npad >> 6;                       // wavefronts per replica
         const int wid = __builtin_amdgcn_readfirstlane(tid >> 6);
@@ -197,6 +204,8 @@ __device__ __forceinline__ ItemCtx item_ctx(const SetDev& d, const Item& it) {
         const int row = wid & ~3, in_row = (nw - row) < 4 ? nw - row : 4;
         const int rank = (row & 4) ? row + in_row - 1 - (wid - row) : wid;
         const int chunk = rank / x.R;                      // scalar division
+        x.unit = rank;
+        x.wpr = wpr;
         x.q = chunk < wpr ? rank - chunk * x.R : x.R;
         x.la = (chunk < wpr ? chunk << 6 : 0) + (tid & 63);
         x.g = 64;
@@ -204,7 +213,7 @@ __device__ __forceinline__ ItemCtx item_ctx(const SetDev& d, const Item& it) {
     x.active = (x.q < x.R) && (x.la < x.Ns);
     x.atom = x.a0 + (x.active ? x.la : 0);
     x.steps = (it.nc + x.R - 1) / x.R;
-    x.slot = it.slot + (x.npad > 64 ? (x.la >> 6) : 0);
+    x.slot = it.slot;
     x.xsz = it.xsz;
     x.block_sync = x.npad > 64;
     // own exchange slot base: the first chunk's slots start at 0, and a chunk's
@@ -229,21 +238,51 @@ __device__ __forceinline__ void exchange_sync(bool block) {
     }
 }
 
-// Store the group sums of v[0..7] into partial[c][slot][off + vidx].  GF is
-// the group size when known at compile time (0: x.g at run time).
-template <int GF = 0>
-__device__ __forceinline__ void store_group(double* v, const ItemCtx& x, bool group_ok,
-                                            double* __restrict__ partial, int nslots, int nv,
-                                            int c, int off, int wmask) {
+// One structure total of candidate c: value k of the partial-sum slot, or, for
+// an evaluation that needs no more, the energy or virial itself.
+template <int MODE, typename S>
+__device__ __forceinline__ void put_sum(const BArgs<S>& A, const ItemCtx& x, int c, int k, double sum, bool valid) {
+    if (MODE == MODE_EVAL && A.direct) {
+        const double v = valid ? sum : __longlong_as_double(0x7ff8000000000000ll);
+        const size_t cs = (size_t)c * A.set.S + x.s;
+        if (k == 0 && A.energy) A.energy[cs] = v;
+        if (k >= 1 && k <= 6 && A.virial) A.virial[cs * 6 + k - 1] = v;
+    } else {
+        A.partial[((size_t)c * A.set.nslots + x.slot) * A.nv + k] = sum;
+    }
+}
+
+// Sum v[0..7] over the lane group.  A replica inside one wavefront is done
+// (put_sum); the wavefronts of a larger one leave their sums, values off ..
+// off + 7 of those in wmask, in red[unit] for flush_sums.  GF is the group size
+// when known at compile time (0: x.g at run time).
+template <int MODE, int NV, int GF = 0, int SYNC = -1, typename S>
+__device__ __forceinline__ void store_group(double* v, const BArgs<S>& A, const ItemCtx& x, bool group_ok, int c,
+                                            int off, int wmask, bool valid, double* __restrict__ red) {
     int vidx;
     const double sum = GF ? group_reduce8_t<(GF ? GF : 64)>(v, &vidx) : group_reduce8(v, x.g, &vidx);
     const int lane = threadIdx.x & 63;
-    if (group_ok && (lane & ((x.g >> 3) - 1)) == 0 && ((wmask >> vidx) & 1))
-        partial[((size_t)c * nslots + x.slot) * nv + off + vidx] = sum;
+    if ((lane & ((x.g >> 3) - 1)) == 0 && ((wmask >> vidx) & 1)) {
+        if (SYNC < 0 ? x.block_sync : SYNC == 1) red[x.unit * NV + off + vidx] = sum;
+        else if (group_ok) put_sum<MODE>(A, x, c, off + vidx, sum, valid);
+    }
 }
 
-// LDS layout of a block while it works on an item: [it.nc x kNParam parameter
-// records][R x xsz exchange slots (Vec4); adjoint: R x npad force residuals
+// Total of a structure of several wavefronts for candidate c: the wavefronts'
+// sums in chunk order, by the replica's last (cheapest) wavefront.  Called one
+// block barrier after the store_group that left them, and one before the next.
+template <int MODE, int NV, typename S>
+__device__ __forceinline__ void flush_sums(const BArgs<S>& A, const ItemCtx& x, int c, int nval, bool valid,
+                                           const double* __restrict__ red) {
+    const int lane = threadIdx.x & 63;
+    if (x.unit / x.R != x.wpr - 1 || lane >= nval) return;
+    double t = 0.0;
+    for (int w = 0; w < x.wpr; ++w) t += red[(w * x.R + x.q) * NV + lane];
+    put_sum<MODE>(A, x, c, lane, t, valid);
+}
+
+// LDS layout of a block while it works on an item: [kRedBytes of wavefront
+// sums][it.nc x kNParam parameter records][R x xsz exchange slots (Vec4); adjoint: R x npad force residuals
 // (Vec4) instead].  The exchange follows the item's own records, so the LDS a launch
 // gets for the largest (records + exchange) of its structures covers every
 // item, whatever the candidate tiles of the other structures in the launch.
@@ -268,14 +307,19 @@ struct ParkSlots {
     }
 };
 
+// SYNC: 1 the replicas span several wavefronts, 0 each lies inside one, -1 known
+// at run time only (x.block_sync).
 // Resid (fitness mode): also write each atom's force residual to A.resid (the
 // gradient's fitness call; a separate instance, so the fitness alone carries
 // no trace of it).
-template <typename S, int MODE, int M, int GF = 0, bool Full = false, bool Resid = false>
+template <typename S, int MODE, int M, int GF = 0, int SYNC = -1, bool Full = false, bool Resid = false>
 __device__ __forceinline__ void run_batched(const BArgs<S>& A, const Item& it, const ItemCtx& x,
                                             unsigned char* __restrict__ lds) {
     const SetDev& d = A.set;
     const int N = d.N;
+    constexpr int NV = MODE == MODE_FIT ? kNVFit : kNVEval;
+    const bool sync = SYNC < 0 ? x.block_sync : SYNC == 1;
+    double* __restrict__ red = reinterpret_cast<double*>(lds - kRedBytes);
     const S* __restrict__ pbuf = reinterpret_cast<const S*>(lds);
     Vec4<S>* __restrict__ xb = reinterpret_cast<Vec4<S>*>(lds + lds_param_bytes<S>(it.nc));
     Geo<S, M, Full> g;
@@ -296,6 +340,12 @@ __device__ __forceinline__ void run_batched(const BArgs<S>& A, const Item& it, c
         vx = (S)A.vel[orig]; vy = (S)A.vel[(size_t)N + orig]; vz = (S)A.vel[(size_t)2 * N + orig];
     }
     __syncthreads();                                   // the records
+    // the structure totals of a step, once its wavefronts' sums are all there
+    auto flush = [&](int step) __attribute__((always_inline)) {
+        const int cl = x.q + step * x.R;
+        if (cl < it.nc)
+            flush_sums<MODE, NV>(A, x, it.c0 + cl, MODE == MODE_FIT ? 8 : 11, pbuf[kNParam * cl + P_VALID] != S(0), red);
+    };
 
     for (int step = 0; step < x.steps; ++step) {
         const int cl = x.q + step * x.R;
@@ -325,7 +375,8 @@ __device__ __forceinline__ void run_batched(const BArgs<S>& A, const Item& it, c
                 w6[3] -= dy * gz; w6[4] -= dz * gx; w6[5] -= dx * gy;
             },
             ParkSlots<S>{xb + x.own, x.g});
-        exchange_sync(x.block_sync);
+        exchange_sync(sync);
+        if (sync && step > 0) flush(step - 1);
         S wi[9];
 #pragma unroll
         for (int k = 0; k < 9; ++k) wi[k] = S(0);
@@ -342,7 +393,7 @@ __device__ __forceinline__ void run_batched(const BArgs<S>& A, const Item& it, c
                 wi[6] += dz * r.x; wi[7] += dz * r.y; wi[8] += dz * r.z;
             }
         }
-        exchange_sync(x.block_sync);
+        exchange_sync(sync);
         // Lanes outside the structure have zero geometry and zero reference
         // forces, so their energy, virial and residual are exactly zero.
         double v[8];
@@ -358,10 +409,10 @@ __device__ __forceinline__ void run_batched(const BArgs<S>& A, const Item& it, c
                 r[(size_t)N + x.atom] = ay;
                 r[(size_t)2 * N + x.atom] = az;
             }
-            store_group<GF>(v, x, group_ok, A.partial, d.nslots, A.nv, c, 0, 0xff);
+            store_group<MODE, NV, GF, SYNC>(v, A, x, group_ok, c, 0, 0xff, true, red);
         } else {
             v[7] = 0.0;
-            store_group<GF>(v, x, group_ok, A.partial, d.nslots, A.nv, c, 0, 0xff);
+            store_group<MODE, NV, GF, SYNC>(v, A, x, group_ok, c, 0, 0xff, p.valid != S(0), red);
             double u[8];
             const S jx = wi[0] * vx + wi[1] * vy + wi[2] * vz;
             const S jy = wi[3] * vx + wi[4] * vy + wi[5] * vz;
@@ -370,7 +421,7 @@ __device__ __forceinline__ void run_batched(const BArgs<S>& A, const Item& it, c
             u[1] = (double)jy;
             u[2] = (double)jz;
             u[3] = u[4] = u[5] = u[6] = u[7] = 0.0;
-            store_group<GF>(u, x, group_ok, A.partial, d.nslots, A.nv, c, 8, 0x07);
+            store_group<MODE, NV, GF, SYNC>(u, A, x, group_ok, c, 8, 0x07, p.valid != S(0), red);
             if (cok && A.force) {
                 double* f = A.force + (size_t)c * 3 * N;
                 f[orig] = (double)Fx;
@@ -384,12 +435,17 @@ __device__ __forceinline__ void run_batched(const BArgs<S>& A, const Item& it, c
             }
         }
     }
+    if (sync) {
+        __syncthreads();
+        flush(x.steps - 1);
+    }
 }
 
 __device__ __forceinline__ void run_idle(int steps, int barriers) {
     __syncthreads();                                   // the records
     for (int step = 0; step < steps; ++step)
         for (int b = 0; b < barriers; ++b) __syncthreads();
+    __syncthreads();                                   // the last step's sums
 }
 
 // Call f(integral_constant<M>) for the variant that serves coordination m.
@@ -432,17 +488,25 @@ __device__ __forceinline__ void batched_item(const BArgs<S>& A, const Item& it, 
         return;
     }
     dispatch_m<ClassLo<MC>::value, MC>(Mw, [&](auto mv) {
-        // the float fitness kernel of the minimal potential gets a copy with
-        // 64-lane groups (structures of 64 atoms or more) fixed at compile
-        // time: the reduction then needs no branches and no copies around the
-        // in-place lane swaps
+        // the float fitness kernel of the minimal potential gets copies for
+        // structures of several wavefronts and (M <= 4) of one: with the group
+        // size and the kind of exchange fixed at compile time the reduction
+        // needs no branches and no copies around the in-place lane swaps
         if constexpr (MODE == MODE_FIT && sizeof(S) == 4 && !Full) {
-            if (x.g == 64) {
-                run_batched<S, MODE, decltype(mv)::value, 64, Full, Resid>(A, it, x, lds);
+            if (x.block_sync) {
+                run_batched<S, MODE, decltype(mv)::value, 64, 1, Full, Resid>(A, it, x, lds);
                 return;
             }
+            if constexpr (MC <= 4) {
+                if (x.g == 64) {
+                    run_batched<S, MODE, decltype(mv)::value, 64, 0, Full, Resid>(A, it, x, lds);
+                    return;
+                }
+            }
+            run_batched<S, MODE, decltype(mv)::value, 0, 0, Full, Resid>(A, it, x, lds);
+            return;
         }
-        run_batched<S, MODE, decltype(mv)::value, 0, Full, Resid>(A, it, x, lds);
+        run_batched<S, MODE, decltype(mv)::value, 0, -1, Full, Resid>(A, it, x, lds);
     });
 }
 
@@ -462,7 +526,7 @@ void k_batched(BArgs<S> A) {
     const int b1 = A.bin_off ? A.bin_off[blockIdx.x + 1] : b0 + 1;
     for (int i = b0; i < b1; ++i) {
         const Item it = A.items[i];
-        batched_item<S, MODE, MC, Full, Resid>(A, it, lds_raw);
+        batched_item<S, MODE, MC, Full, Resid>(A, it, lds_raw + kRedBytes);
         __syncthreads();
     }
 }
@@ -474,7 +538,7 @@ template <typename S, int MODE, int MC, bool Full = false>
 __global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(WavesPerEU<S, MODE, MC>::value)))
 void k_plain(BArgs<S> A) {
     extern __shared__ __align__(32) unsigned char lds_raw[];
-    batched_item<S, MODE, MC, Full>(A, A.items[0], lds_raw);
+    batched_item<S, MODE, MC, Full>(A, A.items[0], lds_raw + kRedBytes);
 }
 
 // ---------------------------------------------------------------------------
@@ -776,10 +840,16 @@ __device__ __forceinline__ void run_adjoint(const BArgs<S>& A, const Item& it, c
     g.load(d, x.atom, x.active);
     constexpr int MM = M > 0 ? M : 1;
     constexpr int NL = GradSums<Full>::value;
+    constexpr int NV = Full ? kNVGradTF : kNVGrad;
+    double* __restrict__ red = reinterpret_cast<double*>(lds - kRedBytes);
     int jl[MM];
 #pragma unroll
     for (int m = 0; m < M; ++m) jl[m] = x.active ? d.jl[(size_t)m * N + x.atom] : x.la;
     __syncthreads();                                   // the records
+    auto flush = [&](int step) __attribute__((always_inline)) {
+        const int cl = x.q + step * x.R;
+        if (cl < it.nc) flush_sums<MODE_FIT, NV>(A, x, it.c0 + cl, NL, true, red);
+    };
 
     for (int step = 0; step < x.steps; ++step) {
         const int cl = x.q + step * x.R;
@@ -796,6 +866,7 @@ __device__ __forceinline__ void run_adjoint(const BArgs<S>& A, const Item& it, c
         }
         ab[x.la] = Vec4<S>{ax, ay, az, S(0)};
         exchange_sync(x.block_sync);
+        if (x.block_sync && step > 0) flush(step - 1);
         S L[NL];
         adjoint_sums<S, M, Full>(
             g, prec, ax, ay, az,
@@ -810,14 +881,18 @@ __device__ __forceinline__ void run_adjoint(const BArgs<S>& A, const Item& it, c
         double v[8];
 #pragma unroll
         for (int k = 0; k < 8; ++k) v[k] = k < NL ? (double)L[k < NL ? k : 0] : 0.0;
-        store_group(v, x, group_ok, A.partial, d.nslots, A.nv, c, 0, Full ? 0xff : 0x7f);
+        store_group<MODE_FIT, NV>(v, A, x, group_ok, c, 0, Full ? 0xff : 0x7f, true, red);
         if constexpr (Full) {
             double u[8];
             u[0] = (double)L[8];
 #pragma unroll
             for (int k = 1; k < 8; ++k) u[k] = 0.0;
-            store_group(u, x, group_ok, A.partial, d.nslots, A.nv, c, 8, 0x01);
+            store_group<MODE_FIT, NV>(u, A, x, group_ok, c, 8, 0x01, true, red);
         }
+    }
+    if (x.block_sync) {
+        __syncthreads();
+        flush(x.steps - 1);
     }
 }
 
@@ -843,7 +918,7 @@ __global__ __launch_bounds__(512) void k_adjoint(BArgs<S> A) {
     const int b1 = A.bin_off ? A.bin_off[blockIdx.x + 1] : b0 + 1;
     for (int i = b0; i < b1; ++i) {
         const Item it = A.items[i];
-        adjoint_item<S, MC, Full>(A, it, lds_raw);
+        adjoint_item<S, MC, Full>(A, it, lds_raw + kRedBytes);
         __syncthreads();
     }
 }
@@ -871,31 +946,25 @@ struct Stage4<double> {
 struct LArgs {
     int s, c0;                 // structure, first candidate of the chunk
     void* gbuf;                // [chunk][nbs] of Stage4<S> (x, y, z, unused)
-    // 1: the structure has one partial-sum slot per block (a structure over
-    // the batching limit); 0: one per wavefront (a batched structure sent to
-    // the two-pass path)
-    int per_block;
+    // where the blocks' partial sums go, [candidate][pslots][nv] (null: nowhere):
+    // the set's slots, one per block of a structure over the batching limit, or
+    // a buffer of their own that k_sum_blocks adds up (a batched structure sent
+    // to the two-pass path has one slot)
+    double* part;
+    int pslots;
     // the structure's first atom, atom count, bond count, first partial-sum
     // slot and largest coordination, copied from the host tables so no kernel
     // waits on reading them
     int a0, ns, nbs, slot0, kmax;
 };
 
-// Store a wavefront's group sums (lanes with (lane & 7) == 0 hold value vidx)
-// in the structure's partial-sum slots, values off + k for the k set in mask:
-// per wavefront (wavefronts past the structure, wave_in false, write
-// nothing), or per block, the block's wavefront sums added in wavefront order
-// through LDS.  Every thread of the block calls it; a wavefront with no atom
-// passes sum = 0 and vidx = (lane >> 3).
-__device__ __forceinline__ void large_store(const SetDev& d, const LArgs& L, double* __restrict__ partial,
-                                            int nv, int c, int la, bool wave_in, double sum, int vidx,
-                                            unsigned mask, int off, double (*sh)[8]) {
+// Store a block's sums, values off + k for the k set in mask: its wavefronts'
+// group sums (lanes with (lane & 7) == 0 hold value vidx) added in wavefront
+// order through LDS.  Every thread of the block calls it; a wavefront with no
+// atom passes sum = 0 and vidx = (lane >> 3).
+__device__ __forceinline__ void large_store(const LArgs& L, int nv, int c, double sum, int vidx, unsigned mask,
+                                            int off, double (*sh)[8]) {
     const int lane = threadIdx.x & 63;
-    if (!L.per_block) {
-        if (wave_in && (lane & 7) == 0 && ((mask >> vidx) & 1))
-            partial[((size_t)c * d.nslots + L.slot0 + (la >> 6)) * nv + off + vidx] = sum;
-        return;
-    }
     const int w = threadIdx.x >> 6, nw = blockDim.x >> 6;
     if ((lane & 7) == 0) sh[w][vidx] = sum;
     __syncthreads();
@@ -903,7 +972,7 @@ __device__ __forceinline__ void large_store(const SetDev& d, const LArgs& L, dou
     if (k < 8 && ((mask >> k) & 1)) {
         double t = sh[0][k];
         for (int q = 1; q < nw; ++q) t += sh[q][k];
-        partial[((size_t)c * d.nslots + L.slot0 + blockIdx.x) * nv + off + k] = t;
+        L.part[((size_t)c * L.pslots + L.slot0 + blockIdx.x) * nv + off + k] = t;
     }
     __syncthreads();
 }
@@ -982,8 +1051,7 @@ __global__ __launch_bounds__(256) void k_large_site(BArgs<S> A, LArgs L) {
             });
     }
     // no partial sums when only the staged bond gradients are wanted
-    if (A.partial)
-        large_store(d, L, A.partial, A.nv, L.c0 + blockIdx.y, la, wave_in, sum, vidx, 0x7f, 0, sh);
+    if (L.part) large_store(L, A.nv, L.c0 + blockIdx.y, sum, vidx, 0x7f, 0, sh);
 }
 
 template <typename S, int MODE, int MC>
@@ -1043,7 +1111,7 @@ __global__ __launch_bounds__(256) void k_large_gather(BArgs<S> A, LArgs L) {
             v[7] = (double)(ax * ax + ay * ay + az * az);
         }
         const double sum = group_reduce8(v, 64, &vidx);
-        large_store(d, L, A.partial, A.nv, c, la, wave_in, sum, vidx, 0x80, 0, sh);
+        large_store(L, A.nv, c, sum, vidx, 0x80, 0, sh);
     } else {
         if (active && A.vel) {
             const S vx = (S)A.vel[orig], vy = (S)A.vel[(size_t)N + orig], vz = (S)A.vel[(size_t)2 * N + orig];
@@ -1052,7 +1120,7 @@ __global__ __launch_bounds__(256) void k_large_gather(BArgs<S> A, LArgs L) {
             v[2] = (double)(wi[6] * vx + wi[7] * vy + wi[8] * vz);
         }
         const double sum = group_reduce8(v, 64, &vidx);
-        large_store(d, L, A.partial, A.nv, c, la, wave_in, sum, vidx, 0x07, 8, sh);
+        large_store(L, A.nv, c, sum, vidx, 0x07, 8, sh);
         if (active && A.force) {
             double* f = A.force + (size_t)c * 3 * N;
             f[orig] = (double)Fx; f[(size_t)N + orig] = (double)Fy; f[(size_t)2 * N + orig] = (double)Fz;
@@ -1165,8 +1233,8 @@ __global__ __launch_bounds__(256) void k_large_adjoint(BArgs<S> A, LArgs L, cons
         }
     }
     const int c = L.c0 + blockIdx.y;
-    large_store(d, L, A.partial, A.nv, c, la, Mw >= 0, sum, vidx, Full ? 0xffu : 0x7fu, 0, sh);
-    if constexpr (Full) large_store(d, L, A.partial, A.nv, c, la, Mw >= 0, sum2, vidx2, 0x01, 8, sh);
+    large_store(L, A.nv, c, sum, vidx, Full ? 0xffu : 0x7fu, 0, sh);
+    if constexpr (Full) large_store(L, A.nv, c, sum2, vidx2, 0x01, 8, sh);
 }
 
 // Launchers, one per kernel family (defined in the mt_k_*.hip units).

@@ -750,7 +750,7 @@ int build_set(mt_set* set, const int64_t* atom_offset, const double* pos, const 
         const bool large = set->h_large[s] != 0;
         const int npad = set->h_npad[s];
         // over the batching limit: one slot per block of the two-pass kernels
-        const int nsl = large ? (ns + kLargeBlock - 1) / kLargeBlock : std::max(1, npad / 64);
+        const int nsl = large ? (ns + kLargeBlock - 1) / kLargeBlock : 1;
         set->h_slot[s + 1] = set->h_slot[s] + nsl;
         if (large) ++set->n_large; else ++set->n_batched;
     }
