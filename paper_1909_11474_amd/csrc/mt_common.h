@@ -49,44 +49,25 @@ constexpr int kNVEval = 16;        // E, W6, |F-F*|^2, J3, unused
 // Tersoff form's nine, seven unused.
 constexpr int kNVGrad = 8;
 constexpr int kNVGradTF = 16;
-constexpr int kNParam = 26;        // per-candidate decoded parameter record (25 used)
 
-// Decoded parameter record (float or double), filled per work item in LDS.
-// Both potential forms share it: f_R = DR e^{-lambda (r - r0)},
-// f_A = DA e^{-mu (r - r0)} with lambda = alpha sqrt(2S), mu = alpha sqrt(2/S),
-// DR = D0/(S-1), DA = S D0/(S-1) (Sec. II.B Eqs. 11-14; S = 2 in the minimal
-// potential); zeta = ZS sum_k f_C g(theta) with g = (cos - h)^2 and ZS = beta
-// (minimal), or g = g^T = gamma + K t^2 / (d^2 + t^2), t = cos - h,
-// K = gamma c^2 / d^2 and ZS = 1 (Tersoff form, Sec. II.A Eq. 8).
-enum ParamIndex {
-    P_AA = 0,       // mu log2(e)
-    P_R0HI = 1,     // r0 (float: high part)
-    P_R0LO = 2,     // r0 - r0_hi (float only)
-    P_DR = 3,
-    P_DA = 4,
-    P_AR = 5,       // lambda log2(e)
-    P_ZS = 6,       // zeta scale: beta, or 1
-    P_N = 7,
-    P_NINV2N = 8,   // -1 / (2 n)
-    P_H = 9,
-    P_VALID = 10,   // 1 if the candidate is inside the potential's domain
-    P_HMU = 11,     // mu / 2
-    P_CCS = 12,     // gradient coefficient scale: beta / 2, or 1 / 2
-    // float records: low parts (value - float(value)) of the parameters the
-    // float64 energy terms use; zero in double records
-    P_AALO = 13,
-    P_DRLO = 14,
-    P_NLO = 15,
-    P_NINV2NLO = 16,
-    P_ARLO = 17,
-    P_DALO = 18,
-    P_HLAMBDA = 19, // lambda / 2
-    // Tersoff angular function
-    P_GAM = 20,     // gamma
-    P_K = 21,       // gamma c^2 / d^2
-    P_D2 = 22,      // d^2
-    P_KD2 = 23,     // K d^2
-    P_HLO = 24      // h - float(h) (float records; zero in double records)
+// Decoded parameter record, filled per work item in LDS.  Both potential forms
+// share it: f_R = DR e^{-lambda (r - r0)}, f_A = DA e^{-mu (r - r0)} with
+// lambda = alpha sqrt(2S), mu = alpha sqrt(2/S), DR = D0/(S-1), DA = S D0/(S-1)
+// (Sec. II.B Eqs. 11-14; S = 2 in the minimal potential); zeta = ZS sum_k f_C g(theta)
+// with g = (cos - h)^2 and ZS = beta (minimal), or g = g^T = gamma + K t^2 / (d^2 + t^2),
+// t = cos - h, K = gamma c^2 / d^2 and ZS = 1 (Tersoff form, Sec. II.A Eq. 8).
+// The float path's energy terms are evaluated in float64: their parameters stand
+// here in float64 too, so that no lane converts or joins them per candidate.
+template <typename S>
+struct alignas(16) Rec {
+    double aA64, r0, DR64, ninv2n64;   // mu log2(e), r0, DR, -1/(2n)
+    double aR64, DA64;                 // lambda log2(e), DA (Tersoff form)
+    S aA, DR, DA, n, ninv2n;
+    S h, hlo;                          // hlo: h - h_S (zero in double records)
+    S zs, hmu, ccs;                    // zeta scale; mu / 2; gradient scale: beta / 2, or 1 / 2
+    S valid;                           // 1 if the candidate is inside the potential's domain
+    S aR, hlambda;                     // lambda log2(e), lambda / 2 (Tersoff form, with the next four)
+    S gam, K, d2, Kd2;                 // gamma, gamma c^2 / d^2, d^2, K d^2
 };
 
 // One (structure, candidate range) work item of the batched kernels, with the

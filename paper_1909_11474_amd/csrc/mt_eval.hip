@@ -472,7 +472,8 @@ size_t item_lds(const mt_set* set, int s, int block, int fam, int nc) {
     const int npad = set->h_npad[s];
     const int R = block / npad;
     const size_t e = (size_t)family_elem(fam);
-    const size_t par = ((size_t)nc * kNParam * e + 31) & ~(size_t)31;
+    const size_t rec = family_f64(fam) ? sizeof(Rec<double>) : sizeof(Rec<float>);
+    const size_t par = ((size_t)nc * rec + 31) & ~(size_t)31;
     const size_t slots = family_adjoint(fam) ? (size_t)npad : (size_t)set->h_xsize[s];
     return kRedBytes + par + (size_t)R * slots * 4 * e;
 }
@@ -565,7 +566,7 @@ static bool upload_class(ClassPlan& cp, const std::vector<Item>& ordered, const 
 // Candidate tile of structure s at R replicas per block (whole steps of the
 // replicas): cfg.tile candidates, or steps per replica where cfg.tile is 0,
 // held to 128 candidates (at least one step) so that the parameter records
-// take at most 13 KB (float) of the LDS that the exchange needs.
+// take at most 15 KB (float) of the LDS that the exchange needs.
 static int tile_for(const LaunchCfg& cfg, int P, int R, bool plain, int steps) {
     int tile = plain ? 1 : std::max(cfg.tile, 1);
     if (!plain && cfg.tile == 0) tile = std::max(R, std::min(steps * R, 128));
@@ -607,7 +608,7 @@ static double step_cost(const mt_set* set, int s, int R) {
 // (Tersoff form) 0.24 -> 0.20 ms; the best of a sweep of fixed tiles takes 0.88
 // and 0.19 ms.
 static double auto_item(double total, double mean, int block, int mc, int fam, int ncu) {
-    const int waves = mc <= 4 && fam == FAM_FIT32 ? 16 : 8;          // per compute unit (registers)
+    const int waves = mc <= 4 && (fam == FAM_FIT32 || fam == FAM_ADJ32) ? 16 : 8;   // per compute unit (registers)
     const double round = total / ((double)ncu * std::max(1, waves * 64 / block));
     return std::min(round, std::sqrt(4.0 * mean * round));
 }

@@ -62,68 +62,56 @@ __device__ __forceinline__ bool params_valid(const double* __restrict__ x) {
     }
 }
 
-template <typename S>
-__device__ __forceinline__ void put_split(S* __restrict__ o, int hi, int lo, double v) {
-    const S h = (S)v;
-    o[hi] = h;
-    o[lo] = (S)(v - (double)h);
-}
-
-// x -> the record of the form-independent site routine (see ParamIndex).
+// x -> the record of the form-independent site routine.  The minimal form leaves
+// the Tersoff form's fields unwritten.
 template <typename S, bool Full>
-__device__ __forceinline__ void decode_record(const double* __restrict__ x, S* __restrict__ o) {
+__device__ __forceinline__ void decode_record(const double* __restrict__ x, Rec<S>& o) {
     const double log2e = 1.4426950408889634;
     const bool ok = params_valid<Full>(x);
+    double D0 = x[0], al = x[1], r0 = x[2], n, h;
     if constexpr (Full) {
-        double D0 = x[0], al = x[1], r0 = x[2], Sl = x[3], gam = x[4], n = x[5], c = x[6],
-               d = x[7], h = x[8];
+        double Sl = x[3], gam = x[4], c = x[6], d = x[7];
+        n = x[5];
+        h = x[8];
         if (!ok) { D0 = 3.0; al = 1.4; r0 = 2.2; Sl = 2.0; gam = 0.3; n = 0.6; c = 1.0; d = 1.0; h = -0.6; }
         const double mu = al * sqrt(2.0 / Sl), lam = al * sqrt(2.0 * Sl);
-        put_split(o, P_AA, P_AALO, mu * log2e);
-        put_split(o, P_AR, P_ARLO, lam * log2e);
-        put_split(o, P_R0HI, P_R0LO, r0);
-        put_split(o, P_DR, P_DRLO, D0 / (Sl - 1.0));
-        put_split(o, P_DA, P_DALO, Sl * D0 / (Sl - 1.0));
-        put_split(o, P_N, P_NLO, n);
-        put_split(o, P_NINV2N, P_NINV2NLO, -1.0 / (2.0 * n));
-        put_split(o, P_H, P_HLO, h);
-        o[P_VALID] = ok ? S(1) : S(0);
-        o[P_HMU] = (S)(0.5 * mu);
-        o[P_HLAMBDA] = (S)(0.5 * lam);
-        o[P_ZS] = S(1);
-        o[P_CCS] = S(0.5);
+        o.aA64 = mu * log2e;
+        o.aR64 = lam * log2e;
+        o.DR64 = D0 / (Sl - 1.0);
+        o.DA64 = Sl * D0 / (Sl - 1.0);
+        o.aR = (S)o.aR64;
+        o.DA = (S)o.DA64;
+        o.zs = S(1);
+        o.ccs = S(0.5);
+        o.hmu = (S)(0.5 * mu);
+        o.hlambda = (S)(0.5 * lam);
         const double K = gam * c * c / (d * d);
-        o[P_GAM] = (S)gam;
-        o[P_K] = (S)K;
-        o[P_D2] = (S)(d * d);
-        o[P_KD2] = (S)(K * d * d);
+        o.gam = (S)gam;
+        o.K = (S)K;
+        o.d2 = (S)(d * d);
+        o.Kd2 = (S)(K * d * d);
     } else {
-        // S = 2: mu = alpha, lambda = 2 alpha, DR = D0, DA = 2 D0.  The slots
-        // that only the Tersoff form reads (P_AR, P_ARLO, P_DALO, P_HLAMBDA,
-        // P_GAM .. P_KD2) are left unwritten: writing them changes the
-        // register allocation of the float fitness kernel's candidate loop
-        // (three more spilled values there, 4 % slower).
-        double D0 = x[0], al = x[1], r0 = x[2], be = x[3], n = x[4], h = x[5];
+        // S = 2: mu = alpha, lambda = 2 alpha, DR = D0, DA = 2 D0
+        double be = x[3];
+        n = x[4];
+        h = x[5];
         if (!ok) { D0 = 3.0; al = 1.4; r0 = 2.2; be = 0.3; n = 0.6; h = -0.6; }
-        o[P_AA] = (S)(al * log2e);
-        const S r0hi = (S)r0;
-        o[P_R0HI] = r0hi;
-        o[P_R0LO] = (S)(r0 - (double)r0hi);
-        o[P_DR] = (S)D0;
-        o[P_DA] = (S)(2.0 * D0);
-        o[P_ZS] = (S)be;
-        o[P_N] = (S)n;
-        o[P_NINV2N] = (S)(-1.0 / (2.0 * n));
-        put_split(o, P_H, P_HLO, h);
-        o[P_VALID] = ok ? S(1) : S(0);
-        o[P_HMU] = (S)(0.5 * al);
-        o[P_CCS] = (S)(0.5 * be);
-        const double aA = al * log2e, ni = -1.0 / (2.0 * n);
-        o[P_AALO] = (S)(aA - (double)(S)aA);
-        o[P_DRLO] = (S)(D0 - (double)(S)D0);
-        o[P_NLO] = (S)(n - (double)(S)n);
-        o[P_NINV2NLO] = (S)(ni - (double)(S)ni);
+        o.aA64 = al * log2e;
+        o.DR64 = D0;
+        o.DA = (S)(2.0 * D0);
+        o.zs = (S)be;
+        o.ccs = (S)(0.5 * be);
+        o.hmu = (S)(0.5 * al);
     }
+    o.r0 = r0;
+    o.ninv2n64 = -1.0 / (2.0 * n);
+    o.aA = (S)o.aA64;
+    o.DR = (S)o.DR64;
+    o.n = (S)n;
+    o.ninv2n = (S)o.ninv2n64;
+    o.h = (S)h;
+    o.hlo = (S)(h - (double)o.h);
+    o.valid = ok ? S(1) : S(0);
 }
 
 template <typename S>
@@ -282,13 +270,13 @@ __device__ __forceinline__ void flush_sums(const BArgs<S>& A, const ItemCtx& x, 
 }
 
 // LDS layout of a block while it works on an item: [kRedBytes of wavefront
-// sums][it.nc x kNParam parameter records][R x xsz exchange slots (Vec4); adjoint: R x npad force residuals
+// sums][it.nc parameter records][R x xsz exchange slots (Vec4); adjoint: R x npad force residuals
 // (Vec4) instead].  The exchange follows the item's own records, so the LDS a launch
 // gets for the largest (records + exchange) of its structures covers every
 // item, whatever the candidate tiles of the other structures in the launch.
 template <typename S>
 __device__ __forceinline__ size_t lds_param_bytes(int nc) {
-    return ((size_t)nc * kNParam * sizeof(S) + 31) & ~(size_t)31;
+    return ((size_t)nc * sizeof(Rec<S>) + 31) & ~(size_t)31;
 }
 
 // The moment path's two values per bond wait in the bond's own exchange slot
@@ -320,7 +308,7 @@ __device__ __forceinline__ void run_batched(const BArgs<S>& A, const Item& it, c
     constexpr int NV = MODE == MODE_FIT ? kNVFit : kNVEval;
     const bool sync = SYNC < 0 ? x.block_sync : SYNC == 1;
     double* __restrict__ red = reinterpret_cast<double*>(lds - kRedBytes);
-    const S* __restrict__ pbuf = reinterpret_cast<const S*>(lds);
+    const Rec<S>* __restrict__ pbuf = reinterpret_cast<const Rec<S>*>(lds);
     Vec4<S>* __restrict__ xb = reinterpret_cast<Vec4<S>*>(lds + lds_param_bytes<S>(it.nc));
     Geo<S, M, Full> g;
     g.load(d, x.atom, x.active);
@@ -344,7 +332,7 @@ __device__ __forceinline__ void run_batched(const BArgs<S>& A, const Item& it, c
     auto flush = [&](int step) __attribute__((always_inline)) {
         const int cl = x.q + step * x.R;
         if (cl < it.nc)
-            flush_sums<MODE, NV>(A, x, it.c0 + cl, MODE == MODE_FIT ? 8 : 11, pbuf[kNParam * cl + P_VALID] != S(0), red);
+            flush_sums<MODE, NV>(A, x, it.c0 + cl, MODE == MODE_FIT ? 8 : 11, pbuf[cl].valid != S(0), red);
     };
 
     for (int step = 0; step < x.steps; ++step) {
@@ -354,7 +342,7 @@ __device__ __forceinline__ void run_batched(const BArgs<S>& A, const Item& it, c
         const int clv = group_ok ? cl : 0;
         const int c = it.c0 + clv;
         Cand<S, Full> p;
-        load_cand(pbuf + kNParam * clv, p);
+        load_cand(pbuf[clv], p);
         // Each bond gradient G_j goes to its exchange slot as soon as the site
         // routine emits it and is folded into this atom's own force sum and
         // the virial, so no bond-gradient array stays live across the exchange.
@@ -370,7 +358,7 @@ __device__ __forceinline__ void run_batched(const BArgs<S>& A, const Item& it, c
                 slot[1] = gy;
                 slot[2] = gz;
                 Fx += gx; Fy += gy; Fz += gz;
-                const S dx = g.rhi[m] * g.ux[m], dy = g.rhi[m] * g.uy[m], dz = g.rhi[m] * g.uz[m];
+                const S rm = g.length(m), dx = rm * g.ux[m], dy = rm * g.uy[m], dz = rm * g.uz[m];
                 w6[0] -= dx * gx; w6[1] -= dy * gy; w6[2] -= dz * gz;
                 w6[3] -= dy * gz; w6[4] -= dz * gx; w6[5] -= dx * gy;
             },
@@ -387,7 +375,7 @@ __device__ __forceinline__ void run_batched(const BArgs<S>& A, const Item& it, c
             Fy -= r.y;
             Fz -= r.z;
             if (MODE == MODE_EVAL) {
-                const S dx = g.rhi[m] * g.ux[m], dy = g.rhi[m] * g.uy[m], dz = g.rhi[m] * g.uz[m];
+                const S rm = g.length(m), dx = rm * g.ux[m], dy = rm * g.uy[m], dz = rm * g.uz[m];
                 wi[0] += dx * r.x; wi[1] += dx * r.y; wi[2] += dx * r.z;
                 wi[3] += dy * r.x; wi[4] += dy * r.y; wi[5] += dy * r.z;
                 wi[6] += dz * r.x; wi[7] += dz * r.y; wi[8] += dz * r.z;
@@ -471,9 +459,9 @@ struct ClassLo {
 // (run_batched, run_adjoint, run_idle), so one memory round trip covers both.
 template <typename S, bool Full = false>
 __device__ __forceinline__ void decode_item(const BArgs<S>& A, const Item& it, unsigned char* lds) {
-    S* pbuf = reinterpret_cast<S*>(lds);
+    Rec<S>* pbuf = reinterpret_cast<Rec<S>*>(lds);
     for (int t = threadIdx.x; t < it.nc; t += blockDim.x)
-        decode_record<S, Full>(A.x + Form<Full>::nx * (size_t)(it.c0 + t), pbuf + kNParam * t);
+        decode_record<S, Full>(A.x + Form<Full>::nx * (size_t)(it.c0 + t), pbuf[t]);
 }
 
 template <typename S, int MODE, int MC, bool Full, bool Resid = false>
@@ -594,7 +582,7 @@ constexpr int kAdjointPairs = sizeof(S) == 8 ? 4 : 12;
 // m, cf the coefficients k_e, k_f, C_s (xx yy zz yz zx xy, off-diagonals halved)
 // of the (candidate, structure).
 template <typename S, int M, bool Full, typename Aj>
-__device__ __forceinline__ void adjoint_sums(Geo<S, M, Full>& g, const S* __restrict__ rec, S ax, S ay, S az,
+__device__ __forceinline__ void adjoint_sums(Geo<S, M, Full>& g, const Rec<S>& rec, S ax, S ay, S az,
                                              Aj&& aj, const double* __restrict__ cf,
                                              S (&L)[GradSums<Full>::value]) {
     constexpr int MM = M > 0 ? M : 1;
@@ -603,8 +591,10 @@ __device__ __forceinline__ void adjoint_sums(Geo<S, M, Full>& g, const S* __rest
     const S cyz = (S)cf[5], czx = (S)cf[6], cxy = (S)cf[7];
     Cand<S, Full> p;
     load_cand(rec, p);
+    // keep the float copies of r and the uncached cos(theta) out of registers
+    // across candidates
+    if constexpr (sizeof(S) == 4 && M > 0) opaque(g.r);
     if constexpr (!Geo<S, M, Full>::kCache && M > 1) {
-        // keep the uncached cos(theta) out of registers across candidates
         opaque(g.ux);
         opaque(g.uy);
         opaque(g.uz);
@@ -615,7 +605,7 @@ __device__ __forceinline__ void adjoint_sums(Geo<S, M, Full>& g, const S* __rest
     };
     auto bond_d = [&](int m) __attribute__((always_inline)) {
         const Vec4<S> a = aj(m);
-        const S dx = g.rhi[m] * g.ux[m], dy = g.rhi[m] * g.uy[m], dz = g.rhi[m] * g.uz[m];
+        const S rm = g.length(m), dx = rm * g.ux[m], dy = rm * g.uy[m], dz = rm * g.uz[m];
         const S ex = kf * (a.x - ax) + cxx * dx + cxy * dy + czx * dz;
         const S ey = kf * (a.y - ay) + cxy * dx + cyy * dy + cyz * dz;
         const S ez = kf * (a.z - az) + czx * dx + cyz * dy + czz * dz;
@@ -661,7 +651,7 @@ __device__ __forceinline__ void adjoint_sums(Geo<S, M, Full>& g, const S* __rest
         // zeta = 0: b = 1 and every derivative of b is dropped (zn = 0)
         const bool pos = z > S(0);
         const S zsafe = pos ? z : S(1);
-        const S delta = (g.rhi[j] - p.r0hi) + (g.rlo[j] - p.r0lo);
+        const S delta = (S)(g.r[j] - p.r0);
         const S eA = dexp2(-(p.aA * delta));
         S eR;
         if constexpr (Full) eR = dexp2(-(p.aR * delta));
@@ -833,7 +823,7 @@ __device__ __forceinline__ void run_adjoint(const BArgs<S>& A, const Item& it, c
                                             unsigned char* __restrict__ lds) {
     const SetDev& d = A.set;
     const int N = d.N;
-    const S* __restrict__ pbuf = reinterpret_cast<const S*>(lds);
+    const Rec<S>* __restrict__ pbuf = reinterpret_cast<const Rec<S>*>(lds);
     Vec4<S>* __restrict__ ab =
         reinterpret_cast<Vec4<S>*>(lds + lds_param_bytes<S>(it.nc)) + (size_t)x.q * x.npad;
     Geo<S, M, Full> g;
@@ -856,7 +846,7 @@ __device__ __forceinline__ void run_adjoint(const BArgs<S>& A, const Item& it, c
         const bool group_ok = cl < it.nc;
         const int clv = group_ok ? cl : 0;
         const int c = it.c0 + clv;
-        const S* prec = pbuf + kNParam * clv;
+        const Rec<S>& prec = pbuf[clv];
         // this atom's force residual, from the fitness call (lanes outside the
         // structure: zero, and zero geometry)
         S ax = S(0), ay = S(0), az = S(0);
@@ -989,7 +979,7 @@ __device__ __forceinline__ void run_large_site(const BArgs<S>& A, const LArgs& L
     const int nbs = L.nbs;
     const int Mi = active ? d.nnb[atom] : 0;
     const int lb = active ? d.lbo[atom] : 0;
-    S rec[kNParam];
+    Rec<S> rec;
     decode_record<S, Full>(A.x + Form<Full>::nx * (size_t)c, rec);
     Cand<S, Full> p;
     load_cand(rec, p);
@@ -1010,7 +1000,7 @@ __device__ __forceinline__ void run_large_site(const BArgs<S>& A, const LArgs& L
     for (int k = 0; k < 6; ++k) w6[k] = S(0);
 #pragma unroll
     for (int m = 0; m < M; ++m) {
-        const S dx = g.rhi[m] * g.ux[m], dy = g.rhi[m] * g.uy[m], dz = g.rhi[m] * g.uz[m];
+        const S rm = g.length(m), dx = rm * g.ux[m], dy = rm * g.uy[m], dz = rm * g.uz[m];
         w6[0] -= dx * Gx[m]; w6[1] -= dy * Gy[m]; w6[2] -= dz * Gz[m];
         w6[3] -= dy * Gz[m]; w6[4] -= dz * Gx[m]; w6[5] -= dx * Gy[m];
     }
@@ -1181,7 +1171,7 @@ __device__ __forceinline__ void run_large_adjoint(const BArgs<S>& A, const LArgs
 #pragma unroll
     for (int m = 0; m < M; ++m) jl[m] = (active && m < d.kcap) ? d.jl[(size_t)m * N + atom] : 0;
     const int c = L.c0 + blockIdx.y;
-    S rec[kNParam];
+    Rec<S> rec;
     decode_record<S, Full>(A.x + Form<Full>::nx * (size_t)c, rec);
     const S* a = abuf + (size_t)blockIdx.y * 3 * Ns;
     const S ax = active ? a[la] : S(0), ay = active ? a[Ns + la] : S(0), az = active ? a[2 * Ns + la] : S(0);

@@ -42,7 +42,8 @@ struct Geo {
     static constexpr bool kCache = NP <= 15;       // keep cos(theta) in registers for M <= 6
     static constexpr bool kMoments = !Full && sizeof(S) == 4 && M > kPairMax;
     S ux[M > 0 ? M : 1], uy[M > 0 ? M : 1], uz[M > 0 ? M : 1];
-    S rhi[M > 0 ? M : 1], rlo[M > 0 ? M : 1], rinv[M > 0 ? M : 1];
+    double r[M > 0 ? M : 1];                      // float64 also in the float geometry: r - r0
+    S rinv[M > 0 ? M : 1];
     S fc[M > 0 ? M : 1], hfcp[M > 0 ? M : 1];     // f_C and f_C'/2
     S cs[kCache && NP > 0 ? NP : 1];
     // The minimal form's angular function is (cos - h)^2, so bond j's sum over
@@ -73,6 +74,8 @@ struct Geo {
         }
     }
 
+    __device__ __forceinline__ S length(int m) const { return (S)r[m]; }
+
     __device__ __forceinline__ S cosjk(int j, int k, int pidx) const {
         if constexpr (kCache && NP > 0) {
             return cs[pidx];
@@ -97,8 +100,8 @@ struct Geo {
                 const bool ok = active && m < rows;
                 const float4 a = ok ? d.gf.pk0[o] : make_float4(0.f, 0.f, 0.f, 3.f);
                 const float4 b = ok ? d.gf.pk1[o] : make_float4(0.f, 0.f, 0.f, 0.f);
-                ux[m] = a.x; uy[m] = a.y; uz[m] = a.z; rhi[m] = a.w;
-                rlo[m] = b.x; rinv[m] = b.y; fc[m] = b.z; hfcp[m] = b.w;
+                ux[m] = a.x; uy[m] = a.y; uz[m] = a.z; r[m] = (double)a.w + (double)b.x;
+                rinv[m] = b.y; fc[m] = b.z; hfcp[m] = b.w;
             }
             if constexpr (kCache && NP > 0) {
                 static_assert(M <= 6, "the pair table holds bonds 0-5");
@@ -118,8 +121,7 @@ struct Geo {
                 ux[m] = ok ? G.ux[o] : S(0);
                 uy[m] = ok ? G.uy[o] : S(0);
                 uz[m] = ok ? G.uz[o] : S(0);
-                rhi[m] = ok ? G.rhi[o] : S(3);
-                rlo[m] = S(0);
+                r[m] = ok ? G.rhi[o] : S(3);
                 rinv[m] = ok ? G.rinv[o] : S(0);
                 fc[m] = ok ? G.fc[o] : S(0);
                 hfcp[m] = ok ? G.hfcp[o] : S(0);
@@ -146,11 +148,11 @@ struct Geo {
 template <typename S, bool Full = false>
 struct Cand {
     static constexpr bool kFull = Full;
-    S aA, aR, r0hi, r0lo, DR, DA, hmu, hlambda, zs, ccs, n, ninv2n, h;
+    S aA, aR, DR, DA, hmu, hlambda, zs, ccs, n, ninv2n, h;
     S gam, K, d2, Kd2;               // g^T = gam + K t^2 / (d2 + t^2)
     S valid;
-    S aAlo, aRlo, DRlo, DAlo, nlo, ninv2nlo;   // low parts for the float64 energy terms
-    S hlo;                                      // h - float(h): zeta of the float path
+    S hlo;                           // h - float(h): zeta of the float path
+    double r0, aA64, aR64, DR64, DA64, ninv2n64;   // float64 energy terms
 };
 
 // Type of the site energy: float64 for the float path (its energy terms are
@@ -160,21 +162,19 @@ struct EnergyOf { using type = S; };
 template <>
 struct EnergyOf<float> { using type = double; };
 
-// The minimal record leaves the Tersoff-form slots unwritten; its candidate
-// takes lambda = 2 mu and does not read them.
+// The minimal record leaves the Tersoff form's fields unwritten; its candidate
+// takes lambda = 2 mu, DA = 2 DR and does not read them.
 template <typename S, bool Full>
-__device__ __forceinline__ void load_cand(const S* __restrict__ p, Cand<S, Full>& c) {
-    c.aA = p[P_AA]; c.r0hi = p[P_R0HI]; c.r0lo = p[P_R0LO];
-    c.DR = p[P_DR]; c.DA = p[P_DA]; c.hmu = p[P_HMU];
-    c.zs = p[P_ZS]; c.ccs = p[P_CCS]; c.n = p[P_N]; c.ninv2n = p[P_NINV2N]; c.h = p[P_H];
-    c.aAlo = p[P_AALO]; c.DRlo = p[P_DRLO]; c.nlo = p[P_NLO]; c.ninv2nlo = p[P_NINV2NLO];
-    c.hlo = p[P_HLO];
-    c.valid = p[P_VALID];
+__device__ __forceinline__ void load_cand(const Rec<S>& p, Cand<S, Full>& c) {
+    c.aA = p.aA; c.DR = p.DR; c.DA = p.DA; c.hmu = p.hmu;
+    c.zs = p.zs; c.ccs = p.ccs; c.n = p.n; c.ninv2n = p.ninv2n; c.h = p.h; c.hlo = p.hlo;
+    c.valid = p.valid;
+    c.r0 = p.r0; c.aA64 = p.aA64; c.DR64 = p.DR64; c.ninv2n64 = p.ninv2n64;
     if constexpr (Full) {
-        c.aR = p[P_AR]; c.hlambda = p[P_HLAMBDA]; c.aRlo = p[P_ARLO]; c.DAlo = p[P_DALO];
-        c.gam = p[P_GAM]; c.K = p[P_K]; c.d2 = p[P_D2]; c.Kd2 = p[P_KD2];
+        c.aR = p.aR; c.hlambda = p.hlambda; c.aR64 = p.aR64; c.DA64 = p.DA64;
+        c.gam = p.gam; c.K = p.K; c.d2 = p.d2; c.Kd2 = p.Kd2;
     } else {
-        c.aR = S(2) * c.aA; c.hlambda = S(2) * c.hmu; c.aRlo = S(2) * c.aAlo; c.DAlo = S(2) * c.DRlo;
+        c.aR = S(2) * c.aA; c.hlambda = S(2) * c.hmu; c.aR64 = 2.0 * c.aA64; c.DA64 = 2.0 * c.DR64;
         c.gam = S(0); c.K = S(0); c.d2 = S(1); c.Kd2 = S(0);
     }
 }
@@ -204,8 +204,8 @@ __device__ __forceinline__ void ang_g_dg(const P& p, S t, S& gv, S& hg) {
 
 // Make the compiler treat the values as changed here (no instruction is
 // emitted): expressions of them after this point are recomputed, not reused.
-template <typename S, int N>
-__device__ __forceinline__ void opaque(S (&a)[N]) {
+template <typename T, int N>
+__device__ __forceinline__ void opaque(T (&a)[N]) {
 #pragma unroll
     for (int i = 0; i < N; ++i) asm volatile("" : "+v"(a[i]));
 }
@@ -247,6 +247,12 @@ __device__ __forceinline__ void site_eval_sink(Geo<S, M, Full>& g, const Cand<S,
     // float hi/lo pair, so that a float rounding of h does not shift every
     // (cos - h)^2 of a candidate the same way.
     constexpr bool kE64 = Energy64 && std::is_same<S, float>::value;
+    // the float copies of r and float64 copies of f_C are made per candidate:
+    // hoisted out of the candidate loop they would hold 3 M registers
+    if constexpr (kE64 && M > 0) {
+        opaque(g.r);
+        opaque(g.fc);
+    }
     // Energy64: in float32 the rounding of f_R and b f_A (up to ~15 eV each
     // for parameters inside the fitting box) and the one-ulp errors of the
     // hardware exponentials reach 1e-6 eV per bond.  The exponentials whose
@@ -262,35 +268,29 @@ __device__ __forceinline__ void site_eval_sink(Geo<S, M, Full>& g, const Cand<S,
         const S z = zeta * p.zs;
         // zeta = 0 (no other neighbour inside the cutoff, or all at g = 0):
         // zeta^n = 0 exactly, so b = 1 and db/dzeta * zeta^n-terms vanish
-        const bool pos = z > S(0);
-        const S zsafe = pos ? z : S(1);
-        S eA, zn, b;
+        S zsafe, eA, zn, b;
         [[maybe_unused]] S eR;
         if constexpr (kE64) {
-            // float64 copies of the bond's geometry are made here, per candidate:
-            // hoisted out of the candidate loop they would hold 6 M registers
-            S rh = g.rhi[j], rl = g.rlo[j], fcj = g.fc[j];
-            asm volatile("" : "+v"(rh), "+v"(rl), "+v"(fcj));
-            const double dl = ((double)rh - (double)p.r0hi) + ((double)rl - (double)p.r0lo);
-            const double eA64 = exp2_acc(-(((double)p.aA + (double)p.aAlo) * dl));
-            const float zn32 = pos ? dexp2(p.n * dlog2(zsafe)) : 0.f;
-            const double b64 =
-                exp2_acc(((double)p.ninv2n + (double)p.ninv2nlo) * (double)dlog2(1.f + zn32));
-            const double DR = (double)p.DR + (double)p.DRlo;
+            const double dl = g.r[j] - p.r0;
+            const double eA64 = exp2_acc(-(p.aA64 * dl));
+            // log2 0 = -inf and 2^-inf = 0; the divisor below stays positive
+            zn = dexp2(p.n * dlog2(z));
+            zsafe = __builtin_fmaxf(z, 1e-30f);
+            const double b64 = exp2_acc(p.ninv2n64 * (double)dlog2(1.f + zn));
             if constexpr (Full) {
-                const double eR64 = exp2_acc(-(((double)p.aR + (double)p.aRlo) * dl));
-                const double DA = (double)p.DA + (double)p.DAlo;
-                usum64 += (double)fcj * (DR * eR64 - b64 * (DA * eA64));
+                const double eR64 = exp2_acc(-(p.aR64 * dl));
+                usum64 += (double)g.fc[j] * (p.DR64 * eR64 - b64 * (p.DA64 * eA64));
                 eR = (float)eR64;
             } else {
                 // DA = 2 DR, e_R = e_A^2
-                usum64 += (double)fcj * (DR * eA64 * (eA64 - 2.0 * b64));
+                usum64 += (double)g.fc[j] * (p.DR64 * eA64 * (eA64 - 2.0 * b64));
             }
             eA = (float)eA64;
-            zn = zn32;
             b = (float)b64;
         } else {
-            const S delta = (g.rhi[j] - p.r0hi) + (g.rlo[j] - p.r0lo);
+            const bool pos = z > S(0);
+            zsafe = pos ? z : S(1);
+            const S delta = (S)(g.r[j] - p.r0);
             eA = dexp2(-(p.aA * delta));
             if constexpr (Full) eR = dexp2(-(p.aR * delta));
             // formed before the selection: a branch around it splits the chain
