@@ -280,7 +280,8 @@ static int eval_impl(mt_set* set, const double* x, int form, int P, int precisio
 }
 
 static int fitness_sequence(mt_set* set, const double* x, int form, int P, const double* w,
-                            int precision, int schedule, double* Z, hipStream_t st) {
+                            int precision, int schedule, double* Z, hipStream_t st,
+                            double* coef = nullptr) {
     set->cur_x = x;
     set->cur_form = form;
     if (schedule == MT_BATCHED) {
@@ -290,7 +291,7 @@ static int fitness_sequence(mt_set* set, const double* x, int form, int P, const
         TRY(launch_plain(set, P, precision, MODE_FIT, EvalOut{}, st));
     }
     TRY(launch_large(set, P, precision, MODE_FIT, nullptr, nullptr, nullptr, st));
-    return launch_finalize_fit(set, P, w, Z, st);
+    return launch_finalize_fit(set, P, w, Z, st, nullptr, coef);
 }
 
 static int check_fitness(mt_set* set, const double* x, int P, const double* w, int precision, double* Z) {
@@ -413,16 +414,18 @@ static int grad_impl(mt_set* set, const double* x, int form, int P, const double
     // the adjoint
     HIPCHECK(set->resid.reserve((precision == MT_FP64 ? sizeof(double) : sizeof(float)) * 3 * (size_t)P *
                                 set->N));
+    HIPCHECK(set->zwork.reserve(sizeof(double) * 8 * (size_t)P * set->S));
     set->fit_P = 0;
     set->grad_resid = set->resid.p;
-    const int frc = fitness_sequence(set, x, form, P, w, precision, MT_BATCHED, Z, st);
+    const int frc =
+        fitness_sequence(set, x, form, P, w, precision, MT_BATCHED, Z, st, set->zwork.as<double>());
     set->grad_resid = nullptr;
     TRY(frc);
     set->fit_P = P;
     set->fit_form = form;
     const LaunchCfg cfg = cfg_for(set, P, precision);
-    TRY(launch_adjoint(set, cfg, P, precision, w, Z, st));
-    return launch_finalize_grad(set, P, Z, dZdx, st);
+    TRY(launch_adjoint(set, cfg, P, precision, st));
+    return launch_finalize_grad(set, P, dZdx, st);
 }
 
 extern "C" {

@@ -82,6 +82,42 @@ __device__ __forceinline__ void struct_sums(const FinArgs& F, int c, int s, doub
     }
 }
 
+// Z of candidate c from the three residual sums, which every thread of the
+// block (or wavefront) holds: written by the one with first, and by all of them
+// the gradient coefficients of their structures (s0, s0 + stride, ...) where the
+// gradient asks for them: k_e, k_f, and C_s (xx yy zz yz zx xy, off-diagonals
+// halved).
+__device__ __forceinline__ void finish_fit(const FinArgs& F, int c, const double* acc, bool first, int s0,
+                                           int stride) {
+    const SetDev& d = F.set;
+    const double Ze = sqrt(acc[0] / F.Qe), Zv = sqrt(acc[1] / F.Qv), Zf = sqrt(acc[2] / F.Qf);
+    if (first) {
+        const bool ok = cand_valid(F.x, c, F.full);
+        const double Z = F.we * Ze + F.wv * Zv + F.wf * Zf;
+        const double nan = __longlong_as_double(0x7ff8000000000000ll);
+        F.Z[4 * c + 0] = ok ? Z : nan;
+        F.Z[4 * c + 1] = ok ? Ze : nan;
+        F.Z[4 * c + 2] = ok ? Zv : nan;
+        F.Z[4 * c + 3] = ok ? Zf : nan;
+    }
+    if (!F.coef) return;
+    const double ge = Ze > 0 ? F.we / (Ze * F.Qe) : 0.0;
+    const double gv = Zv > 0 ? F.wv / (Zv * F.Qv) : 0.0;
+    const double gf = Zf > 0 ? F.wf / (Zf * F.Qf) : 0.0;
+    for (int s = s0; s < d.S; s += stride) {
+        double e, w6[6], rf, j3[3];
+        struct_sums(F, c, s, &e, w6, &rf, j3);
+        const double n = (double)(d.st_off[s + 1] - d.st_off[s]);
+        double* o = F.coef + ((size_t)c * d.S + s) * 8;
+        o[0] = ge * (e / n - F.eref[s]) / n;
+        o[1] = gf;
+        double r[6];
+        for (int k = 0; k < 6; ++k) r[k] = gv * (w6[k] / n - F.wref[6 * s + k]) / n;
+        o[2] = r[0]; o[3] = r[1]; o[4] = r[2];
+        o[5] = 0.5 * r[3]; o[6] = 0.5 * r[4]; o[7] = 0.5 * r[5];
+    }
+}
+
 // Structures with more partial-sum slots than this (over 2,048 atoms: a
 // structure over the batching limit has one slot per 256-atom block, a batched
 // one at most 8) are summed by the whole block; smaller ones by one thread each.
@@ -181,16 +217,7 @@ __global__ __launch_bounds__(256) void k_finalize_fit(FinArgs F) {
         acc[2] += rf;
     }
     block_sum3_waves(acc, sh);
-    if (threadIdx.x == 0) {
-        const bool ok = cand_valid(F.x, c, F.full);
-        const double Ze = sqrt(acc[0] / F.Qe), Zv = sqrt(acc[1] / F.Qv), Zf = sqrt(acc[2] / F.Qf);
-        const double Z = F.we * Ze + F.wv * Zv + F.wf * Zf;
-        const double nan = __longlong_as_double(0x7ff8000000000000ll);
-        F.Z[4 * c + 0] = ok ? Z : nan;
-        F.Z[4 * c + 1] = ok ? Ze : nan;
-        F.Z[4 * c + 2] = ok ? Zv : nan;
-        F.Z[4 * c + 3] = ok ? Zf : nan;
-    }
+    finish_fit(F, c, acc, threadIdx.x == 0, threadIdx.x, blockDim.x);
 }
 
 // Z for sets of at most 64 structures without block-wide ones: one wavefront
@@ -227,16 +254,7 @@ __global__ __launch_bounds__(256) void k_finalize_fit_wave(FinArgs F, int P) {
     for (int o = 32; o > 0; o >>= 1)
 #pragma unroll
         for (int k = 0; k < 3; ++k) acc[k] += __shfl_xor(acc[k], o, 64);
-    if (lane == 0) {
-        const bool ok = cand_valid(F.x, c, F.full);
-        const double Ze = sqrt(acc[0] / F.Qe), Zv = sqrt(acc[1] / F.Qv), Zf = sqrt(acc[2] / F.Qf);
-        const double Z = F.we * Ze + F.wv * Zv + F.wf * Zf;
-        const double nan = __longlong_as_double(0x7ff8000000000000ll);
-        F.Z[4 * c + 0] = ok ? Z : nan;
-        F.Z[4 * c + 1] = ok ? Ze : nan;
-        F.Z[4 * c + 2] = ok ? Zv : nan;
-        F.Z[4 * c + 3] = ok ? Zf : nan;
-    }
+    finish_fit(F, c, acc, lane == 0, lane, 64);
 }
 
 // Z for sets without block-wide structures when S is small: one block per
@@ -272,39 +290,7 @@ __global__ __launch_bounds__(256) void k_finalize_fit_block(FinArgs F) {
         acc[2] += rf;
     }
     block_sum3_waves(acc, sh);
-    if (threadIdx.x == 0) {
-        const bool ok = cand_valid(F.x, c, F.full);
-        const double Ze = sqrt(acc[0] / F.Qe), Zv = sqrt(acc[1] / F.Qv), Zf = sqrt(acc[2] / F.Qf);
-        const double Z = F.we * Ze + F.wv * Zv + F.wf * Zf;
-        const double nan = __longlong_as_double(0x7ff8000000000000ll);
-        F.Z[4 * c + 0] = ok ? Z : nan;
-        F.Z[4 * c + 1] = ok ? Ze : nan;
-        F.Z[4 * c + 2] = ok ? Zv : nan;
-        F.Z[4 * c + 3] = ok ? Zf : nan;
-    }
-}
-
-// Gradient coefficients per (candidate, structure), from the forward partials
-// and Z: k_e, k_f, and C_s (xx yy zz yz zx xy, off-diagonals halved).
-__global__ __launch_bounds__(256) void k_grad_coef(FinArgs F) {
-    const int c = blockIdx.x;
-    const SetDev& d = F.set;
-    const double Ze = F.Z[4 * c + 1], Zv = F.Z[4 * c + 2], Zf = F.Z[4 * c + 3];
-    const double ge = Ze > 0 ? F.we / (Ze * F.Qe) : 0.0;
-    const double gv = Zv > 0 ? F.wv / (Zv * F.Qv) : 0.0;
-    const double gf = Zf > 0 ? F.wf / (Zf * F.Qf) : 0.0;
-    for (int s = threadIdx.x; s < d.S; s += blockDim.x) {
-        double e, w6[6], rf, j3[3];
-        struct_sums(F, c, s, &e, w6, &rf, j3);
-        const double n = (double)(d.st_off[s + 1] - d.st_off[s]);
-        double* o = F.coef + ((size_t)c * d.S + s) * 8;
-        o[0] = ge * (e / n - F.eref[s]) / n;
-        o[1] = gf;
-        double r[6];
-        for (int k = 0; k < 6; ++k) r[k] = gv * (w6[k] / n - F.wref[6 * s + k]) / n;
-        o[2] = r[0]; o[3] = r[1]; o[4] = r[2];
-        o[5] = 0.5 * r[3]; o[6] = 0.5 * r[4]; o[7] = 0.5 * r[5];
-    }
+    finish_fit(F, c, acc, threadIdx.x == 0, threadIdx.x, blockDim.x);
 }
 
 // dZ/dx [P][nx], nx = 6 (minimal) or 9 (Tersoff form): the totals of the grad
@@ -516,14 +502,14 @@ const std::vector<int>& family_classes(int fam) {
         {4, 8, 16},          // EVAL32
         {4, 16},             // FIT64
         {4, 16},             // EVAL64
-        {4, 8, 12},          // ADJ32
-        {4, 12},             // ADJ64
+        {4, 8, 16},          // ADJ32
+        {4, 16},             // ADJ64
         {4, 16},             // FIT32F
         {4, 16},             // EVAL32F
         {4, 16},             // FIT64F
         {4, 16},             // EVAL64F
-        {4, 12},             // ADJ32F
-        {4, 12},             // ADJ64F
+        {4, 16},             // ADJ32F
+        {4, 16},             // ADJ64F
     };
     return k[fam];
 }
@@ -683,7 +669,7 @@ ItemPlan* get_plan(mt_set* set, int P, const LaunchCfg& cfg, int fam) {
     for (int s = 0; s < set->S; ++s) {
         if (set->h_large[s]) continue;
         if (set->h_kmax[s] > classes.back()) {
-            // above the family's widest class (the adjoint's 12): two-pass
+            // above the family's widest class: two-pass
             plan->twopass.push_back(s);
             continue;
         }
@@ -1119,10 +1105,11 @@ int launch_large(mt_set* set, int P, int precision, int mode, const double* vel,
 }
 
 int launch_finalize_fit(mt_set* set, int P, const double* w, double* Z, hipStream_t st,
-                        const double* partial) {
+                        const double* partial, double* coef) {
     FinArgs F = make_fin(set, kNVFit, partial ? partial : set->partial.as<double>());
     F.we = w[0]; F.wv = w[1]; F.wf = w[2];
     F.Z = Z;
+    F.coef = coef;
     if (F.coop) {
         hipLaunchKernelGGL(k_finalize_fit, dim3(P), dim3(256), 0, st, F);
     } else if (set->S > 64) {
@@ -1158,17 +1145,6 @@ int launch_finalize_eval(mt_set* set, int P, double* energy, double* virial, dou
 int launch_fitness_terms(mt_set* set, int P, double* e, double* w, double* rf, hipStream_t st) {
     FinArgs F = make_fin(set, kNVFit, set->partial.as<double>());
     hipLaunchKernelGGL(k_fitness_terms, dim3(P), dim3(256), 0, st, F, e, w, rf);
-    HIPCHECK(hipGetLastError());
-    return MT_OK;
-}
-
-static int launch_grad_coef(mt_set* set, int P, const double* w, const double* Z, hipStream_t st) {
-    HIPCHECK(set->zwork.reserve(sizeof(double) * 8 * (size_t)P * set->S));
-    FinArgs F = make_fin(set, kNVFit, set->partial.as<double>());
-    F.we = w[0]; F.wv = w[1]; F.wf = w[2];
-    F.Z = const_cast<double*>(Z);
-    F.coef = set->zwork.as<double>();
-    hipLaunchKernelGGL(k_grad_coef, dim3(P), dim3(256), 0, st, F);
     HIPCHECK(hipGetLastError());
     return MT_OK;
 }
@@ -1218,10 +1194,8 @@ static int launch_twopass_adjoint(mt_set* set, const std::vector<int>& structs, 
     return MT_OK;
 }
 
-static int adjoint_common(mt_set* set, const LaunchCfg& cfg, int P, int precision, const double* w,
-                          const double* Z, hipStream_t st) {
+int launch_adjoint(mt_set* set, const LaunchCfg& cfg, int P, int precision, hipStream_t st) {
     if (precision != MT_FP64) TRY_RC(float_tables(set, st));
-    TRY_RC(launch_grad_coef(set, P, w, Z, st));
     const int nv = set->cur_form ? kNVGradTF : kNVGrad;
     HIPCHECK(set->partial2.reserve(sizeof(double) * nv * (size_t)P * set->nslots));
     const bool f64 = precision == MT_FP64;
@@ -1251,13 +1225,7 @@ static int adjoint_common(mt_set* set, const LaunchCfg& cfg, int P, int precisio
                : launch_twopass_adjoint<float>(set, structs, P, nv, st);
 }
 
-int launch_adjoint(mt_set* set, const LaunchCfg& cfg, int P, int precision, const double* w,
-                   const double* Z, hipStream_t st) {
-    return adjoint_common(set, cfg, P, precision, w, Z, st);
-}
-
-int launch_finalize_grad(mt_set* set, int P, const double* Z, double* dZdx, hipStream_t st) {
-    (void)Z;
+int launch_finalize_grad(mt_set* set, int P, double* dZdx, hipStream_t st) {
     FinArgs F = make_fin(set, set->cur_form ? kNVGradTF : kNVGrad, set->partial2.as<double>());
     if (set->cur_form) hipLaunchKernelGGL(k_finalize_grad<true>, dim3(P), dim3(256), 0, st, F, dZdx);
     else hipLaunchKernelGGL(k_finalize_grad<false>, dim3(P), dim3(256), 0, st, F, dZdx);

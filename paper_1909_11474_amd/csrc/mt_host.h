@@ -159,7 +159,7 @@ struct mt_set {
     // the adjoint reads it; grad_resid is set only for that fitness call
     mt::DevBuf resid;
     void* grad_resid = nullptr;
-    mt::DevBuf zwork;                        // [P][4] scratch for fitness_grad
+    mt::DevBuf zwork;                        // gradient coefficients, [P][S][8]
     mt::DevBuf gbuf;                         // large path bond gradients
     mt::DevBuf tpart;                        // block sums of batched structures on the two-pass path
     mt::DevBuf scalars;                      // small device scratch
@@ -221,20 +221,20 @@ int launch_large(mt_set* set, int P, int precision, int mode, const double* vel,
 // Reserve the two-pass staging buffer for the set's large structures and the
 // plan's two-pass structures (before graph capture: capture may not allocate).
 int reserve_twopass(mt_set* set, const ItemPlan* plan, int P, int precision);
-// partial: the per-slot partial sums to finalize (null: the set's workspace)
+// partial: the per-slot partial sums to finalize (null: the set's workspace);
+// coef: where the gradient's coefficients go ([P][S][8]), null without one
 int launch_finalize_fit(mt_set* set, int P, const double* w, double* Z, hipStream_t stream,
-                        const double* partial = nullptr);
+                        const double* partial = nullptr, double* coef = nullptr);
 int launch_finalize_eval(mt_set* set, int P, double* energy, double* virial, double* heat,
                          hipStream_t stream);
 // Per-structure e_s, w_s and squared force residual from the fitness partial
 // sums in the set's workspace (set->cur_x and cur_form select the candidates'
 // domain check).
 int launch_fitness_terms(mt_set* set, int P, double* e, double* w, double* rf, hipStream_t stream);
-// The adjoint of the batched structures reads the force residuals the
-// fitness call just before it wrote to set->resid (set->grad_resid).
-int launch_adjoint(mt_set* set, const LaunchCfg& cfg, int P, int precision, const double* w,
-                   const double* Z, hipStream_t stream);
-int launch_finalize_grad(mt_set* set, int P, const double* Z, double* dZdx, hipStream_t stream);
+// The adjoint reads what the fitness call just before it wrote: the batched
+// structures' force residuals (set->resid) and the coefficients (set->zwork).
+int launch_adjoint(mt_set* set, const LaunchCfg& cfg, int P, int precision, hipStream_t stream);
+int launch_finalize_grad(mt_set* set, int P, double* dZdx, hipStream_t stream);
 
 // MODE_STAGE (two-pass path only): stage the bond gradients, no partial sums
 // and no gather.

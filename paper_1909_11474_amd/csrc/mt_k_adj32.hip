@@ -10,7 +10,7 @@ hipError_t launch_adj32(int mc, dim3 g, dim3 b, size_t lds, hipStream_t st, cons
     switch (mc) {
         case 4: hipExtLaunchKernelGGL((k_adjoint<float, 4>), g, b, lds, st, e0, e1, 0, A); break;
         case 8: hipExtLaunchKernelGGL((k_adjoint<float, 8>), g, b, lds, st, e0, e1, 0, A); break;
-        case 12: hipExtLaunchKernelGGL((k_adjoint<float, 12>), g, b, lds, st, e0, e1, 0, A); break;
+        case 16: hipExtLaunchKernelGGL((k_adjoint<float, 16>), g, b, lds, st, e0, e1, 0, A); break;
         default: return hipErrorInvalidValue;
     }
     return hipGetLastError();

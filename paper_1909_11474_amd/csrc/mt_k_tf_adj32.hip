@@ -10,7 +10,7 @@ hipError_t launch_adj32f(int mc, dim3 g, dim3 b, size_t lds, hipStream_t st, con
                          hipEvent_t e0, hipEvent_t e1) {
     switch (mc) {
         case 4: hipExtLaunchKernelGGL((k_adjoint<float, 4, true>), g, b, lds, st, e0, e1, 0, A); break;
-        case 12: hipExtLaunchKernelGGL((k_adjoint<float, 12, true>), g, b, lds, st, e0, e1, 0, A); break;
+        case 16: hipExtLaunchKernelGGL((k_adjoint<float, 16, true>), g, b, lds, st, e0, e1, 0, A); break;
         default: return hipErrorInvalidValue;
     }
     return hipGetLastError();
