@@ -54,7 +54,7 @@ mt::SetDev mt_set::dev() const {
     d.S = S; d.N = N; d.kcap = kcap; d.nb = nb; d.nslots = nslots;
     d.st_off = st_off.as<int>(); d.st_boff = st_boff.as<int>(); d.st_slot = st_slot.as<int>();
     d.perm = perm.as<int>(); d.nnb = nnb.as<int>(); d.lbo = lbo.as<int>(); d.xbase = xbase.as<int>();
-    d.rev = rev.as<int>(); d.revc = revc.as<int>(); d.jl = jl.as<int>();
+    d.rev = rev.as<int>(); d.revc = revc.as<int>(); d.jl = jl.as<int>(); d.nbr_j = nbr_j.as<int>();
     const size_t KN = (size_t)kcap * N;
     const float* f = gf.as<float>();
     const float4* pk = gpk.as<float4>();
@@ -275,7 +275,8 @@ static int eval_impl(mt_set* set, const double* x, int form, int P, int precisio
         TRY(launch_plain(set, P, precision, MODE_EVAL, out, st, &direct));
     }
     if (direct) return MT_OK;
-    TRY(launch_large(set, P, precision, MODE_EVAL, vel, force, atom_virial, st));
+    TRY(launch_large(set, P, precision, MODE_EVAL, out, st));
+    if (finished_by_gather(set)) return MT_OK;
     return launch_finalize_eval(set, P, energy, virial, heat_current, st);
 }
 
@@ -290,7 +291,7 @@ static int fitness_sequence(mt_set* set, const double* x, int form, int P, const
     } else {
         TRY(launch_plain(set, P, precision, MODE_FIT, EvalOut{}, st));
     }
-    TRY(launch_large(set, P, precision, MODE_FIT, nullptr, nullptr, nullptr, st));
+    TRY(launch_large(set, P, precision, MODE_FIT, EvalOut{}, st));
     return launch_finalize_fit(set, P, w, Z, st, nullptr, coef);
 }
 

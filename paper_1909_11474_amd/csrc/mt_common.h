@@ -103,6 +103,7 @@ struct SetDev {
     const int* rev;                             // [kcap][N] exchange slot of the reverse bond
     const int* revc;                            // [kcap][N] structure-local CSR index of it
     const int* jl;                              // [kcap][N] structure-local neighbour atom
+    const int* nbr_j;                           // [kcap][N] neighbour atom, caller's numbering (-1: padding)
     GeomArrays<float> gf;
     GeomArrays<double> gd;
     // [15][N] cos(theta_jk) of the bond pairs j < k < 6, pair k (k - 1) / 2 + j:

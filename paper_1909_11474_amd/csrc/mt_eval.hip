@@ -353,20 +353,6 @@ __global__ __launch_bounds__(256) void k_finalize_eval(FinArgs F) {
     const bool ok = cand_valid(F.x, c, F.full);
     const double nan = __longlong_as_double(0x7ff8000000000000ll);
     double jacc[3] = {0, 0, 0};
-    if (d.S == 1) {
-        // one structure (a large cell): the whole block sums its slots, no
-        // slot-table reads and no block reduction of the heat current
-        double e, w6[6], rf, j3[3];
-        coop_struct_sums(F, c, 0, &e, w6, &rf, j3, sh);
-        if (threadIdx.x == 0) {
-            if (F.energy) F.energy[c] = ok ? e : nan;
-            if (F.virial)
-                for (int k = 0; k < 6; ++k) F.virial[(size_t)c * 6 + k] = ok ? w6[k] : nan;
-            if (F.heat)
-                for (int k = 0; k < 3; ++k) F.heat[3 * c + k] = ok ? j3[k] : nan;
-        }
-        return;
-    }
     for (int s = 0; F.coop && s < d.S; ++s) {
         if (!coop_struct(d, s)) continue;
         double e, w6[6], rf, j3[3];
@@ -845,9 +831,8 @@ static int run_plan(mt_set* set, ItemPlan* plan, const LaunchCfg& cfg, int fam, 
     return MT_OK;
 }
 
-static int launch_twopass(mt_set* set, const std::vector<int>& structs, int P, int precision,
-                          int mode, const double* vel, double* force, double* atom_virial,
-                          hipStream_t st);
+static int launch_twopass(mt_set* set, const std::vector<int>& structs, int P, int precision, int mode,
+                          const EvalOut& out, hipStream_t st);
 
 int launch_batched(mt_set* set, const LaunchCfg& cfg, int P, int precision, int mode, const EvalOut& out,
                    hipStream_t st, bool* direct) {
@@ -880,7 +865,7 @@ int launch_batched(mt_set* set, const LaunchCfg& cfg, int P, int precision, int 
     TRY_RC(run_plan(set, plan, cfg, fam, Af, Ad, 0, st));
     if (plan->twopass.empty()) return MT_OK;
     TRY_RC(reserve_twopass(set, plan, P, precision));     // no-op once reserved
-    return launch_twopass(set, plan->twopass, P, precision, mode, out.vel, out.force, out.atom_virial, st);
+    return launch_twopass(set, plan->twopass, P, precision, mode, out, st);
 }
 
 int launch_plan_fit(mt_set* set, ItemPlan* plan, const LaunchCfg& cfg, int precision, double* partial,
@@ -1031,6 +1016,10 @@ __global__ __launch_bounds__(256) void k_sum_blocks(const double* __restrict__ p
     out[((size_t)c * nslots + slot) * nv + k] = t;
 }
 
+// A set of one structure over the batching limit: the gather kernel finishes an
+// evaluation's sums.
+bool finished_by_gather(const mt_set* set) { return set->S == 1 && set->n_large == 1; }
+
 // Where the partial sums of structure s's two-pass blocks go.
 static void place_sums(mt_set* set, int s, double* partial, LArgs& L) {
     const int ns = set->h_off[s + 1] - set->h_off[s];
@@ -1050,12 +1039,15 @@ static int finish_sums(mt_set* set, int s, int P, double* partial, int nv, int n
 // Two-pass evaluation (bond gradients staged in global memory, then gathered)
 // of the listed structures, for structures too large for one block's LDS.
 template <typename S>
-static int launch_twopass_t(mt_set* set, const std::vector<int>& structs, int P, int mode, int nv,
-                            const double* vel, double* force, double* atom_virial, hipStream_t st) {
+static int launch_twopass_t(mt_set* set, const std::vector<int>& structs, int P, int mode, int nv, const EvalOut& out,
+                            hipStream_t st) {
     BArgs<S> A = make_args<S>(set, set->partial.as<double>(), nv);
-    A.vel = vel;
-    A.force = force;
-    A.atom_virial = atom_virial;
+    A.vel = out.heat ? out.vel : nullptr;
+    A.force = out.force;
+    A.atom_virial = out.atom_virial;
+    A.energy = out.energy;
+    A.virial = out.virial;
+    A.heat = out.heat;
     for (int s : structs) {
         const int mc = set->h_kmax[s] <= 4 ? 4 : 16;
         const int ns = set->h_off[s + 1] - set->h_off[s];
@@ -1070,6 +1062,8 @@ static int launch_twopass_t(mt_set* set, const std::vector<int>& structs, int P,
             LArgs L{s, c0, set->gbuf.p, nullptr, 0, set->h_off[s], ns, set->h_boff[s + 1] - set->h_boff[s], 0,
                     set->h_kmax[s]};
             place_sums(set, s, set->partial.as<double>(), L);
+            L.fin = mode == MODE_EVAL && finished_by_gather(set);
+            L.form = set->cur_form;
             dim3 grid(grid_of(ns, kLargeBlock), nc);
             hipError_t e;
             if constexpr (std::is_same<S, double>::value)
@@ -1083,25 +1077,22 @@ static int launch_twopass_t(mt_set* set, const std::vector<int>& structs, int P,
     return MT_OK;
 }
 
-static int launch_twopass(mt_set* set, const std::vector<int>& structs, int P, int precision,
-                          int mode, const double* vel, double* force, double* atom_virial,
-                          hipStream_t st) {
+static int launch_twopass(mt_set* set, const std::vector<int>& structs, int P, int precision, int mode,
+                          const EvalOut& out, hipStream_t st) {
     if (structs.empty()) return MT_OK;
     const int nv = mode == MODE_FIT ? kNVFit : kNVEval;
-    return precision == MT_FP64
-               ? launch_twopass_t<double>(set, structs, P, mode, nv, vel, force, atom_virial, st)
-               : launch_twopass_t<float>(set, structs, P, mode, nv, vel, force, atom_virial, st);
+    return precision == MT_FP64 ? launch_twopass_t<double>(set, structs, P, mode, nv, out, st)
+                                : launch_twopass_t<float>(set, structs, P, mode, nv, out, st);
 }
 
-int launch_large(mt_set* set, int P, int precision, int mode, const double* vel, double* force,
-                 double* atom_virial, hipStream_t st) {
+int launch_large(mt_set* set, int P, int precision, int mode, const EvalOut& out, hipStream_t st) {
     if (precision != MT_FP64) TRY_RC(float_tables(set, st));
     if (set->n_large == 0) return MT_OK;
     std::vector<int> structs;
     for (int s = 0; s < set->S; ++s)
         if (set->h_large[s]) structs.push_back(s);
     TRY_RC(reserve_twopass(set, nullptr, P, precision));
-    return launch_twopass(set, structs, P, precision, mode, vel, force, atom_virial, st);
+    return launch_twopass(set, structs, P, precision, mode, out, st);
 }
 
 int launch_finalize_fit(mt_set* set, int P, const double* w, double* Z, hipStream_t st,

@@ -216,8 +216,10 @@ int time_batched_kernels(mt_set* set, const LaunchCfg& cfg, int P, int precision
 int time_class_launches(mt_set* set, const LaunchCfg& cfg, int P, int precision, int reps,
                         hipStream_t stream, int max_launches, double* ms, int* mc, int* struct_launch,
                         int* n_launches);
-int launch_large(mt_set* set, int P, int precision, int mode, const double* vel, double* force,
-                 double* atom_virial, hipStream_t stream);
+int launch_large(mt_set* set, int P, int precision, int mode, const EvalOut& out, hipStream_t stream);
+// Whether launch_large's evaluation writes energy, virial and heat current itself
+// (a set of one large structure).
+bool finished_by_gather(const mt_set* set);
 // Reserve the two-pass staging buffer for the set's large structures and the
 // plan's two-pass structures (before graph capture: capture may not allocate).
 int reserve_twopass(mt_set* set, const ItemPlan* plan, int P, int precision);

@@ -136,6 +136,7 @@ struct BArgs {
     int direct;
     double* energy;
     double* virial;
+    double* heat;             // [P][3], two-pass evaluation of a set of one structure
     // adjoint inputs
     const double* coef;       // [P][S][8]
     // force residuals F - F* of the batched atoms, [P][3][N] (sorted atom
@@ -916,8 +917,8 @@ __global__ __launch_bounds__(512) void k_adjoint(BArgs<S> A) {
 // ---------------------------------------------------------------------------
 // Large structures (more atoms than one block holds): two passes per
 // candidate.  Pass 1 writes every bond gradient to global memory and the
-// energy/virial partials; pass 2 gathers forces, per-atom virial, heat
-// current and the force residual.
+// energy, virial and heat current partials; pass 2 gathers forces, per-atom
+// virial and the force residual.
 // ---------------------------------------------------------------------------
 // One staged bond gradient of the two-pass path: x, y, z and an unused
 // fourth value, so that the gather reads a partner's reverse bond with one
@@ -946,6 +947,10 @@ struct LArgs {
     // slot and largest coordination, copied from the host tables so no kernel
     // waits on reading them
     int a0, ns, nbs, slot0, kmax;
+    // evaluation of a set of one structure: the gather's last block adds up the
+    // site kernel's sums and writes energy, virial and heat current (form: 1 for
+    // Tersoff-form parameters)
+    int fin, form;
 };
 
 // Store a block's sums, values off + k for the k set in mask: its wavefronts'
@@ -969,7 +974,8 @@ __device__ __forceinline__ void large_store(const LArgs& L, int nv, int c, doubl
 
 template <typename S, int M, bool E64, bool Full>
 __device__ __forceinline__ void run_large_site(const BArgs<S>& A, const LArgs& L, int la, int atom,
-                                               bool active, double& sum, int& vidx, int rows = M) {
+                                               bool active, double& sum, int& vidx, double& jsum, int& jvidx,
+                                               int rows = M) {
     const SetDev& d = A.set;
     const int N = d.N;
     Geo<S, M, Full> g;
@@ -979,6 +985,21 @@ __device__ __forceinline__ void run_large_site(const BArgs<S>& A, const LArgs& L
     const int nbs = L.nbs;
     const int Mi = active ? d.nnb[atom] : 0;
     const int lb = active ? d.lbo[atom] : 0;
+    // the bond partners' velocities (caller's numbering): read beside the
+    // geometry where the registers hold them, else when they are used
+    constexpr bool kEarly = M <= 6;
+    int oj[MM];
+    S vj[kEarly ? MM : 1][3];
+    if (A.vel) {
+#pragma unroll
+        for (int m = 0; m < M; ++m) oj[m] = active && m < rows ? max(d.nbr_j[(size_t)m * N + atom], 0) : 0;
+        if constexpr (kEarly) {
+#pragma unroll
+            for (int m = 0; m < M; ++m)
+#pragma unroll
+                for (int k = 0; k < 3; ++k) vj[m][k] = (S)A.vel[(size_t)k * N + oj[m]];
+        }
+    }
     Rec<S> rec;
     decode_record<S, Full>(A.x + Form<Full>::nx * (size_t)c, rec);
     Cand<S, Full> p;
@@ -1009,7 +1030,27 @@ __device__ __forceinline__ void run_large_site(const BArgs<S>& A, const LArgs& L
 #pragma unroll
     for (int k = 0; k < 6; ++k) v[1 + k] = active ? (double)w6[k] : 0.0;
     v[7] = 0.0;
-    sum = group_reduce8(v, 64, &vidx);
+    sum = group_reduce8_t<64>(v, &vidx);
+    if (A.vel) {
+        // heat current sum_i W_i v_i, bond by bond from the centre's side: W_i
+        // has -d (x) G of every bond (d, G) that ends at i
+        S j3[3] = {S(0), S(0), S(0)};
+#pragma unroll
+        for (int m = 0; m < M; ++m) {
+            S vx, vy, vz;
+            if constexpr (kEarly) {
+                vx = vj[m][0]; vy = vj[m][1]; vz = vj[m][2];
+            } else {
+                vx = (S)A.vel[oj[m]]; vy = (S)A.vel[(size_t)N + oj[m]]; vz = (S)A.vel[(size_t)2 * N + oj[m]];
+            }
+            const S gv = Gx[m] * vx + Gy[m] * vy + Gz[m] * vz;
+            const S rm = g.length(m), dx = rm * g.ux[m], dy = rm * g.uy[m], dz = rm * g.uz[m];
+            j3[0] -= dx * gv; j3[1] -= dy * gv; j3[2] -= dz * gv;
+        }
+#pragma unroll
+        for (int k = 0; k < 8; ++k) v[k] = active && k < 3 ? (double)j3[k < 3 ? k : 0] : 0.0;
+        jsum = group_reduce8_t<64>(v, &jvidx);
+    }
 }
 
 // E64: float64 energy terms (the float path's energy/force/virial mode).
@@ -1021,43 +1062,82 @@ __global__ __launch_bounds__(256) void k_large_site(BArgs<S> A, LArgs L) {
     const bool active = la < Ns;
     const int atom = a0 + (active ? la : 0);
     __shared__ double sh[kLargeBlock / 64][8];
-    double sum = 0.0;
-    int vidx = (threadIdx.x & 63) >> 3;
-    bool wave_in;
+    double sum = 0.0, jsum = 0.0;
+    int vidx = (threadIdx.x & 63) >> 3, jvidx = vidx;
     if constexpr (MC <= 4) {
         // one variant for the class: the geometry rows (up to the structure's
         // largest coordination) are read without first waiting for the
         // wavefront's bond counts
-        wave_in = (la & ~63) < Ns;
-        if (wave_in) run_large_site<S, MC, E64, Full>(A, L, la, atom, active, sum, vidx, L.kmax);
+        if ((la & ~63) < Ns) run_large_site<S, MC, E64, Full>(A, L, la, atom, active, sum, vidx, jsum, jvidx, L.kmax);
     } else {
         // the wavefront's first atom has its largest coordination (sorted)
         const int first = __builtin_amdgcn_readfirstlane(la & ~63);
         const int Mw = first < Ns ? d.nnb[a0 + first] : -1;
-        wave_in = Mw >= 0;
-        if (wave_in)
+        if (Mw >= 0)
             dispatch_m<ClassLo<MC>::value, MC>(Mw, [&](auto mv) {
-                run_large_site<S, decltype(mv)::value, E64, Full>(A, L, la, atom, active, sum, vidx);
+                run_large_site<S, decltype(mv)::value, E64, Full>(A, L, la, atom, active, sum, vidx, jsum, jvidx);
             });
     }
     // no partial sums when only the staged bond gradients are wanted
     if (L.part) large_store(L, A.nv, L.c0 + blockIdx.y, sum, vidx, 0x7f, 0, sh);
+    if (L.part && A.vel) large_store(L, A.nv, L.c0 + blockIdx.y, jsum, jvidx, 0x07, 8, sh);
 }
 
+// Energy, virial and heat current of candidate c from the site kernel's sums,
+// one block: consecutive threads on consecutive values (thread t only ever sees
+// value t % 16), sixteen loads in flight each, then the lanes of equal value and
+// the wavefronts in order.
+template <typename S>
+__device__ __forceinline__ void finish_eval(const BArgs<S>& A, const LArgs& L, int c, double (*sh)[16]) {
+    static_assert(kNVEval == 16, "sixteen values per slot");
+    const double* base = L.part + ((size_t)c * L.pslots + L.slot0) * kNVEval;
+    const int total = ((L.ns + kLargeBlock - 1) / kLargeBlock) * kNVEval;
+    double acc = 0.0;
+    for (int e = threadIdx.x; e < total; e += 16 * kLargeBlock) {
+        double v[16];
+#pragma unroll
+        for (int u = 0; u < 16; ++u) v[u] = e + u * kLargeBlock < total ? base[e + u * kLargeBlock] : 0.0;
+#pragma unroll
+        for (int u = 0; u < 16; ++u) acc += v[u];
+    }
+    acc += __shfl_xor(acc, 16, 64);
+    acc += __shfl_xor(acc, 32, 64);
+    const int lane = threadIdx.x & 63, k = threadIdx.x;
+    if (lane < 16) sh[threadIdx.x >> 6][lane] = acc;
+    __syncthreads();
+    if (k >= 11 || k == 7) return;
+    double t = sh[0][k];
+    for (int w = 1; w < kLargeBlock / 64; ++w) t += sh[w][k];
+    const bool ok = L.form ? params_valid<true>(A.x + 9 * (size_t)c) : params_valid<false>(A.x + 6 * (size_t)c);
+    if (!ok) t = __longlong_as_double(0x7ff8000000000000ll);
+    if (k == 0) { if (A.energy) A.energy[c] = t; }
+    else if (k <= 6) { if (A.virial) A.virial[(size_t)c * 6 + k - 1] = t; }
+    else if (A.heat) A.heat[(size_t)c * 3 + k - 8] = t;
+}
+
+// Bound by memory latency and, for a large cell, by its 40 MB a call through the
+// caches: the rows of four bonds are read together, predicated, so that the
+// round trips go with the quads of the structure's coordination (8,000 atoms with
+// skin neighbours 11.0 us bond by bond, 10.0 us).  For a set of one structure a
+// block beyond the atoms' finishes the sums meanwhile: its own launch took 4.3 us
+// of a 23.3 us call (64,000 atoms, float64), 20.6 us without.
 template <typename S, int MODE, int MC>
 __global__ __launch_bounds__(256) void k_large_gather(BArgs<S> A, LArgs L) {
     const SetDev& d = A.set;
     const int N = d.N;
     const int a0 = L.a0, Ns = L.ns;
     const int nbs = L.nbs;
-    const int la = blockIdx.x * blockDim.x + threadIdx.x;
-    // wavefronts past the structure own no per-wavefront slot; they still take
-    // part in a block's sums (with zeros)
-    const bool wave_in = (la & ~63) < Ns;
-    const bool active = la < Ns;
-    __shared__ double sh[kLargeBlock / 64][8];
-    const int atom = a0 + (active ? la : 0);
     const int c = L.c0 + blockIdx.y;
+    if constexpr (MODE == MODE_EVAL) {
+        __shared__ double shf[kLargeBlock / 64][16];
+        if (L.fin && (int)blockIdx.x * kLargeBlock >= Ns) {
+            finish_eval(A, L, c, shf);
+            return;
+        }
+    }
+    const int la = blockIdx.x * blockDim.x + threadIdx.x;
+    const bool active = la < Ns;
+    const int atom = a0 + (active ? la : 0);
     using V4 = typename Stage4<S>::T;
     const V4* gb = reinterpret_cast<const V4*>(L.gbuf) + (size_t)blockIdx.y * nbs;
     const GeomArrays<S> G = geom_of<S>(d);
@@ -1073,49 +1153,60 @@ __global__ __launch_bounds__(256) void k_large_gather(BArgs<S> A, LArgs L) {
     S wi[9];
     for (int k = 0; k < 9; ++k) wi[k] = S(0);
 #pragma unroll
-    for (int m = 0; m < MC; ++m) {
-        if (m >= Mi) break;
-        const size_t o = (size_t)m * N + atom;
-        const int r = rv[m];
-        const V4 rg = gb[r], og = gb[lb + m];
-        const S rx = rg.x, ry = rg.y, rz = rg.z;
-        Fx += og.x - rx;
-        Fy += og.y - ry;
-        Fz += og.z - rz;
-        if (MODE == MODE_EVAL) {
-            const S rr = G.rhi[o];
-            const S dx = rr * G.ux[o], dy = rr * G.uy[o], dz = rr * G.uz[o];
-            wi[0] += dx * rx; wi[1] += dx * ry; wi[2] += dx * rz;
-            wi[3] += dy * rx; wi[4] += dy * ry; wi[5] += dy * rz;
-            wi[6] += dz * rx; wi[7] += dz * ry; wi[8] += dz * rz;
+    for (int m0 = 0; m0 < MC; m0 += 4) {
+        if (m0 >= rows) break;
+        V4 rg[4], og[4];
+        S dx[4], dy[4], dz[4];
+#pragma unroll
+        for (int q = 0; q < 4; ++q) {
+            const int m = m0 + q;
+            const bool ok = m < Mi;
+            rg[q] = ok ? gb[rv[m]] : V4{S(0), S(0), S(0), S(0)};
+            og[q] = ok ? gb[lb + m] : V4{S(0), S(0), S(0), S(0)};
+            if (MODE == MODE_EVAL) {
+                const size_t o = (size_t)m * N + atom;
+                if constexpr (sizeof(S) == 4) {
+                    const float4 u = ok ? G.pk0[o] : make_float4(0.f, 0.f, 0.f, 0.f);
+                    dx[q] = u.w * u.x; dy[q] = u.w * u.y; dz[q] = u.w * u.z;
+                } else {
+                    const S rr = ok ? G.rhi[o] : S(0), ux = ok ? G.ux[o] : S(0), uy = ok ? G.uy[o] : S(0),
+                            uz = ok ? G.uz[o] : S(0);
+                    dx[q] = rr * ux; dy[q] = rr * uy; dz[q] = rr * uz;
+                }
+            }
+        }
+#pragma unroll
+        for (int q = 0; q < 4; ++q) {
+            const S rx = rg[q].x, ry = rg[q].y, rz = rg[q].z;
+            Fx += og[q].x - rx;
+            Fy += og[q].y - ry;
+            Fz += og[q].z - rz;
+            if (MODE == MODE_EVAL) {
+                wi[0] += dx[q] * rx; wi[1] += dx[q] * ry; wi[2] += dx[q] * rz;
+                wi[3] += dy[q] * rx; wi[4] += dy[q] * ry; wi[5] += dy[q] * rz;
+                wi[6] += dz[q] * rx; wi[7] += dz[q] * ry; wi[8] += dz[q] * rz;
+            }
         }
     }
-    const int orig = active ? d.perm[atom] : 0;
-    double v[8];
-    for (int k = 0; k < 8; ++k) v[k] = 0.0;
-    int vidx;
     if (MODE == MODE_FIT) {
+        __shared__ double sh[kLargeBlock / 64][8];
+        double v[8];
+        for (int k = 0; k < 8; ++k) v[k] = 0.0;
+        int vidx;
         const S* fr = fref_of<S>(d);
         if (active) {
             const S ax = Fx - fr[atom], ay = Fy - fr[(size_t)N + atom], az = Fz - fr[(size_t)2 * N + atom];
             v[7] = (double)(ax * ax + ay * ay + az * az);
         }
-        const double sum = group_reduce8(v, 64, &vidx);
+        const double sum = group_reduce8_t<64>(v, &vidx);
         large_store(L, A.nv, c, sum, vidx, 0x80, 0, sh);
-    } else {
-        if (active && A.vel) {
-            const S vx = (S)A.vel[orig], vy = (S)A.vel[(size_t)N + orig], vz = (S)A.vel[(size_t)2 * N + orig];
-            v[0] = (double)(wi[0] * vx + wi[1] * vy + wi[2] * vz);
-            v[1] = (double)(wi[3] * vx + wi[4] * vy + wi[5] * vz);
-            v[2] = (double)(wi[6] * vx + wi[7] * vy + wi[8] * vz);
-        }
-        const double sum = group_reduce8(v, 64, &vidx);
-        large_store(L, A.nv, c, sum, vidx, 0x07, 8, sh);
-        if (active && A.force) {
+    } else if (active) {
+        const int orig = d.perm[atom];
+        if (A.force) {
             double* f = A.force + (size_t)c * 3 * N;
             f[orig] = (double)Fx; f[(size_t)N + orig] = (double)Fy; f[(size_t)2 * N + orig] = (double)Fz;
         }
-        if (active && A.atom_virial) {
+        if (A.atom_virial) {
             double* w = A.atom_virial + (size_t)c * 9 * N;
             for (int k = 0; k < 9; ++k) w[(size_t)k * N + orig] = (double)wi[k];
         }

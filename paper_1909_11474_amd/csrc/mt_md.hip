@@ -103,35 +103,33 @@ __global__ __launch_bounds__(1024) void k_kinetic(int N, const double* __restric
     if (threadIdx.x < 4) out[threadIdx.x] = sh[threadIdx.x][0];
 }
 
-// out[0] = max_i |r_i - r0_i|^2 (one block, exact: max is order independent).
-__global__ __launch_bounds__(1024) void k_max_disp(int N, const double* __restrict__ pos,
-                                                   const double* __restrict__ ref,
-                                                   double* __restrict__ out) {
-    __shared__ double sh[1024];
+// out[0] = max_i |r_i - r0_i|^2 (exact: max is order independent).  The blocks
+// meet in an atomic maximum of the bit patterns, which order like the values of
+// doubles that are not negative; k_clear sets out to zero first.  One block for
+// all atoms is bound by a single compute unit's loads: 8,000 atoms 9.6 us, 3.9 us
+// with the clear.
+__global__ void k_clear(unsigned long long* out) { *out = 0ull; }
+__global__ __launch_bounds__(256) void k_max_disp(int N, const double* __restrict__ pos,
+                                                  const double* __restrict__ ref,
+                                                  unsigned long long* __restrict__ out) {
+    __shared__ double sh[4];
+    const int i = blockIdx.x * blockDim.x + threadIdx.x;
     double a = 0.0;
-    for (int i0 = threadIdx.x; i0 < N; i0 += kBatch * blockDim.x) {
-        double d[kBatch][3];
-#pragma unroll
-        for (int b = 0; b < kBatch; ++b) {
-            const int i = i0 + b * blockDim.x;
-            const bool in = i < N;
-#pragma unroll
-            for (int k = 0; k < 3; ++k)
-                d[b][k] = in ? pos[(size_t)k * N + i] - ref[(size_t)k * N + i] : 0.0;
+    if (i < N)
+        for (int k = 0; k < 3; ++k) {
+            const double d = pos[(size_t)k * N + i] - ref[(size_t)k * N + i];
+            a += d * d;
         }
-#pragma unroll
-        for (int b = 0; b < kBatch; ++b) {
-            const double d2 = d[b][0] * d[b][0] + d[b][1] * d[b][1] + d[b][2] * d[b][2];
-            a = a > d2 ? a : d2;
-        }
+    for (int o = 32; o > 0; o >>= 1) {
+        const double b = __shfl_xor(a, o, 64);
+        a = a > b ? a : b;
     }
-    sh[threadIdx.x] = a;
+    if ((threadIdx.x & 63) == 0) sh[threadIdx.x >> 6] = a;
     __syncthreads();
-    for (int o = blockDim.x / 2; o > 0; o >>= 1) {
-        if ((int)threadIdx.x < o) sh[threadIdx.x] = fmax(sh[threadIdx.x], sh[threadIdx.x + o]);
-        __syncthreads();
+    if (threadIdx.x == 0) {
+        for (int w = 1; w < 4; ++w) a = a > sh[w] ? a : sh[w];
+        atomicMax(out, (unsigned long long)__double_as_longlong(a));
     }
-    if (threadIdx.x == 0) out[0] = sh[0];
 }
 
 }  // namespace
@@ -173,7 +171,9 @@ int mt_md_scale(int N, double* vel, double lambda, void* stream) {
 
 int mt_md_max_disp(int N, const double* pos, const double* ref, double* out, void* stream) {
     if (N <= 0 || !pos || !ref || !out) { set_error("N must be positive, pointers not NULL"); return MT_EINVAL; }
-    hipLaunchKernelGGL(k_max_disp, dim3(1), dim3(1024), 0, (hipStream_t)stream, N, pos, ref, out);
+    auto bits = reinterpret_cast<unsigned long long*>(out);
+    hipLaunchKernelGGL(k_clear, dim3(1), dim3(1), 0, (hipStream_t)stream, bits);
+    hipLaunchKernelGGL(k_max_disp, dim3(blocks_for(N)), dim3(256), 0, (hipStream_t)stream, N, pos, ref, bits);
     const hipError_t e = hipGetLastError();
     return e == hipSuccess ? MT_OK : hip_fail(e, "k_max_disp");
 }
