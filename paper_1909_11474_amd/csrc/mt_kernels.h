@@ -352,7 +352,7 @@ __device__ __forceinline__ void run_batched(const BArgs<S>& A, const Item& it, c
         S w6[6];
 #pragma unroll
         for (int k = 0; k < 6; ++k) w6[k] = S(0);
-        site_eval_sink<S, M, true, (M > kPairwiseMax), Full>(
+        site_eval_sink<S, M, true, (M > kPairwiseMax<S, Full>), Full>(
             g, p, U, [&](int m, S gx, S gy, S gz) {
                 S* slot = &xb[x.own + m * x.g].x;     // the fourth component is never read
                 slot[0] = gx;
