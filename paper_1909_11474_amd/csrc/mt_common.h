@@ -81,7 +81,8 @@ struct Item {
     int npad;
     int slot;       // its first partial-sum slot
     int xsz;        // exchange slots of one replica
-    int unused[3];  // 48 bytes
+    int R;          // replicas a block holds
+    int unused[2];  // 48 bytes
 };
 
 template <typename S>

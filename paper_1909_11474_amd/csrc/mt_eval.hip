@@ -440,9 +440,8 @@ int fit_family(int fam) {
 
 // LDS of one item of nc candidates: parameter records and the bond-gradient
 // exchange slots (4 values each) or, for the adjoint, the force residuals.
-size_t item_lds(const mt_set* set, int s, int block, int fam, int nc) {
+size_t item_lds(const mt_set* set, int s, int R, int fam, int nc) {
     const int npad = set->h_npad[s];
-    const int R = block / npad;
     const size_t e = (size_t)family_elem(fam);
     const size_t rec = family_f64(fam) ? sizeof(Rec<double>) : sizeof(Rec<float>);
     const size_t par = ((size_t)nc * rec + 31) & ~(size_t)31;
@@ -546,17 +545,16 @@ static int tile_for(const LaunchCfg& cfg, int P, int R, bool plain, int steps) {
     return std::min(tile, ((P + R - 1) / R) * R);
 }
 
-// Block size for structure s: the requested one when its LDS fits the device at
-// the smallest tile (replicas that do not fill the block leave whole wavefronts
-// idle), else the largest smaller multiple of 64 threads, at least the padded
-// size, that fits; 0 when a single replica does not fit.  Keeping the requested
-// size keeps every structure of a class in one launch.
-static int block_for(const mt_set* set, int s, const LaunchCfg& cfg, int P, int fam, bool plain) {
+// Replicas of structure s per block: as many as its threads hold, or fewer
+// (whole wavefronts of them) where the LDS cannot hold their exchanges at the
+// smallest tile; 0 when a single one does not fit.  Every structure of a class
+// stays in one launch: in a launch of its own at a smaller block size one 64-atom
+// packing of 60 structures (float64, 64 candidates) took 34 us: 150 us a call, 138 now.
+static int replicas_for(const mt_set* set, int s, int block, const LaunchCfg& cfg, int P, int fam, bool plain) {
     const int npad = set->h_npad[s];
-    const int least = std::max(64, npad);
-    for (int block = plain ? least : cfg.block; block >= least; block -= 64)
-        if (item_lds(set, s, block, fam, std::min(tile_for(cfg, P, block / npad, plain, 1), P)) <= set->lds_max)
-            return block;
+    const int step = npad < 64 ? 64 / npad : 1;
+    for (int R = block / npad; R > 0; R -= step)
+        if (item_lds(set, s, R, fam, std::min(tile_for(cfg, P, R, plain, 1), P)) <= set->lds_max) return R;
     return 0;
 }
 
@@ -643,38 +641,38 @@ ItemPlan* get_plan(mt_set* set, int P, const LaunchCfg& cfg, int fam) {
         if (!fit) return nullptr;
         not_batched.insert(fit->twopass.begin(), fit->twopass.end());
     }
-    // Launch class of each structure.  A class above 4 whose work items would
-    // fill fewer blocks than the device has compute units (with an open tile:
-    // under 16 steps for each) joins the next larger class that has work: on its
-    // own its launch leaves most of the device idle, and the larger class's kernel runs the same compiled
-    // variants (chosen per wavefront by the largest coordination, never
-    // below 3) on the same exchange-slot layout, so results are unchanged.
+    // Launch class and replicas of each structure.  A class above 4 whose work
+    // items would fill fewer blocks than the device has compute units (with an
+    // open tile: under 16 steps for each) joins the next larger class that has
+    // work: on its own its launch leaves most of the device idle, and the larger
+    // class's kernel runs the same compiled variants (chosen per wavefront by the
+    // largest coordination, never below 3) on the same exchange-slot layout, so
+    // results are unchanged.
     const std::vector<int>& classes = family_classes(fam);
-    std::vector<int> cls(set->S, 0);
+    std::vector<int> cls(set->S, 0), Rs(set->S, 0);
     std::map<int, long long> nitems;
     for (int s = 0; s < set->S; ++s) {
         if (set->h_large[s]) continue;
-        if (set->h_kmax[s] > classes.back()) {
-            // above the family's widest class: two-pass
+        const int npad = set->h_npad[s];
+        if (!plain && cfg.block < npad) return nullptr;
+        Rs[s] = replicas_for(set, s, plain ? std::max(64, npad) : cfg.block, cfg, P, fam, plain);
+        if (set->h_kmax[s] > classes.back() || Rs[s] == 0 || not_batched.count(s)) {
+            // above the family's widest class, or too large for a block's LDS
             plan->twopass.push_back(s);
             continue;
         }
         cls[s] = class_of(fam, set->h_kmax[s]);
     }
-    // block steps of structure s and their time
-    auto block_steps = [&](int s, int block) {
-        const int R = std::max(1, block / set->h_npad[s]);
-        return (P + R - 1) / R;
-    };
-    auto add_work = [&](int s, int block, std::pair<double, double>& w) {
-        const double n = block_steps(s, block);
+    // block steps of a launch and their time
+    auto add_work = [&](int s, std::pair<double, double>& w) {
+        const double n = (P + Rs[s] - 1) / Rs[s];
         w.first += n;
-        w.second += n * step_cost(set, s, std::max(1, block / set->h_npad[s]));
+        w.second += n * step_cost(set, s, Rs[s]);
     };
     // steps per item of structure s in a launch of work w (steps, time)
     auto open_steps = [&](int s, int block, int mc, const std::pair<double, double>& w) {
         const double item = auto_item(w.second, w.second / w.first, block, mc, fam, ncu);
-        return std::max(1, (int)std::lround(item / step_cost(set, s, std::max(1, block / set->h_npad[s]))));
+        return std::max(1, (int)std::lround(item / step_cost(set, s, Rs[s])));
     };
     // work and work items per class
     std::map<int, std::pair<double, double>> work_of;
@@ -682,11 +680,10 @@ ItemPlan* get_plan(mt_set* set, int P, const LaunchCfg& cfg, int fam) {
         work_of.clear();
         nitems.clear();
         for (int s = 0; s < set->S; ++s)
-            if (cls[s]) add_work(s, cfg.block, work_of[cls[s]]);
+            if (cls[s]) add_work(s, work_of[cls[s]]);
         for (int s = 0; s < set->S; ++s)
             if (cls[s]) {
-                const int steps = open_steps(s, std::max(64, cfg.block), cls[s], work_of[cls[s]]);
-                const int tile = tile_for(cfg, P, std::max(1, cfg.block / set->h_npad[s]), plain, steps);
+                const int tile = tile_for(cfg, P, Rs[s], plain, open_steps(s, cfg.block, cls[s], work_of[cls[s]]));
                 nitems[cls[s]] += (P + tile - 1) / tile;
             }
     };
@@ -699,58 +696,47 @@ ItemPlan* get_plan(mt_set* set, int P, const LaunchCfg& cfg, int fam) {
             const int to = classes[j];
             if (nitems[to] == 0) continue;
             for (int s = 0; s < set->S; ++s)
-                if (!set->h_large[s] && cls[s] == mc) cls[s] = to;
+                if (cls[s] == mc) cls[s] = to;
             count();
             break;
         }
     }
     for (int mc : classes) {
-        std::map<int, std::vector<int>> members;   // launch block size -> structures
-        std::map<int, std::pair<double, double>> work;      // and their block steps and time
+        // launch block size (one, but for the plain schedule) -> work items
+        std::map<int, Group> groups;
         for (int s = 0; s < set->S; ++s) {
-            if (set->h_large[s] || cls[s] != mc) continue;
-            if (!plain && cfg.block < set->h_npad[s]) return nullptr;
-            const int block = block_for(set, s, cfg, P, fam, plain);
-            if (block == 0 || not_batched.count(s)) {
-                plan->twopass.push_back(s);
-                continue;
-            }
-            members[block].push_back(s);
-            add_work(s, block, work[block]);
-        }
-        std::map<int, Group> groups;               // launch block size -> work items
-        for (auto& [block, structs] : members) {
+            if (cls[s] != mc) continue;
+            const int R = Rs[s];
+            const int block = plain ? std::max(64, set->h_npad[s]) : cfg.block;
             Group& g = groups[block];
-            for (int s : structs) {
-                const int R = block / set->h_npad[s];
-                int steps = open_steps(s, block, mc, work[block]);
-                int tile = tile_for(cfg, P, R, plain, steps);
-                // an open tile is halved until its records fit beside the exchange
-                while (steps > 1 && cfg.tile == 0 && item_lds(set, s, block, fam, std::min(tile, P)) > set->lds_max)
-                    tile = tile_for(cfg, P, R, plain, steps /= 2);
-                g.lds = std::max(g.lds, item_lds(set, s, block, fam, std::min(tile, P)));
-                for (int c0 = 0; c0 < P;) {
-                    Item it{};
-                    it.s = s;
-                    it.a0 = set->h_off[s];
-                    it.ns = set->h_off[s + 1] - set->h_off[s];
-                    it.npad = set->h_npad[s];
-                    it.slot = set->h_slot[s];
-                    it.xsz = set->h_xsize[s];
-                    it.c0 = c0;
-                    it.nc = std::min(tile, P - c0);
-                    if (!plain && cfg.tile == 0) {
-                        // an open tile shrinks to half of what is left (at
-                        // least a quarter of it), so that the launch ends on
-                        // short items
-                        const int left = (P - c0 + 2 * R - 1) / (2 * R), least = std::max(1, steps / 4);
-                        it.nc = std::min(it.nc, std::max(left, least) * R);
-                    }
-                    c0 += it.nc;
-                    const int n = (it.nc + R - 1) / R;
-                    it.cost = (int)std::min(16.0 * n * step_cost(set, s, R) + 1.0, 1e9);
-                    g.items.push_back(it);
+            int steps = plain ? 1 : open_steps(s, block, mc, work_of[mc]);
+            int tile = tile_for(cfg, P, R, plain, steps);
+            // an open tile is halved until its records fit beside the exchange
+            while (steps > 1 && cfg.tile == 0 && item_lds(set, s, R, fam, std::min(tile, P)) > set->lds_max)
+                tile = tile_for(cfg, P, R, plain, steps /= 2);
+            g.lds = std::max(g.lds, item_lds(set, s, R, fam, std::min(tile, P)));
+            for (int c0 = 0; c0 < P;) {
+                Item it{};
+                it.s = s;
+                it.a0 = set->h_off[s];
+                it.ns = set->h_off[s + 1] - set->h_off[s];
+                it.npad = set->h_npad[s];
+                it.slot = set->h_slot[s];
+                it.xsz = set->h_xsize[s];
+                it.R = R;
+                it.c0 = c0;
+                it.nc = std::min(tile, P - c0);
+                if (!plain && cfg.tile == 0) {
+                    // an open tile shrinks to half of what is left (at
+                    // least a quarter of it), so that the launch ends on
+                    // short items
+                    const int left = (P - c0 + 2 * R - 1) / (2 * R), least = std::max(1, steps / 4);
+                    it.nc = std::min(it.nc, std::max(left, least) * R);
                 }
+                c0 += it.nc;
+                const int n = (it.nc + R - 1) / R;
+                it.cost = (int)std::min(16.0 * n * step_cost(set, s, R) + 1.0, 1e9);
+                g.items.push_back(it);
             }
         }
         for (auto it = groups.rbegin(); it != groups.rend(); ++it) {
@@ -821,7 +807,7 @@ static int run_plan(mt_set* set, ItemPlan* plan, const LaunchCfg& cfg, int fam, 
             for (int k = 0; k < cp.n_items; ++k) {
                 const int s = cp.h_items[k].s;
                 const dim3 block(cp.block);
-                const size_t lds = item_lds(set, s, block.x, fam, 1);
+                const size_t lds = item_lds(set, s, cp.h_items[k].R, fam, 1);
                 Af.items = Ad.items = cp.items.as<Item>() + k;
                 HIPCHECK(f64 ? launch_plain64(mode, full, cp.mc, block, lds, st, Ad)
                              : launch_plain32(mode, full, cp.mc, block, lds, st, Af));

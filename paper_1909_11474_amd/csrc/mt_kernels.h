@@ -4,18 +4,20 @@
 // Batched kernel.  A work item is (structure s, candidates c0 .. c0+nc-1).  A
 // block of B threads holds R = B / npad_s replicas of the structure (npad_s is
 // the atom count rounded up to 8/16/32/64 or to a multiple of 64), one atom per
-// thread; replica q evaluates candidates c0 + q, c0 + q + R, ...  At the start
-// of an item the block decodes the item's parameter sets into LDS; the bond
-// geometry of the thread's atom is loaded once into registers and reused for
-// every candidate.  Forces need the other atom's bond gradient
+// thread, or fewer where its LDS does not hold as many exchanges (the last
+// wavefronts are idle then); replica q evaluates candidates c0 + q, c0 + q + R,
+// ...  At the start of an item the block decodes the item's parameter sets into
+// LDS; the bond geometry of the thread's atom is loaded once into registers and
+// reused for every candidate.  Forces need the other atom's bond gradient
 // (F_i = sum_j G_ij - G_ji): every thread writes its bond gradients to its
 // exchange slots in LDS and reads back the reverse bonds.  A replica of up to
 // 64 atoms lives inside one wavefront, whose LDS accesses are ordered, so it
 // needs no barrier; larger replicas synchronise the block.  Per-atom energy,
 // virial and squared force residual are reduced in float64 over aligned lane
-// groups (transpose reduction over DPP / permlane exchanges) and written to one
-// partial-sum slot per (candidate, structure, wavefront); the finalize kernels
-// add the slots in a fixed order, so results are deterministic.
+// groups (transpose reduction over DPP / permlane exchanges), the wavefronts of
+// a larger replica in LDS after that, and written to one partial-sum slot per
+// (candidate, structure); the finalize kernels add the slots in a fixed order,
+// so results are deterministic.
 //
 // Coordination classes.  Atoms inside a structure are sorted by coordination
 // and each wavefront runs the variant compiled for its largest coordination M,
@@ -170,10 +172,10 @@ __device__ __forceinline__ ItemCtx item_ctx(const SetDev& d, const Item& it) {
     x.a0 = it.a0;
     x.Ns = it.ns;
     x.npad = it.npad;
+    x.R = it.R;
     const int tid = threadIdx.x;
     if (x.npad <= 64) {
         const int sh = 31 - __clz(x.npad);
-        x.R = blockDim.x >> sh;
         x.q = tid >> sh;
         x.la = tid & (x.npad - 1);
         x.g = x.npad;
@@ -183,7 +185,6 @@ __device__ __forceinline__ ItemCtx item_ctx(const SetDev& d, const Item& it) {
         const int wpr = x.npad >> 6;                       // wavefronts per replica
         const int wid = __builtin_amdgcn_readfirstlane(tid >> 6);
         const int nw = blockDim.x >> 6;
-        x.R = nw / wpr;
         // A structure's chunks of 64 atoms get cheaper in order (atoms are
         // sorted by coordination), and wavefront w of a block runs on SIMD
         // w mod 4: rows of four wavefronts take the (chunk, replica) pairs in
@@ -211,7 +212,7 @@ __device__ __forceinline__ ItemCtx item_ctx(const SetDev& d, const Item& it) {
     x.own = x.q < x.R ? (chunk0 ? d.xbase[x.a0 + chunk0] : 0) + (x.la - chunk0) + x.q * x.xsz : 0;
     // the wavefront's largest coordination is that of its first atom (sorted);
     // -1: no replica here (whole wavefronts past the last replica)
-    x.Mw = x.npad > 64 && __builtin_amdgcn_readfirstlane(x.q) >= x.R ? -1 : d.nnb[x.a0 + chunk0];
+    x.Mw = __builtin_amdgcn_readfirstlane(x.q) >= x.R ? -1 : d.nnb[x.a0 + chunk0];
     return x;
 }
 
@@ -430,11 +431,9 @@ __device__ __forceinline__ void run_batched(const BArgs<S>& A, const Item& it, c
     }
 }
 
-__device__ __forceinline__ void run_idle(int steps, int barriers) {
+__device__ __forceinline__ void run_idle(int barriers) {
     __syncthreads();                                   // the records
-    for (int step = 0; step < steps; ++step)
-        for (int b = 0; b < barriers; ++b) __syncthreads();
-    __syncthreads();                                   // the last step's sums
+    for (int b = 0; b < barriers; ++b) __syncthreads();
 }
 
 // Call f(integral_constant<M>) for the variant that serves coordination m.
@@ -471,9 +470,9 @@ __device__ __forceinline__ void batched_item(const BArgs<S>& A, const Item& it, 
     decode_item<S, Full>(A, it, lds);
     const int Mw = x.Mw;
     if (Mw < 0) {
-        // whole wavefront outside every replica: only larger replicas have such
-        // wavefronts, and they synchronise the block twice per step
-        run_idle(x.steps, 2);
+        // whole wavefront outside every replica; replicas of several wavefronts
+        // synchronise the block twice per step and once at the end
+        run_idle(x.block_sync ? 2 * x.steps + 1 : 0);
         return;
     }
     dispatch_m<ClassLo<MC>::value, MC>(Mw, [&](auto mv) {
@@ -893,7 +892,7 @@ __device__ __forceinline__ void adjoint_item(const BArgs<S>& A, const Item& it, 
     decode_item<S, Full>(A, it, lds);
     const int Mw = x.Mw;
     if (Mw < 0) {
-        run_idle(x.steps, 2);
+        run_idle(x.block_sync ? 2 * x.steps + 1 : 0);
         return;
     }
     dispatch_m<ClassLo<MC>::value, MC>(Mw, [&](auto mv) {

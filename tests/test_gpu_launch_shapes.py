@@ -1,7 +1,8 @@
 """Launch shapes the other tests do not reach: every block size in whole
 wavefronts (rows of one to four wavefronts in the last place of a block, which
 take the costly and cheap chunks of 64 atoms in turn), and the work lists of an
-open tile at small, odd and large populations.
+open tile at small, odd and large populations, and structures of many neighbours
+of which a block's LDS holds fewer replicas than its threads would.
 
 Z in float64 is bit-identical to the plain schedule (one item per launch); in
 float32 it is bit-identical across shapes.
@@ -63,3 +64,36 @@ def test_open_tile(tset, P):
     _, G = tset.fitness_grad(X, precision="fp64")
     _, g = tset.fitness_grad(X[-1:], precision="fp64")
     assert np.array_equal(G[-1:].cpu().numpy(), g.cpu().numpy())
+
+
+# atoms, density (random packing, at least 1.9 A apart) and seed; 256 atoms are
+# a close-packed cell, whose exchange fills more than half of a block's LDS
+DENSE = [(8, 0.1, 8010), (16, 0.1, 16010), (32, 0.1, 32050), (64, 0.1, 64010), (256, None, 0)]
+
+
+@pytest.mark.parametrize("n,rho,seed", DENSE)
+def test_fewer_replicas_than_a_block_has_threads_for(n, rho, seed):
+    import torch
+    if not torch.cuda.is_available():
+        pytest.skip("no GPU")
+    from paper_1909_11474_amd import api
+    if rho is None:
+        grid = np.array([[i, j, k] for i in range(4) for j in range(4) for k in range(4)], dtype=float)
+        base = 0.5 * np.array([[0, 0, 0], [0, 1, 1], [1, 0, 1], [1, 1, 0]])
+        a = 2.95 * np.sqrt(2.0)
+        dense = (W.displace(rng(1), (grid[:, None] + base[None]).reshape(-1, 3) * a, 0.02), np.eye(3) * 4 * a)
+    else:
+        dense = W.random_packing(rng(seed), n, rho=rho, dmin=1.9)
+    s = W.make_set([W.random_packing(rng(9), 9), dense])
+    X = W.draw_params(rng(3), 70)
+    ts = api.from_structures(s)
+    kmax = ts.stats()["max_coordination"]
+    assert 512 * kmax * 32 > 160 * 1024              # bytes of exchange of a full block
+    ref = ts.tersoff_eval(X[:1], precision="fp64")
+    m = torch.as_tensor(s.sizes(), dtype=torch.float64, device="cuda")
+    ts.attach_reference(ref["E"][0] / m, ref["W"][0] / m[:, None], ref["F"][0])
+    for P in (1, 7, 70):
+        got = ts.fitness(X[:P], precision="fp64").cpu().numpy()
+        plain = ts.fitness(X[:P], precision="fp64", schedule="plain").cpu().numpy()
+        assert np.array_equal(got, plain), P
+    ts.close()
