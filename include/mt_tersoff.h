@@ -331,6 +331,13 @@ int mt_md_scale(int N, double* vel, double lambda, void* stream);
 int mt_md_kinetic(int N, const double* vel, const double* mass, double* out, void* stream);
 /* out (device [1]) = max_i |r_i - ref_i|^2 (A^2), for the skin check. */
 int mt_md_max_disp(int N, const double* pos, const double* ref, double* out, void* stream);
+/*
+ * mt_md_kick(dt_half), mt_md_drift(dt) and, with ref and out (both or neither),
+ * mt_md_max_disp in one pass over the atoms; the same results.
+ */
+int mt_md_first_half(int N, double* vel, const double* force, const double* atom_virial,
+                     const double* virial, const double* fe, const double* inv_mass, double dt_half,
+                     double* pos, double dt, const double* ref, double* out, void* stream);
 
 /*
  * Choose launch shapes (block size, candidate tile, schedule) for this set

@@ -47,6 +47,7 @@ SIGNATURES = {
     "mt_md_max_disp": (_i, [_i, _vp, _vp, _vp, _vp]),
     "mt_md_kick": (_i, [_i, _vp, _vp, _vp, _vp, ctypes.POINTER(_d), _vp, _d, _vp]),
     "mt_md_drift": (_i, [_i, _vp, _vp, _d, _vp]),
+    "mt_md_first_half": (_i, [_i, _vp, _vp, _vp, _vp, ctypes.POINTER(_d), _vp, _d, _vp, _d, _vp, _vp, _vp]),
     "mt_md_scale": (_i, [_i, _vp, _d, _vp]),
     "mt_md_kinetic": (_i, [_i, _vp, _vp, _vp, _vp]),
     "tersoff_eval": (_i, [_vp, _vp, _i, _i, _i, _vp, _vp, _vp, _vp, _vp, _vp, _vp]),

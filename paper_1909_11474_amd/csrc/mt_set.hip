@@ -409,7 +409,13 @@ __global__ void k_ang_moments(int N, int kcap, const int* __restrict__ nnb, cons
 
 // Bond geometry for every (sorted atom, slot).  Padded slots (m >= coordination)
 // get f_C = f_C' = 0 and a zero unit vector, so they add nothing anywhere.
-__global__ void k_geometry(int N, int S, int kcap, double R1, double R2,
+// Lists: the lists are new.  Otherwise only positions moved: the padded slots
+// and the tables of reverse bonds and neighbour atoms stand as they are, and the
+// grid covers the slots up to the set's largest coordination.  A step of molecular
+// dynamics is bound by such short kernels (8,000 atoms, most with 4 of 16 slots in
+// use: 8.8 us with the lists, 4.4 us without).
+template <bool Lists>
+__global__ void k_geometry(int N, int S, int kcap, int slots, double R1, double R2,
                            const int* __restrict__ st_off, const double* __restrict__ pos,
                            const StructMeta* __restrict__ meta, const int* __restrict__ perm,
                            const int* __restrict__ inv, const int* __restrict__ cnt,
@@ -421,12 +427,13 @@ __global__ void k_geometry(int N, int S, int kcap, double R1, double R2,
                            int* __restrict__ rev, int* __restrict__ revc, int* __restrict__ jl,
                            int* __restrict__ nbr_j, int* __restrict__ nbr_sh, int* __restrict__ flags) {
     int idx = blockIdx.x * blockDim.x + threadIdx.x;
-    if (idx >= N * kcap) return;
+    if (idx >= N * slots) return;
     const int a = idx % N;          // sorted atom
     const int m = idx / N;          // slot
     const size_t KN = (size_t)kcap * N;
     const int i = perm[a];
     const int M = cnt[i];
+    if (!Lists && m >= M) return;
     const int o = m * N + a;
     float* f_ux = gf;         float* f_uy = gf + KN;    float* f_uz = gf + 2 * KN;
     float* f_rhi = gf + 3 * KN; float* f_rinv = gf + 4 * KN;
@@ -479,6 +486,7 @@ __global__ void k_geometry(int N, int S, int kcap, double R1, double R2,
     f_rinv[o] = (float)rinv; f_fc[o] = (float)fc; f_hfcp[o] = (float)hfcp;
     gpk[o] = make_float4((float)ux, (float)uy, (float)uz, rhi);
     gpk[KN + o] = make_float4((float)(r - (double)rhi), (float)rinv, (float)fc, (float)hfcp);
+    if (!Lists) return;
     // reverse entry: (j -> i, -shift) in j's sorted list
     const int want = pack_shift(-n1, -n2, -n3);
     const int Mj = cnt[j];
@@ -775,8 +783,8 @@ int build_set(mt_set* set, const int64_t* atom_offset, const double* pos, const 
     HIPCHECK(set->nbr_j.reserve(sizeof(int) * KN));
     HIPCHECK(set->nbr_sh.reserve(sizeof(int) * KN));
     HIPCHECK(hipMemsetAsync(B.flags, 0, sizeof(int) * 4, st));
-    k_geometry<<<grid_of((long long)KN, 256), 256, 0, st>>>(
-        N, S, kcap, set->R1, set->R2, set->st_off.as<int>(), set->pos.as<double>(),
+    k_geometry<true><<<grid_of((long long)KN, 256), 256, 0, st>>>(
+        N, S, kcap, kcap, set->R1, set->R2, set->st_off.as<int>(), set->pos.as<double>(),
         meta.as<StructMeta>(), set->perm.as<int>(), inv.as<int>(), cnt.as<int>(), ent_j.as<int>(),
         ent_sh.as<int>(), set->lbo.as<int>(), set->xbase.as<int>(), set->st_npad.as<int>(),
         set->gf.as<float>(), set->gf_rlo.as<float>(), set->gpk.as<float4>(),
@@ -797,11 +805,10 @@ int build_set(mt_set* set, const int64_t* atom_offset, const double* pos, const 
 int update_geometry(mt_set* set, const double* pos, hipStream_t st) {
     const int S = set->S, N = set->N, kcap = set->kcap;
     BuildScratch& B = set->build;
-    const size_t KN = (size_t)kcap * N;
     if (pos != set->pos.p)
         HIPCHECK(hipMemcpyAsync(set->pos.p, pos, sizeof(double) * 3 * N, hipMemcpyDeviceToDevice, st));
-    k_geometry<<<grid_of((long long)KN, 256), 256, 0, st>>>(
-        N, S, kcap, set->R1, set->R2, set->st_off.as<int>(), set->pos.as<double>(),
+    if (set->kmax > 0) k_geometry<false><<<grid_of((long long)set->kmax * N, 256), 256, 0, st>>>(
+        N, S, kcap, set->kmax, set->R1, set->R2, set->st_off.as<int>(), set->pos.as<double>(),
         B.meta.as<StructMeta>(), set->perm.as<int>(), B.inv.as<int>(), B.cnt.as<int>(), B.ent_j.as<int>(),
         B.ent_sh.as<int>(), set->lbo.as<int>(), set->xbase.as<int>(), set->st_npad.as<int>(),
         set->gf.as<float>(), set->gf_rlo.as<float>(), set->gpk.as<float4>(),

@@ -2,7 +2,7 @@
 Sec. IV.C: equilibrium MD and homogeneous non-equilibrium MD of diamond Si).
 
 One structure (a periodic cell) per run.  A step is velocity Verlet:
-  mt_md_kick(dt/2), mt_md_drift(dt), position update,
+  mt_md_first_half (kick by dt/2, drift by dt), position update,
   tersoff_eval (forces, virial, per-atom virial, heat current), mt_md_kick(dt/2),
 then, with a thermostat, a velocity rescaling toward the target temperature
 (Berendsen: lambda^2 = 1 + dt/tau (T0/T - 1)).  With a driving force F_e the
@@ -13,7 +13,7 @@ kappa = <J> . F_e / (T V |F_e|^2) (Sec. IV.C).
 The position update rebuilds the neighbour lists (mt_set_update_positions)
 when skin = 0; with a Verlet skin the lists hold pairs within R2 + skin and
 only the bond geometry is recomputed (mt_set_update_geometry) until some atom
-has moved skin/2 since the last rebuild (mt_md_max_disp).
+has moved skin/2 since the last rebuild (checked in mt_md_first_half).
 
 Every step runs in the library's kernels; the host keeps only per-step
 scalars (potential energy, kinetic sums, J and the skin's displacement check),
@@ -112,11 +112,12 @@ class MD:
         self._a_kick = (self.N, P(self.vel), P(self.F), P(self.Wi) if drive else None,
                         P(self.W) if drive else None, self.fe if drive else None, P(self.inv_mass),
                         ctypes.c_double(0.5 * self.dt), st)
-        self._a_drift = (self.N, P(self.pos), P(self.vel), ctypes.c_double(self.dt), st)
         self._a_kinetic = (self.N, P(self.vel), P(self.mass), P(self.kin), st)
         self._a_geometry = (self.ts._handle, P(self.pos), st)
+        self._a_first = self._a_kick[:-1] + (P(self.pos), ctypes.c_double(self.dt),
+                                             P(self.ref) if self.skin > 0 else None,
+                                             P(self.disp) if self.skin > 0 else None, st)
         if self.skin > 0:
-            self._a_disp = (self.N, P(self.pos), P(self.ref), P(self.disp), st)
             self._disp_limit = (0.5 * self.skin) ** 2
 
     def _forces(self):
@@ -126,11 +127,8 @@ class MD:
         L.check(self._lib.mt_md_kick(*self._a_kick), "mt_md_kick")
 
     def _first_half(self):
-        """Kick, drift and, with a skin, the displacement check (on the GPU)."""
-        self._kick()
-        L.check(self._lib.mt_md_drift(*self._a_drift), "mt_md_drift")
-        if self.skin > 0:
-            L.check(self._lib.mt_md_max_disp(*self._a_disp), "mt_md_max_disp")
+        """Kick, drift and, with a skin, the displacement check (one kernel)."""
+        L.check(self._lib.mt_md_first_half(*self._a_first), "mt_md_first_half")
 
     def _read_scalars(self):
         with torch.cuda.stream(self._tstream):
