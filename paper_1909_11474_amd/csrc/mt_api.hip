@@ -113,9 +113,9 @@ ProfScope::ProfScope(mt_set* set, int kind) {
 }  // namespace mt
 
 // Reserve per-call workspaces; any reallocation invalidates captured graphs.
-static int ensure_workspace(mt_set* set, int P, int nv) {
+static int ensure_workspace(mt_set* set, int P, int nv, int slots) {
     const void* before = set->partial.p;
-    HIPCHECK(set->partial.reserve(sizeof(double) * nv * (size_t)P * std::max(1, set->nslots)));
+    HIPCHECK(set->partial.reserve(sizeof(double) * nv * (size_t)P * std::max(1, slots)));
     if (before != set->partial.p) clear_graphs(set);
     return MT_OK;
 }
@@ -260,7 +260,7 @@ static int eval_impl(mt_set* set, const double* x, int form, int P, int precisio
         return fail(MT_EINVAL, "schedule must be MT_BATCHED or MT_PLAIN");
     if (heat_current && !vel) return fail(MT_EINVAL, "heat_current needs vel");
     hipStream_t st = (hipStream_t)stream;
-    TRY(ensure_workspace(set, P, kNVEval));
+    TRY(ensure_workspace(set, P, kNVEval, eval_slots(set, P)));
     set->fit_P = 0;
     set->cur_x = x;
     set->cur_form = form;
@@ -313,7 +313,7 @@ static int fitness_impl(mt_set* set, const double* x, int form, int P, const dou
     if (schedule != MT_BATCHED && schedule != MT_PLAIN)
         return fail(MT_EINVAL, "schedule must be MT_BATCHED or MT_PLAIN");
     hipStream_t st = (hipStream_t)stream;
-    TRY(ensure_workspace(set, P, kNVFit));
+    TRY(ensure_workspace(set, P, kNVFit, set->nslots));
     set->fit_P = 0;
     const LaunchCfg cfg = cfg_for(set, P, precision);
     if (schedule == MT_PLAIN || set->profiling || !cfg.graph)
@@ -410,7 +410,7 @@ static int grad_impl(mt_set* set, const double* x, int form, int P, const double
     TRY(check_fitness(set, x, P, w, precision, Z));
     if (!dZdx) return fail(MT_EINVAL, "dZdx must not be NULL");
     hipStream_t st = (hipStream_t)stream;
-    TRY(ensure_workspace(set, P, kNVFit));
+    TRY(ensure_workspace(set, P, kNVFit, set->nslots));
     // force residuals of the batched atoms, written by the fitness and read by
     // the adjoint
     HIPCHECK(set->resid.reserve((precision == MT_FP64 ? sizeof(double) : sizeof(float)) * 3 * (size_t)P *
@@ -530,7 +530,7 @@ int mt_profile_fitness_kernels(mt_set* set, const double* x, int nx, int P, int 
     if (reps <= 0) return fail(MT_EINVAL, "reps must be positive");
     if (!ms || !launches) return fail(MT_EINVAL, "ms and launches must not be NULL");
     if (!set->has_ref) return fail(MT_ENOREF, "no reference data attached to the set");
-    TRY(ensure_workspace(set, P, kNVFit));
+    TRY(ensure_workspace(set, P, kNVFit, set->nslots));
     set->fit_P = 0;
     set->cur_x = x;
     set->cur_form = nx == 9 ? 1 : 0;
@@ -546,7 +546,7 @@ int mt_profile_fitness_launches(mt_set* set, const double* x, int nx, int P, int
     if (reps <= 0 || max_launches <= 0) return fail(MT_EINVAL, "reps and max_launches must be positive");
     if (!ms || !coordination_class || !n_launches) return fail(MT_EINVAL, "NULL output");
     if (!set->has_ref) return fail(MT_ENOREF, "no reference data attached to the set");
-    TRY(ensure_workspace(set, P, kNVFit));
+    TRY(ensure_workspace(set, P, kNVFit, set->nslots));
     set->fit_P = 0;
     set->cur_x = x;
     set->cur_form = nx == 9 ? 1 : 0;
@@ -641,7 +641,7 @@ int mt_autotune(mt_set* set, int P, int precision, const char* cache_path) {
         HIPCHECK(hipMemset(set->fref32.p, 0, sizeof(float) * 3 * set->N));
         HIPCHECK(hipMemset(set->fref64.p, 0, sizeof(double) * 3 * set->N));
     }
-    int rc = ensure_workspace(set, P, kNVFit);
+    int rc = ensure_workspace(set, P, kNVFit, set->nslots);
     if (rc) { (void)hipStreamDestroy(st); return rc; }
     set->fit_P = 0;
     set->cur_x = xb.as<double>();

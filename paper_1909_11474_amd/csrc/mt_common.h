@@ -40,8 +40,9 @@ constexpr int kMaxBatched = 512;   // largest structure of the batched kernel
 // LDS in front of a batched block's records: the sums of up to eight wavefronts,
 // sixteen values each.
 constexpr int kRedBytes = 8 * 16 * 8;
-// Threads per block of the two-pass kernels; a structure over the batching
-// limit has one partial-sum slot per such block.
+// Threads per block of the two-pass kernels (evaluations of one structure of few
+// atoms: see site_block); a structure over the batching limit has one partial-sum
+// slot per such block.
 constexpr int kLargeBlock = 256;
 constexpr int kNVFit = 8;          // partial sums per slot: E, W6, |F - F*|^2
 constexpr int kNVEval = 16;        // E, W6, |F-F*|^2, J3, unused

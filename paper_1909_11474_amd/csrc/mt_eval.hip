@@ -1006,6 +1006,19 @@ __global__ __launch_bounds__(256) void k_sum_blocks(const double* __restrict__ p
 // evaluation's sums.
 bool finished_by_gather(const mt_set* set) { return set->S == 1 && set->n_large == 1; }
 
+// Threads per block of that evaluation's two kernels by atoms times candidates:
+// single wavefronts while blocks of four would leave compute units idle (8,000
+// atoms, of skin neighbours: 32 compute units busy, site 12.8 us and gather 9.0 us;
+// 10.4 and 5.2 us over 125).  Above, the block that finishes the sums decides: it
+// adds one slot per site block with the threads of a gather block, 64,000 atoms
+// 20.4 us a call with one-wavefront site blocks and 32.4 us with both (20.9 with
+// neither), 125,000 atoms 29.3 and 51.8 us (26.6).
+static int site_block(long long atoms) { return atoms <= 65536 ? 64 : kLargeBlock; }
+static int gather_block(long long atoms) { return atoms <= 16384 ? 64 : kLargeBlock; }
+int eval_slots(const mt_set* set, int P) {
+    return finished_by_gather(set) ? grid_of(set->N, site_block((long long)P * set->N)) : set->nslots;
+}
+
 // Where the partial sums of structure s's two-pass blocks go.
 static void place_sums(mt_set* set, int s, double* partial, LArgs& L) {
     const int ns = set->h_off[s + 1] - set->h_off[s];
@@ -1050,12 +1063,15 @@ static int launch_twopass_t(mt_set* set, const std::vector<int>& structs, int P,
             place_sums(set, s, set->partial.as<double>(), L);
             L.fin = mode == MODE_EVAL && finished_by_gather(set);
             L.form = set->cur_form;
-            dim3 grid(grid_of(ns, kLargeBlock), nc);
+            const int block = L.fin ? site_block((long long)P * ns) : kLargeBlock;
+            L.gblock = gather_block((long long)P * ns);
+            if (L.fin) L.pslots = eval_slots(set, P);
+            dim3 grid(grid_of(ns, block), nc);
             hipError_t e;
             if constexpr (std::is_same<S, double>::value)
-                e = launch_large64(mc, mode, set->cur_form, grid, dim3(kLargeBlock), st, A, L);
+                e = launch_large64(mc, mode, set->cur_form, grid, dim3(block), st, A, L);
             else
-                e = launch_large32(mc, mode, set->cur_form, grid, dim3(kLargeBlock), st, A, L);
+                e = launch_large32(mc, mode, set->cur_form, grid, dim3(block), st, A, L);
             HIPCHECK(e);
         }
         TRY_RC(finish_sums(set, s, P, set->partial.as<double>(), nv, mode == MODE_FIT ? 8 : 11, st));

@@ -220,6 +220,8 @@ int launch_large(mt_set* set, int P, int precision, int mode, const EvalOut& out
 // Whether launch_large's evaluation writes energy, virial and heat current itself
 // (a set of one large structure).
 bool finished_by_gather(const mt_set* set);
+// Partial-sum slots per candidate of an evaluation of P candidates.
+int eval_slots(const mt_set* set, int P);
 // Reserve the two-pass staging buffer for the set's large structures and the
 // plan's two-pass structures (before graph capture: capture may not allocate).
 int reserve_twopass(mt_set* set, const ItemPlan* plan, int P, int precision);

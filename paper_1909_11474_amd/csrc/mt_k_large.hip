@@ -33,7 +33,10 @@ static hipError_t launch_large_pair(int mc, int mode, int full, dim3 g, dim3 b, 
                               : launch_large_form<S, false>(mc, mode, g, b, st, A, L);
     if (e != hipSuccess) return e;
     if (mode == MODE_STAGE) return hipGetLastError();
-    if (mode == MODE_EVAL && L.fin) ++g.x;         // the block that finishes the sums
+    if (mode == MODE_EVAL && L.fin) {
+        b = dim3(L.gblock);
+        g.x = (L.ns + L.gblock - 1) / L.gblock + 1;    // one block finishes the sums
+    }
     if (mc == 4) {
         if (mode == MODE_FIT) hipLaunchKernelGGL((k_large_gather<S, MODE_FIT, 4>), g, b, 0, st, A, L);
         else hipLaunchKernelGGL((k_large_gather<S, MODE_EVAL, 4>), g, b, 0, st, A, L);

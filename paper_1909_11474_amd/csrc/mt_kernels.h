@@ -937,19 +937,20 @@ struct LArgs {
     int s, c0;                 // structure, first candidate of the chunk
     void* gbuf;                // [chunk][nbs] of Stage4<S> (x, y, z, unused)
     // where the blocks' partial sums go, [candidate][pslots][nv] (null: nowhere):
-    // the set's slots, one per block of a structure over the batching limit, or
-    // a buffer of their own that k_sum_blocks adds up (a batched structure sent
-    // to the two-pass path has one slot)
+    // the set's slots, one per block of a structure over the batching limit, as
+    // many as the site kernel has blocks (fin), or a buffer of their own that
+    // k_sum_blocks adds up (a batched structure sent to the two-pass path has one slot)
     double* part;
     int pslots;
     // the structure's first atom, atom count, bond count, first partial-sum
     // slot and largest coordination, copied from the host tables so no kernel
     // waits on reading them
     int a0, ns, nbs, slot0, kmax;
-    // evaluation of a set of one structure: the gather's last block adds up the
+    // evaluation of a set of one structure: the gather's first block adds up the
     // site kernel's sums and writes energy, virial and heat current (form: 1 for
     // Tersoff-form parameters)
     int fin, form;
+    int gblock;                // with fin: threads of a gather block
 };
 
 // Store a block's sums, values off + k for the k set in mask: its wavefronts'
@@ -1083,19 +1084,19 @@ __global__ __launch_bounds__(256) void k_large_site(BArgs<S> A, LArgs L) {
 }
 
 // Energy, virial and heat current of candidate c from the site kernel's sums,
-// one block: consecutive threads on consecutive values (thread t only ever sees
-// value t % 16), sixteen loads in flight each, then the lanes of equal value and
-// the wavefronts in order.
+// one block of any number of wavefronts: consecutive threads on consecutive
+// values (thread t only ever sees value t % 16), sixteen loads in flight each,
+// then the lanes of equal value and the wavefronts in order.
 template <typename S>
 __device__ __forceinline__ void finish_eval(const BArgs<S>& A, const LArgs& L, int c, double (*sh)[16]) {
     static_assert(kNVEval == 16, "sixteen values per slot");
-    const double* base = L.part + ((size_t)c * L.pslots + L.slot0) * kNVEval;
-    const int total = ((L.ns + kLargeBlock - 1) / kLargeBlock) * kNVEval;
+    const double* base = L.part + (size_t)c * L.pslots * kNVEval;
+    const int total = L.pslots * kNVEval, nt = blockDim.x;
     double acc = 0.0;
-    for (int e = threadIdx.x; e < total; e += 16 * kLargeBlock) {
+    for (int e = threadIdx.x; e < total; e += 16 * nt) {
         double v[16];
 #pragma unroll
-        for (int u = 0; u < 16; ++u) v[u] = e + u * kLargeBlock < total ? base[e + u * kLargeBlock] : 0.0;
+        for (int u = 0; u < 16; ++u) v[u] = e + u * nt < total ? base[e + u * nt] : 0.0;
 #pragma unroll
         for (int u = 0; u < 16; ++u) acc += v[u];
     }
@@ -1106,7 +1107,7 @@ __device__ __forceinline__ void finish_eval(const BArgs<S>& A, const LArgs& L, i
     __syncthreads();
     if (k >= 11 || k == 7) return;
     double t = sh[0][k];
-    for (int w = 1; w < kLargeBlock / 64; ++w) t += sh[w][k];
+    for (int w = 1; w < nt >> 6; ++w) t += sh[w][k];
     const bool ok = L.form ? params_valid<true>(A.x + 9 * (size_t)c) : params_valid<false>(A.x + 6 * (size_t)c);
     if (!ok) t = __longlong_as_double(0x7ff8000000000000ll);
     if (k == 0) { if (A.energy) A.energy[c] = t; }
@@ -1118,7 +1119,7 @@ __device__ __forceinline__ void finish_eval(const BArgs<S>& A, const LArgs& L, i
 // caches: the rows of four bonds are read together, predicated, so that the
 // round trips go with the quads of the structure's coordination (8,000 atoms with
 // skin neighbours 11.0 us bond by bond, 10.0 us).  For a set of one structure a
-// block beyond the atoms' finishes the sums meanwhile: its own launch took 4.3 us
+// block before the atoms' finishes the sums meanwhile: its own launch took 4.3 us
 // of a 23.3 us call (64,000 atoms, float64), 20.6 us without.
 template <typename S, int MODE, int MC>
 __global__ __launch_bounds__(256) void k_large_gather(BArgs<S> A, LArgs L) {
@@ -1129,12 +1130,12 @@ __global__ __launch_bounds__(256) void k_large_gather(BArgs<S> A, LArgs L) {
     const int c = L.c0 + blockIdx.y;
     if constexpr (MODE == MODE_EVAL) {
         __shared__ double shf[kLargeBlock / 64][16];
-        if (L.fin && (int)blockIdx.x * kLargeBlock >= Ns) {
+        if (L.fin && blockIdx.x == 0) {
             finish_eval(A, L, c, shf);
             return;
         }
     }
-    const int la = blockIdx.x * blockDim.x + threadIdx.x;
+    const int la = (blockIdx.x - (MODE == MODE_EVAL && L.fin)) * blockDim.x + threadIdx.x;
     const bool active = la < Ns;
     const int atom = a0 + (active ? la : 0);
     using V4 = typename Stage4<S>::T;
