@@ -19,8 +19,8 @@
 //
 // Exchange slots (LDS of the batched kernels).  A replica of structure s is cut
 // into chunks of G = min(npad, 64) lanes; chunk c reserves K_c * G slots, K_c
-// being the largest coordination in the chunk (at least the lowest variant of
-// the structure's class), and bond m of the atom in lane l of the chunk uses
+// being the largest coordination in the chunk (at least 3, the lowest variant of
+// the classes above 4), and bond m of the atom in lane l of the chunk uses
 // slot off_c + m * G + l.  Padded bonds (m >= coordination) own a slot too and
 // their reverse index is that slot, so the exchange needs no predicates.
 //

@@ -647,7 +647,12 @@ ItemPlan* get_plan(mt_set* set, int P, const LaunchCfg& cfg, int fam) {
     // work: on its own its launch leaves most of the device idle, and the larger
     // class's kernel runs the same compiled variants (chosen per wavefront by the
     // largest coordination, never below 3) on the same exchange-slot layout, so
-    // results are unchanged.
+    // results are unchanged.  Class 4 joins where the whole call is latency: an open
+    // tile, at most three steps for a structure on average and fewer steps than
+    // compute units (18 structures x 5 candidates, Tersoff form, gradient:
+    // 199 us a call with launches of its own, 178 us).  With more steps its own
+    // kernel, of twice the wavefronts in flight in float, soon makes up for the
+    // launch, and the launches' times stay those of one class each.
     const std::vector<int>& classes = family_classes(fam);
     std::vector<int> cls(set->S, 0), Rs(set->S, 0);
     std::map<int, long long> nitems;
@@ -690,7 +695,10 @@ ItemPlan* get_plan(mt_set* set, int P, const LaunchCfg& cfg, int fam) {
     if (!plain) count();
     for (size_t i = 0; !plain && i < classes.size(); ++i) {
         const int mc = classes[i];
-        if (mc <= 4 || nitems[mc] == 0) continue;
+        if (nitems[mc] == 0) continue;
+        if (mc <= 4 && (cfg.tile != 0 || work_of[mc].first >= ncu ||
+                        work_of[mc].first > 3.0 * std::count(cls.begin(), cls.end(), mc)))
+            continue;
         if (cfg.tile == 0 ? work_of[mc].first >= 16.0 * ncu : nitems[mc] >= ncu) continue;
         for (size_t j = i + 1; j < classes.size(); ++j) {
             const int to = classes[j];

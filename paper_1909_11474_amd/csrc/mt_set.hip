@@ -324,7 +324,8 @@ __global__ __launch_bounds__(kSortMax) void k_sort_tables(
     }
     // Exchange slots of the batched kernels (structures up to kMaxBatched atoms):
     // chunks of G lanes, chunk c holds K_c * G slots, K_c the coordination of
-    // its first atom (at least the lowest variant of the structure's class).
+    // its first atom (at least the lowest variant of the classes above 4, whose
+    // launches may also run structures of class 4).
     const int npad = st_npad[s];
     __shared__ int choff[kMaxBatched / 8 + 1];
     __syncthreads();
@@ -332,7 +333,7 @@ __global__ __launch_bounds__(kSortMax) void k_sort_tables(
         const int G = npad < 64 ? npad : 64;
         const int nch = npad / G;
         if (t == 0) {
-            const int lo = nnb[a0] <= 4 ? 0 : 3;     // lowest variant of the structure's class
+            const int lo = 3;
             int off = 0;
             for (int c = 0; c < nch; ++c) {
                 choff[c] = off;

@@ -2,7 +2,8 @@
 wavefronts (rows of one to four wavefronts in the last place of a block, which
 take the costly and cheap chunks of 64 atoms in turn), and the work lists of an
 open tile at small, odd and large populations, and structures of many neighbours
-of which a block's LDS holds fewer replicas than its threads would.
+of which a block's LDS holds fewer replicas than its threads would; structures of
+few neighbours, down to none, in the launch of a class above theirs.
 
 Z in float64 is bit-identical to the plain schedule (one item per launch); in
 float32 it is bit-identical across shapes.
@@ -96,4 +97,34 @@ def test_fewer_replicas_than_a_block_has_threads_for(n, rho, seed):
         got = ts.fitness(X[:P], precision="fp64").cpu().numpy()
         plain = ts.fitness(X[:P], precision="fp64", schedule="plain").cpu().numpy()
         assert np.array_equal(got, plain), P
+    ts.close()
+
+
+@pytest.mark.parametrize("P", [1, 3, 40])
+def test_few_neighbours_in_the_launch_of_a_larger_class(P):
+    import torch
+    if not torch.cuda.is_available():
+        pytest.skip("no GPU")
+    from paper_1909_11474_amd import api
+    box, c = 20.0 * np.eye(3), np.array([10.0, 10.0, 10.0])
+    tri = np.array([[0, 0, 0], [1, 0, 0], [0.5, np.sqrt(3) / 2, 0]])
+    line = np.array([[2.4 * k, 0.0, 0.0] for k in range(70)])      # more than one wavefront of dimers and a chain
+    s = W.make_set([(c[None], box), (c + 2.4 * tri[:2], box), (c + 2.4 * tri, box),
+                    (line + 10.0, np.diag([200.0, 20.0, 20.0])), W.diamond(1, 1, 1), W.diamond(2, 2, 2),
+                    W.random_packing(rng(64), 64)])
+    X = W.draw_params(rng(5), P)
+    ts = api.from_structures(s)
+    assert ts.stats()["max_coordination"] > 4
+    ref = ts.tersoff_eval(W.draw_params(rng(6), 1), precision="fp64")
+    m = torch.as_tensor(s.sizes(), dtype=torch.float64, device="cuda")
+    ts.attach_reference(ref["E"][0] / m, ref["W"][0] / m[:, None], ref["F"][0])
+    plain = ts.tersoff_eval(X, precision="fp64", schedule="plain")
+    got = ts.tersoff_eval(X, precision="fp64")
+    for k in plain:
+        assert torch.equal(got[k], plain[k]), k
+    assert torch.equal(ts.fitness(X, precision="fp64"), ts.fitness(X, precision="fp64", schedule="plain"))
+    _, G = ts.fitness_grad(X, precision="fp64")
+    one = torch.cat([ts.fitness_grad(X[k:k + 1], precision="fp64")[1] for k in range(P)])
+    many = ts.fitness_grad(np.repeat(X, 400, 0), precision="fp64")[1][::400]    # class 4 in a launch of its own
+    assert torch.equal(G, one) and torch.equal(G, many)
     ts.close()
