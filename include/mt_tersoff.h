@@ -79,8 +79,8 @@ enum mt_precision {
 };
 
 enum mt_schedule {
-    MT_BATCHED = 0,          /* one launch covers all candidate x structure pairs
-                                (replayed from a captured HIP graph)                 */
+    MT_BATCHED = 0,          /* one launch per coordination class covers all its
+                                candidate x structure pairs                          */
     MT_PLAIN = 1             /* one launch per (candidate, structure) pair           */
 };
 
@@ -231,8 +231,8 @@ int fitness_eval_tf(mt_set* set, const double* x, int P, const double* w, int pr
  * derivative of the Sec. III.B fitness, including the force and virial terms,
  * which need mixed second derivatives of the energy).  A term with Z_x = 0
  * contributes no gradient.  Every set fitness_eval accepts is handled:
- * structures over MT_MAX_BATCHED_ATOMS atoms (or too large for one block's LDS
- * with the adjoint's residual buffer) take a two-pass adjoint that stages bond
+ * structures that fitness_eval sends to the two-pass path (over
+ * MT_MAX_BATCHED_ATOMS atoms, or too large for one block's LDS) take a two-pass adjoint that stages bond
  * gradients and force residuals in device memory, held by the set.
  *   Z     device [P][4]
  *   dZdx  device [P][6]
@@ -269,8 +269,8 @@ int fitness_grad_tf(mt_set* set, const double* x, int P, const double* w, int pr
  * Every call on one GPU shares that GPU's array, which keeps the last call's
  * contents (each call overwrites every sum it reads, nothing has to start at
  * zero); calls that overlap on one GPU, from any thread or stream, race.
- * Errors: as for fitness_eval; MT_EINVAL when P x (partial-sum slots of the
- * set) x 64 bytes exceeds MT_NOALLOC_SCRATCH_BYTES, when the set has a
+ * Errors: as for fitness_eval; MT_EINVAL when P x (64-atom chunks of the set's
+ * structures, each rounded up) x 64 bytes exceeds MT_NOALLOC_SCRATCH_BYTES, when the set has a
  * structure that takes the two-pass path (over MT_MAX_BATCHED_ATOMS atoms, or
  * too large for one block's LDS), or when the current device is not the set's.
  * fitness_terms does not read these sums (MT_ESTATE after this call).

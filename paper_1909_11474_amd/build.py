@@ -50,8 +50,8 @@ UNIT_FLAGS = {u: ["-mllvm", "-amdgpu-sched-strategy=max-memory-clause"]
 UNIT_FLAGS["mt_k_fit32.hip"] += ["-mllvm", "-amdgpu-use-amdgpu-trackers=1"]
 UNIT_FLAGS["mt_k_fit32_m4.hip"] = ["-mllvm", "-amdgpu-sched-strategy=iterative-minreg"]
 
-# Units that take longest to compile (one to two and a half minutes); the
-# parallel build starts them first.
+# Units that take longest to compile (half a minute to two and a half minutes);
+# the parallel build starts them first.
 SLOW_UNITS = ("mt_k_tf_large_adj32.hip", "mt_k_tf_plain.hip", "mt_k_plain32.hip", "mt_k_large.hip",
               "mt_k_fit32.hip", "mt_k_fitr32.hip", "mt_k_fitr64.hip", "mt_k_f64.hip")
 

@@ -127,7 +127,7 @@ static int check_common(mt_set* set, const double* x, int P, int precision) {
     if (P <= 0) return fail(MT_EINVAL, "P must be positive");
     if (precision != MT_FP64 && precision != MT_FP32_ACC64)
         return fail(MT_EINVAL, "precision must be MT_FP64 or MT_FP32_ACC64");
-    if ((long long)P * std::max(1, set->nslots) * kNVEval > (1ll << 31))
+    if ((long long)P * std::max(1, set->nchunks) * kNVEval > (1ll << 31))
         return fail(MT_EINVAL, "P too large for this set");
     return MT_OK;
 }
@@ -492,7 +492,7 @@ int fitness_eval_noalloc(mt_set* set, const double* x, int P, const double* w, i
     if (set->n_large > 0)
         return fail(MT_EINVAL, "fitness_eval_noalloc: the set has structures over " +
                                    std::to_string(MT_MAX_BATCHED_ATOMS) + " atoms (two-pass path)");
-    const size_t need = sizeof(double) * kNVFit * (size_t)P * std::max(1, set->nslots);
+    const size_t need = sizeof(double) * kNVFit * (size_t)P * std::max(1, set->nchunks);
     if (need > MT_NOALLOC_SCRATCH_BYTES)
         return fail(MT_EINVAL, "fitness_eval_noalloc: P x partial-sum slots needs " + std::to_string(need) +
                                    " bytes of scratch, more than " +

@@ -107,6 +107,7 @@ struct GraphEntry {
 
 struct mt_set {
     int S = 0, N = 0, kcap = 0, kmax = 0, nb = 0, nslots = 0;
+    int nchunks = 0;   // limits on P count these: 64-atom chunks of the batched structures, slots of the others
     long long ntrip = 0;
     int max_atoms = 0, n_batched = 0, n_large = 0;
     size_t lds_max = 65536;   // dynamic LDS bytes a block may use on the set's device

@@ -749,7 +749,7 @@ int build_set(mt_set* set, const int64_t* atom_offset, const double* pos, const 
     set->kmax = 0;
     set->ntrip = 0;
     set->max_atoms = 0;
-    set->n_batched = set->n_large = 0;
+    set->n_batched = set->n_large = set->nchunks = 0;
     for (int s = 0; s < S; ++s) {
         const int ns = set->h_off[s + 1] - set->h_off[s];
         set->h_boff[s + 1] = set->h_boff[s] + hnb[s];
@@ -761,6 +761,7 @@ int build_set(mt_set* set, const int64_t* atom_offset, const double* pos, const 
         // over the batching limit: one slot per block of the two-pass kernels
         const int nsl = large ? (ns + kLargeBlock - 1) / kLargeBlock : 1;
         set->h_slot[s + 1] = set->h_slot[s] + nsl;
+        set->nchunks += large ? nsl : std::max(1, npad / 64);
         if (large) ++set->n_large; else ++set->n_batched;
     }
     set->nb = set->h_boff[S];
