@@ -569,18 +569,34 @@ static double step_cost(const mt_set* set, int s, int R) {
 }
 
 // Time of a launch's work items where the launch shape leaves the tile open, in
-// units of step_cost.  total: the launch's block steps, mean: of one of them;
-// round: their share per block the device holds at once.  Up to a few steps one
-// item per block slot is best; beyond that an item costs about two steps more
-// than its own (records, bond geometry) and the launch ends about half an item
-// after the blocks run out: least at sqrt(4 mean round).  Against items of P S / 1024
-// candidates: 500 candidates x 300 structures 1.15 -> 0.91 ms, 200 x 60
-// (Tersoff form) 0.24 -> 0.20 ms; the best of a sweep of fixed tiles takes 0.88
-// and 0.19 ms.
-static double auto_item(double total, double mean, int block, int mc, int fam, int ncu) {
+// units of step_cost; round: the launch's work per block the device holds at once,
+// mean: a step's.  Up to six steps one item per block is best: the shortest item
+// time at which the items are no more than the blocks, so that no second round
+// begins (64 candidates x 60 structures in float64 138 -> 120 us; at twelve steps
+// the step-cost model's errors cost more than the tail, gradient of 64 x 300 in
+// float 427 -> 437 us).  Beyond, an item costs about two steps more than its own
+// (records, bond geometry) and the launch ends about half an item after the blocks
+// run out: least at sqrt(4 mean round).  Against items of P S / 1024 candidates:
+// 500 candidates x 300 structures 1.15 -> 0.91 ms, 200 x 60 (Tersoff form) 0.24 ->
+// 0.20 ms; the best of a sweep of fixed tiles takes 0.88 and 0.19 ms.
+struct OpenItems {
+    double item = 0.0;   // item time
+    bool even = false;   // one item per block slot: no shorter items towards the end
+};
+struct Steps { double n, cost; };    // a structure's block steps in a launch and the time of one
+static int steps_in(double item, double cost) { return std::max(1, (int)std::lround(item / cost)); }
+static OpenItems open_items(const std::vector<Steps>& work, int block, int mc, int fam, int ncu) {
     const int waves = mc <= 4 && (fam == FAM_FIT32 || fam == FAM_ADJ32) ? 16 : 8;   // per compute unit (registers)
-    const double round = total / ((double)ncu * std::max(1, waves * 64 / block));
-    return std::min(round, std::sqrt(4.0 * mean * round));
+    const int slots = ncu * std::max(1, waves * 64 / block);
+    double n = 0.0, total = 0.0;
+    for (const Steps& w : work) { n += w.n; total += w.n * w.cost; }
+    const double round = total / slots, mean = total / n;
+    for (double t = round; t <= 6.0 * mean; t += 0.25 * mean) {
+        double items = 0.0;
+        for (const Steps& w : work) items += std::ceil(w.n / steps_in(t, w.cost));
+        if (items <= slots) return {t, true};
+    }
+    return {std::min(round, std::sqrt(4.0 * mean * round)), false};
 }
 
 // The blocks of a launch go to the XCDs round robin (block b to XCD b mod 8),
@@ -668,27 +684,29 @@ ItemPlan* get_plan(mt_set* set, int P, const LaunchCfg& cfg, int fam) {
         }
         cls[s] = class_of(fam, set->h_kmax[s]);
     }
-    // block steps of a launch and their time
-    auto add_work = [&](int s, std::pair<double, double>& w) {
-        const double n = (P + Rs[s] - 1) / Rs[s];
-        w.first += n;
-        w.second += n * step_cost(set, s, Rs[s]);
+    // block steps, item times and work items per class
+    std::map<int, double> nsteps;
+    std::map<int, OpenItems> open;
+    auto steps_of = [&](int s) {
+        const int steps = steps_in(open[cls[s]].item, step_cost(set, s, Rs[s]));
+        const int n = (P + Rs[s] - 1) / Rs[s], items = (n + steps - 1) / steps;
+        return open[cls[s]].even ? (n + items - 1) / items : steps;
     };
-    // steps per item of structure s in a launch of work w (steps, time)
-    auto open_steps = [&](int s, int block, int mc, const std::pair<double, double>& w) {
-        const double item = auto_item(w.second, w.second / w.first, block, mc, fam, ncu);
-        return std::max(1, (int)std::lround(item / step_cost(set, s, Rs[s])));
-    };
-    // work and work items per class
-    std::map<int, std::pair<double, double>> work_of;
     auto count = [&]() {
-        work_of.clear();
+        nsteps.clear();
+        open.clear();
         nitems.clear();
-        for (int s = 0; s < set->S; ++s)
-            if (cls[s]) add_work(s, work_of[cls[s]]);
+        std::map<int, std::vector<Steps>> work;
         for (int s = 0; s < set->S; ++s)
             if (cls[s]) {
-                const int tile = tile_for(cfg, P, Rs[s], plain, open_steps(s, cfg.block, cls[s], work_of[cls[s]]));
+                const double n = (P + Rs[s] - 1) / Rs[s];
+                nsteps[cls[s]] += n;
+                work[cls[s]].push_back({n, step_cost(set, s, Rs[s])});
+            }
+        for (auto& [mc, w] : work) open[mc] = open_items(w, cfg.block, mc, fam, ncu);
+        for (int s = 0; s < set->S; ++s)
+            if (cls[s]) {
+                const int tile = tile_for(cfg, P, Rs[s], plain, steps_of(s));
                 nitems[cls[s]] += (P + tile - 1) / tile;
             }
     };
@@ -696,10 +714,10 @@ ItemPlan* get_plan(mt_set* set, int P, const LaunchCfg& cfg, int fam) {
     for (size_t i = 0; !plain && i < classes.size(); ++i) {
         const int mc = classes[i];
         if (nitems[mc] == 0) continue;
-        if (mc <= 4 && (cfg.tile != 0 || work_of[mc].first >= ncu ||
-                        work_of[mc].first > 3.0 * std::count(cls.begin(), cls.end(), mc)))
+        if (mc <= 4 && (cfg.tile != 0 || nsteps[mc] >= ncu ||
+                        nsteps[mc] > 3.0 * std::count(cls.begin(), cls.end(), mc)))
             continue;
-        if (cfg.tile == 0 ? work_of[mc].first >= 16.0 * ncu : nitems[mc] >= ncu) continue;
+        if (cfg.tile == 0 ? nsteps[mc] >= 16.0 * ncu : nitems[mc] >= ncu) continue;
         for (size_t j = i + 1; j < classes.size(); ++j) {
             const int to = classes[j];
             if (nitems[to] == 0) continue;
@@ -717,7 +735,7 @@ ItemPlan* get_plan(mt_set* set, int P, const LaunchCfg& cfg, int fam) {
             const int R = Rs[s];
             const int block = plain ? std::max(64, set->h_npad[s]) : cfg.block;
             Group& g = groups[block];
-            int steps = plain ? 1 : open_steps(s, block, mc, work_of[mc]);
+            int steps = plain ? 1 : steps_of(s);
             int tile = tile_for(cfg, P, R, plain, steps);
             // an open tile is halved until its records fit beside the exchange
             while (steps > 1 && cfg.tile == 0 && item_lds(set, s, R, fam, std::min(tile, P)) > set->lds_max)
@@ -734,7 +752,7 @@ ItemPlan* get_plan(mt_set* set, int P, const LaunchCfg& cfg, int fam) {
                 it.R = R;
                 it.c0 = c0;
                 it.nc = std::min(tile, P - c0);
-                if (!plain && cfg.tile == 0) {
+                if (!plain && cfg.tile == 0 && !open[mc].even) {
                     // an open tile shrinks to half of what is left (at
                     // least a quarter of it), so that the launch ends on
                     // short items
