@@ -132,10 +132,10 @@ constexpr int kCosPairs = 15;
 //
 // double: 2^x, log2 x (x > 0) and 1/x for the arguments the site routine has.
 // They are most of a float64 bond's instructions, and the device library's
-// (special cases, a log2 in double-double) take about twice as many: a bond 250
-// instructions with those, 140 with these (64 candidates x 60 structures 176 ->
+// (special cases) take about twice as many: a bond 250
+// instructions with those, 150 with these (64 candidates x 60 structures 176 ->
 // 152 us).  The polynomials interpolate at Chebyshev nodes (computed in 60
-// digits); errors below 0.7 ulp (2^x), 1.3 ulp (log2) and 1 ulp (1/x).  The
+// digits); errors below 0.7 ulp (2^x), 0.6 ulp (log2) and 1 ulp (1/x).  The
 // float64 kernels' errors against 64-bit sums in another order stay where they
 // were (2e-15 of a force).
 // ---------------------------------------------------------------------------
@@ -171,7 +171,9 @@ __device__ __forceinline__ double dexp2(double x) {
 }
 
 // x = 2^e m, m in [sqrt(1/2), sqrt(2)); with s = (m - 1)/(m + 1),
-// log2 m = s L(s^2), L of degree 7 (relative error 1.4e-17 before rounding).
+// log2 m = s L(s^2), L of degree 7 (relative error 1.4e-17 before rounding); s and
+// the leading product 2/ln 2 s carry their rounding errors to the last sum (without
+// them 2.0 ulp, and gradients off by a fifth more than with the device library).
 // Infinite x counts as the largest finite value.
 __device__ __forceinline__ double dlog2(double x) {
     x = __builtin_fmin(x, 1.7976931348623157e308);
@@ -184,7 +186,8 @@ __device__ __forceinline__ double dlog2(double x) {
     double r = __builtin_amdgcn_rcp(den);
     r = __builtin_fma(r, __builtin_fma(-den, r, 1.0), r);
     const double s0 = num * r;
-    const double s = __builtin_fma(__builtin_fma(-dlo, s0, __builtin_fma(-den, s0, num)), r, s0);
+    const double slo = __builtin_fma(-dlo, s0, __builtin_fma(-den, s0, num)) * r;
+    const double s = s0 + slo;
     const double w = s * s;
     double l = 0.21366122502798326;
     l = __builtin_fma(l, w, 0.22091286734180157);
@@ -193,8 +196,13 @@ __device__ __forceinline__ double dlog2(double x) {
     l = __builtin_fma(l, w, 0.4121985858422942);
     l = __builtin_fma(l, w, 0.577078016345514);
     l = __builtin_fma(l, w, 0.9617966939259898);
-    l = __builtin_fma(l, w, 2.8853900817779268);
-    return __builtin_fma(s, l, (double)e);
+    constexpr double kHi = 2.8853900817779268, kLo = 4.0710547481862066e-17;   // 2 / ln 2
+    const double t = s0 * kHi;
+    double lo = __builtin_fma(s0, kLo, __builtin_fma(slo, kHi, __builtin_fma(s0, kHi, -t)));
+    lo = __builtin_fma(s * w, l, lo);
+    const double ed = (double)e, hi = ed + t;
+    lo += (ed - hi) + t;
+    return hi + lo;
 }
 
 // float64 2^y for the energy terms of the float path, finite arguments only:
