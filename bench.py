@@ -60,7 +60,7 @@ PMC_TRAFFIC = {
     "sources": ["paper_1909_11474_amd/csrc/mt_common.h", "paper_1909_11474_amd/csrc/mt_site.h",
                 "paper_1909_11474_amd/csrc/mt_kernels.h", "paper_1909_11474_amd/csrc/mt_k_fit32.hip",
                 "paper_1909_11474_amd/csrc/mt_eval.hip", "paper_1909_11474_amd/build.py"],
-    "sha256_16": "75c1540cb5204cf7",
+    "sha256_16": "4f865424d9731aa8",
     "fetch_bytes": 21991.2 * 1024 * 2.00,
     "write_bytes": 26270.4 * 1024 * 1.00,
 }

@@ -447,8 +447,8 @@ __device__ __forceinline__ void dispatch_m(int m, F&& f) {
     }
 }
 
-// Lowest compiled variant of a class; the exchange-slot layout of the set
-// reserves at least this many slots per atom for structures of the class.
+// Lowest compiled variant of a class; the exchange-slot layout of a set
+// reserves at least three slots per atom, so every class can run any structure.
 template <int MC>
 struct ClassLo {
     static constexpr int value = MC <= 4 ? 0 : 3;
