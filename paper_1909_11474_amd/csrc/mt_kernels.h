@@ -1289,6 +1289,26 @@ __device__ __forceinline__ void run_large_adjoint(const BArgs<S>& A, const LArgs
     }
 }
 
+// Variant that a wavefront of largest coordination Mw runs in the class above 4;
+// rows past its coordination are padding bonds.  A variant whose pair sums come
+// from moments reads the table that exists only for sets above kPairMax
+// neighbours, so it may serve such wavefronts only.
+template <typename S, bool Full>
+constexpr int large_adjoint_m(int Mw) {
+    return Geo<S, 8, Full>::kMoments && Mw <= kPairMax ? kPairMax : Mw <= 8 ? 8 : kMaxNbr;
+}
+template <typename S, bool Full>
+constexpr bool large_adjoint_tables_exist() {
+    for (int Mw = 0; Mw <= kMaxNbr; ++Mw) {
+        const int m = large_adjoint_m<S, Full>(Mw);
+        const bool moments = m == kMaxNbr ? Geo<S, kMaxNbr, Full>::kMoments
+                             : m == 8     ? Geo<S, 8, Full>::kMoments
+                                          : Geo<S, kPairMax, Full>::kMoments;
+        if (m < Mw || (moments && Mw <= kPairMax)) return false;
+    }
+    return true;
+}
+
 template <typename S, int MC, bool Full>
 __global__ __launch_bounds__(256) void k_large_adjoint(BArgs<S> A, LArgs L, const S* __restrict__ abuf) {
     const SetDev& d = A.set;
@@ -1308,9 +1328,11 @@ __global__ __launch_bounds__(256) void k_large_adjoint(BArgs<S> A, LArgs L, cons
         if constexpr (MC <= 4) {
             dispatch_m<0, MC>(Mw, run);
         } else {
-            // two variants: rows past the wave's coordination are padding bonds
-            if (Mw <= 8) run(std::integral_constant<int, 8>{});
-            else run(std::integral_constant<int, MC>{});
+            static_assert(MC == kMaxNbr && large_adjoint_tables_exist<S, Full>(), "see large_adjoint_m");
+            const int m = large_adjoint_m<S, Full>(Mw);
+            if (m == kMaxNbr) run(std::integral_constant<int, kMaxNbr>{});
+            else if (m == 8) run(std::integral_constant<int, 8>{});
+            else if constexpr (large_adjoint_m<S, Full>(0) == kPairMax) run(std::integral_constant<int, kPairMax>{});
         }
     }
     const int c = L.c0 + blockIdx.y;

@@ -592,6 +592,10 @@ static int refresh_angle_tables(mt_set* set, hipStream_t st) {
 }
 
 int float_tables(mt_set* set, hipStream_t st) {
+    if (set->kmax > kPairMax && !set->gam.p) {
+        set_error("the set has no table of angular moments");
+        return MT_ESTATE;
+    }
     if (set->f32_ready) return MT_OK;
     hipStreamCaptureStatus cap = hipStreamCaptureStatusNone;
     HIPCHECK(hipStreamIsCapturing(st, &cap));
