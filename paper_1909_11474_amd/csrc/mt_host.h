@@ -131,9 +131,11 @@ struct mt_set {
     mt::DevBuf gam;                          // angular moments per bond (sets above kPairMax neighbours)
     mt::DevBuf gcs;                          // cos(theta) of bond pairs j < k < 6, [15][N] float
 
-    // angle tables of the float kernels: built for the present geometry, and
-    // whether any float call has been made (see float_tables)
+    // angle tables of the float kernels: built for the present geometry, whether
+    // any float call has been made, and the graph under capture that builds them
+    // before what it captures next (0: none); see float_tables
     bool f32_ready = false, f32_used = false;
+    unsigned long long f32_graph = 0;
 
     // references (sorted order)
     bool has_ref = false;

@@ -583,12 +583,28 @@ static int launch_angle_tables(mt_set* set, hipStream_t st) {
     return MT_OK;
 }
 
+// The graph that work on the stream is captured into, or 0.
+static int graph_of(hipStream_t st, unsigned long long* graph) {
+    *graph = 0;
+    if (!st) return MT_OK;                 // the default stream is never captured
+    hipStreamCaptureStatus cap = hipStreamCaptureStatusNone;
+    unsigned long long id = 0;
+    HIPCHECK(hipStreamGetCaptureInfo(st, &cap, &id));
+    if (cap == hipStreamCaptureStatusActive) *graph = id + 1;
+    return MT_OK;
+}
+
 // After new bond geometry: sets that have made float calls get their tables at
 // once, in stream order (a captured float call may be replayed next); others
-// when they make the first (float_tables), so that float64 runs do without.
+// when they make the first (float_tables), so that float64 runs do without.  A
+// captured update carries them in any case: it may be replayed after a float call.
 static int refresh_angle_tables(mt_set* set, hipStream_t st) {
-    set->f32_ready = set->f32_used;
-    return set->f32_used ? launch_angle_tables(set, st) : MT_OK;
+    unsigned long long graph = 0;
+    const int rc = graph_of(st, &graph);
+    if (rc != MT_OK) return rc;
+    set->f32_ready = set->f32_used && !graph;
+    set->f32_graph = graph;
+    return set->f32_used || graph ? launch_angle_tables(set, st) : MT_OK;
 }
 
 int float_tables(mt_set* set, hipStream_t st) {
@@ -597,13 +613,16 @@ int float_tables(mt_set* set, hipStream_t st) {
         return MT_ESTATE;
     }
     if (set->f32_ready) return MT_OK;
-    hipStreamCaptureStatus cap = hipStreamCaptureStatusNone;
-    HIPCHECK(hipStreamIsCapturing(st, &cap));
-    const int rc = launch_angle_tables(set, st);
+    unsigned long long graph = 0;
+    int rc = graph_of(st, &graph);
+    if (rc != MT_OK) return rc;
+    if (graph && graph == set->f32_graph) return MT_OK;
+    rc = launch_angle_tables(set, st);
     if (rc != MT_OK) return rc;
     set->f32_used = true;
     // captured launches have not run yet: a call outside the graph builds again
-    set->f32_ready = cap == hipStreamCaptureStatusNone;
+    set->f32_ready = !graph;
+    set->f32_graph = graph;
     return MT_OK;
 }
 
