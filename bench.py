@@ -57,7 +57,8 @@ TUNED_SHAPES = os.path.join(os.path.dirname(os.path.abspath(__file__)), "paper_1
 # (per-unit code-generation flags) it was measured on: reported when their hash
 # still matches.
 PMC_TRAFFIC = {
-    "sources": ["paper_1909_11474_amd/csrc/mt_common.h", "paper_1909_11474_amd/csrc/mt_site.h",
+    "sources": ["paper_1909_11474_amd/csrc/mt_common.h", "paper_1909_11474_amd/csrc/mt_math.h",
+                "paper_1909_11474_amd/csrc/mt_site.h",
                 "paper_1909_11474_amd/csrc/mt_kernels.h", "paper_1909_11474_amd/csrc/mt_k_fit32.hip",
                 "paper_1909_11474_amd/csrc/mt_eval.hip", "paper_1909_11474_amd/build.py"],
     "sha256_16": "4f865424d9731aa8",

@@ -90,7 +90,9 @@ __device__ __forceinline__ void decode_record(const double* __restrict__ x, Rec<
         const double K = gam * c * c / (d * d);
         o.gam = (S)gam;
         o.K = (S)K;
-        o.d2 = (S)(d * d);
+        // where d^2 overflows, the largest value: g^T = gamma then, and no
+        // product with rho = 1/(d^2 + t^2) is infinity times 0
+        o.d2 = (S)(sizeof(S) == 4 ? fmin(d * d, 3.4028234663852886e38) : fmin(d * d, kMaxDouble));
         o.Kd2 = (S)(K * d * d);
     } else {
         // S = 2: mu = alpha, lambda = 2 alpha, DR = D0, DA = 2 D0

@@ -298,9 +298,9 @@ __device__ __forceinline__ void site_eval_sink(Geo<S, M, Full>& g, const Cand<S,
             eA = dexp2(-(p.aA * delta));
             if constexpr (Full) eR = dexp2(-(p.aR * delta));
             // formed before the selection: a branch around it splits the chain
-            const S zne = dexp2(p.n * dlog2(zsafe));
+            const S zne = dexp2(p.n * dlog2<true>(zsafe));
             zn = pos ? zne : S(0);
-            b = dexp2(p.ninv2n * dlog2(S(1) + zn));
+            b = dexp2(p.ninv2n * dlog2<true>(S(1) + zn));
         }
         const S onep = S(1) + zn;
         S fR;
@@ -314,7 +314,7 @@ __device__ __forceinline__ void site_eval_sink(Geo<S, M, Full>& g, const Cand<S,
         if constexpr (Full) Dj = g.hfcp[j] * diff + g.fc[j] * (p.hmu * bfA - p.hlambda * fR);
         else Dj = g.hfcp[j] * diff + (p.hmu * g.fc[j]) * (bfA - S(2) * fR);
         // c~ = -ZS f_C f_A db/dzeta with db/dzeta = -b zeta^n / (2 zeta (1 + zeta^n))
-        ccj = (p.ccs * g.fc[j]) * (bfA * zn) * drcp(zsafe * onep);
+        ccj = (p.ccs * g.fc[j]) * (bfA * zn) * drcp_inf(zsafe * onep);
         // keep the scheduler from interleaving all M bonds' chains (about ten
         // live values each; float64 ones in the energy mode)
         if constexpr (PerBond || Geo<S, M, Full>::kMoments || (kE64 && SerialE64)) __builtin_amdgcn_sched_barrier(0);
