@@ -277,9 +277,10 @@ __device__ __forceinline__ void site_eval_sink(Geo<S, M, Full>& g, const Cand<S,
         if constexpr (kE64) {
             const double dl = g.r[j] - p.r0;
             const double eA64 = exp2_acc(-(p.aA64 * dl));
-            // log2 0 = -inf and 2^-inf = 0; the divisor below stays positive
+            // log2 0 = -inf and 2^-inf = 0; the divisor below stays positive, and
+            // is zeta itself down to the smallest normal value
             zn = dexp2(p.n * dlog2(z));
-            zsafe = __builtin_fmaxf(z, 1e-30f);
+            zsafe = __builtin_fmaxf(z, 1.17549435e-38f);
             const double b64 = exp2_acc(p.ninv2n64 * (double)dlog2(1.f + zn));
             if constexpr (Full) {
                 const double eR64 = exp2_acc(-(p.aR64 * dl));

@@ -1,5 +1,5 @@
 """Parameters at the ends of the domain: intermediate values of a candidate that
-leave the range of the arithmetic type.
+leave the range of the arithmetic type, or a zeta near its smallest value.
 
 The expected values are those of the limit that the formulas have there:
   d -> large:  g^T -> gamma, so a candidate of d = 1e200 (1e30 in float32, where
@@ -8,6 +8,8 @@ The expected values are those of the limit that the formulas have there:
                for equal candidates (1e-12 of the largest value in float64, where
                the gradient's sums round differently; 1e-6 in float32).
   zeta^n -> inf: b = 0.
+  beta small:  zeta^n is of order 0.02 at n = 0.05, beta = 1e-33, and the forces
+               depend on it; float32 against the oracle within 1e-4 eV/A.
 """
 import numpy as np
 import pytest
@@ -82,4 +84,17 @@ def test_zeta_power_overflow(api, structs):
         e = np.exp(-x[1] * (r - x[2]))
         want[k] = 0.5 * (fc * x[0] * (e * e - 2.0 * b * e)).sum()
     assert np.abs(E - want).max() <= 1e-10 * np.abs(want).max(), (E, want)
+    ts.close()
+
+
+def test_small_zeta_float(api, structs):
+    ts = api.from_structures(structs)
+    x = np.array(W.TABLE2_X)
+    x[3], x[4] = 1e-33, 0.05
+    out = ts.tersoff_eval(x[None], precision="fp32")
+    ref = T.evaluate_set(structs, x, R1, R2)
+    F = out["F"].cpu().numpy()[0]
+    assert np.abs(F - ref["F"]).max() <= 1e-4, np.abs(F - ref["F"]).max()
+    n = structs.sizes().astype(float)
+    assert np.abs(out["E"].cpu().numpy()[0] / n - ref["E"] / n).max() <= 1e-6
     ts.close()
