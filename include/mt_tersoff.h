@@ -329,7 +329,8 @@ int mt_md_kick(int N, double* vel, const double* force, const double* atom_viria
 int mt_md_drift(int N, double* pos, const double* vel, double dt, void* stream);
 int mt_md_scale(int N, double* vel, double lambda, void* stream);
 int mt_md_kinetic(int N, const double* vel, const double* mass, double* out, void* stream);
-/* out (device [1]) = max_i |r_i - ref_i|^2 (A^2), for the skin check. */
+/* out (device [1]) = max_i |r_i - ref_i|^2 (A^2), for the skin check; atoms whose
+ * displacement is not a number are left out. */
 int mt_md_max_disp(int N, const double* pos, const double* ref, double* out, void* stream);
 /*
  * mt_md_kick(dt_half), mt_md_drift(dt) and, with ref and out (both or neither),

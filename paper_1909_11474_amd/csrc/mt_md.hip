@@ -119,22 +119,20 @@ __global__ __launch_bounds__(1024) void k_kinetic(int N, const double* __restric
     }
 }
 
-// out[0] = max_i |r_i - r0_i|^2 (exact: max is order independent).  The blocks
-// meet in an atomic maximum of the bit patterns, which order like the values of
-// doubles that are not negative; k_clear sets out to zero first.  One block for
-// all atoms is bound by a single compute unit's loads: 8,000 atoms 9.6 us, 3.9 us
-// with the clear.
+// out[0] = max_i |r_i - r0_i|^2 (exact: max is order independent), atoms whose
+// displacement is not a number left out.  The blocks meet in an atomic maximum of
+// the bit patterns, which order like the values of doubles that are not negative;
+// k_clear sets out to zero first.  One block for all atoms is bound by a single
+// compute unit's loads: 8,000 atoms 9.6 us, 3.9 us with the clear.
 __global__ void k_clear(unsigned long long* out) { *out = 0ull; }
 __device__ __forceinline__ void block_max(double a, unsigned long long* __restrict__ out) {
     __shared__ double sh[4];
-    for (int o = 32; o > 0; o >>= 1) {
-        const double b = __shfl_xor(a, o, 64);
-        a = a > b ? a : b;
-    }
+    a = __builtin_fmax(a, 0.0);
+    for (int o = 32; o > 0; o >>= 1) a = __builtin_fmax(a, __shfl_xor(a, o, 64));
     if ((threadIdx.x & 63) == 0) sh[threadIdx.x >> 6] = a;
     __syncthreads();
     if (threadIdx.x == 0) {
-        for (int w = 1; w < 4; ++w) a = a > sh[w] ? a : sh[w];
+        for (int w = 1; w < 4; ++w) a = __builtin_fmax(a, sh[w]);
         atomicMax(out, (unsigned long long)__double_as_longlong(a));
     }
 }
