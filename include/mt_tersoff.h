@@ -342,7 +342,8 @@ int mt_md_first_half(int N, double* vel, const double* force, const double* atom
 
 /*
  * Choose launch shapes (block size, candidate tile, schedule) for this set
- * and population size by timing the candidates on the GPU; the choice is kept
+ * and population size by timing the candidates on the GPU, among them the open
+ * tile (0: work items derived per launch) of untuned calls; the choice is kept
  * in the set and used by later calls with the same P and precision.  With
  * reference data attached it also chooses between replaying a captured graph
  * per fitness_eval call and launching the kernels directly, by the host-clock

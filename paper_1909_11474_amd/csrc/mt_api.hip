@@ -613,7 +613,9 @@ int mt_autotune(mt_set* set, int P, int precision, const char* cache_path) {
     int maxpad = 8;
     for (int s = 0; s < set->S; ++s)
         if (!set->h_large[s]) maxpad = std::max(maxpad, set->h_npad[s]);
-    std::vector<LaunchCfg> cands;
+    // the open tile first, at the block of untuned calls, so that tuning does not
+    // choose a shape slower than theirs
+    std::vector<LaunchCfg> cands{default_cfg(set, P, precision)};
     for (int block : {64, 128, 256, 512}) {
         if (block < maxpad) continue;
         // powers of two plus tiles that let a whole generation fit in one
@@ -622,8 +624,8 @@ int mt_autotune(mt_set* set, int P, int precision, const char* cache_path) {
             if (tile > P && tile != 1) continue;
             for (int pers : {0, 1}) cands.push_back(LaunchCfg{block, tile, pers});
         }
+        if (block != cands[0].block) cands.push_back(LaunchCfg{block, 0, 0});
     }
-    if (cands.empty()) return fail(MT_EINVAL, "no batched structures to tune");
     // timing inputs: Table 2-like parameters for all candidates, zero references if none
     hipStream_t st;
     HIPCHECK(hipStreamCreateWithFlags(&st, hipStreamNonBlocking));
