@@ -56,10 +56,13 @@ mt::SetDev mt_set::dev() const {
     d.perm = perm.as<int>(); d.nnb = nnb.as<int>(); d.lbo = lbo.as<int>(); d.xbase = xbase.as<int>();
     d.rev = rev.as<int>(); d.revc = revc.as<int>(); d.jl = jl.as<int>(); d.nbr_j = nbr_j.as<int>();
     const size_t KN = (size_t)kcap * N;
+    const float* f = gf.as<float>();
     const float4* pk = gpk.as<float4>();
-    d.gf = GeomArrays<float>{pk, pk + KN};
+    d.gf = GeomArrays<float>{f, f + KN, f + 2 * KN, f + 3 * KN, gf_rlo.as<float>(), f + 4 * KN,
+                             f + 5 * KN, f + 6 * KN, pk, pk + KN};
     const double* g = gd.as<double>();
-    d.gd = GeomArrays<double>{g, g + KN, g + 2 * KN, g + 3 * KN, g + 4 * KN, g + 5 * KN, g + 6 * KN};
+    d.gd = GeomArrays<double>{g, g + KN, g + 2 * KN, g + 3 * KN, nullptr, g + 4 * KN,
+                              g + 5 * KN, g + 6 * KN, nullptr, nullptr};
     d.gcs = gcs.as<float>();
     d.gam = gam.as<float4>();
     d.fref32 = fref32.as<float>();

@@ -88,19 +88,14 @@ struct Item {
     int unused[2];  // 48 bytes
 };
 
-// Bond geometry, [kcap][N] each; float: packed per bond slot as two 4-vectors,
-// (ux, uy, uz, r_hi) and (r_lo, 1/r, f_C, f_C'/2).
 template <typename S>
-struct GeomArrays;
-template <>
-struct GeomArrays<float> {
+struct GeomArrays {
+    const S* ux; const S* uy; const S* uz;
+    const S* rhi; const S* rlo; const S* rinv;
+    const S* fc; const S* hfcp;     // f_C and f_C'/2
+    // float only: the same geometry packed per bond slot as two 4-vectors,
+    // (ux, uy, uz, r_hi) and (r_lo, 1/r, f_C, f_C'/2), [kcap][N] each
     const float4* pk0; const float4* pk1;
-};
-template <>
-struct GeomArrays<double> {
-    const double* ux; const double* uy; const double* uz;
-    const double* r; const double* rinv;
-    const double* fc; const double* hfcp;     // f_C and f_C'/2
 };
 
 struct SetDev {

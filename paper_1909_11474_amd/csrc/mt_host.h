@@ -125,7 +125,8 @@ struct mt_set {
     int *st_kmax = nullptr, *st_xsize = nullptr;   // in build.summary
     mt::DevBuf perm, nnb, lbo, xbase, rev, revc, jl;
     mt::DevBuf nbr_j, nbr_sh;                // caller-numbering neighbour entries, [kcap][N]
-    mt::DevBuf gd;                           // double geometry, 7 arrays of [kcap][N]
+    mt::DevBuf gf, gd;                       // float / double geometry, 8 resp. 7 arrays of [kcap][N]
+    mt::DevBuf gf_rlo;                       // float low part of r, [kcap][N]
     mt::DevBuf gpk;                          // float geometry packed as 2 x float4, [2][kcap][N]
     mt::DevBuf gam;                          // angular moments per bond (sets above kPairMax neighbours)
     mt::DevBuf gcs;                          // cos(theta) of bond pairs j < k < 6, [15][N] float

@@ -1171,7 +1171,7 @@ __global__ __launch_bounds__(256) void k_large_gather(BArgs<S> A, LArgs L) {
                     const float4 u = ok ? G.pk0[o] : make_float4(0.f, 0.f, 0.f, 0.f);
                     dx[q] = u.w * u.x; dy[q] = u.w * u.y; dz[q] = u.w * u.z;
                 } else {
-                    const S rr = ok ? G.r[o] : S(0), ux = ok ? G.ux[o] : S(0), uy = ok ? G.uy[o] : S(0),
+                    const S rr = ok ? G.rhi[o] : S(0), ux = ok ? G.ux[o] : S(0), uy = ok ? G.uy[o] : S(0),
                             uz = ok ? G.uz[o] : S(0);
                     dx[q] = rr * ux; dy[q] = rr * uy; dz[q] = rr * uz;
                 }

@@ -423,7 +423,8 @@ __global__ void k_geometry(int N, int S, int kcap, int slots, double R1, double 
                            const int* __restrict__ ent_j, const int* __restrict__ ent_sh,
                            const int* __restrict__ lbo, const int* __restrict__ xbase,
                            const int* __restrict__ st_npad,
-                           float4* __restrict__ gpk, double* __restrict__ gd,
+                           float* __restrict__ gf, float* __restrict__ gf_rlo, float4* __restrict__ gpk,
+                           double* __restrict__ gd,
                            int* __restrict__ rev, int* __restrict__ revc, int* __restrict__ jl,
                            int* __restrict__ nbr_j, int* __restrict__ nbr_sh, int* __restrict__ flags) {
     int idx = blockIdx.x * blockDim.x + threadIdx.x;
@@ -435,6 +436,9 @@ __global__ void k_geometry(int N, int S, int kcap, int slots, double R1, double 
     const int M = cnt[i];
     if (!Lists && m >= M) return;
     const int o = m * N + a;
+    float* f_ux = gf;         float* f_uy = gf + KN;    float* f_uz = gf + 2 * KN;
+    float* f_rhi = gf + 3 * KN; float* f_rinv = gf + 4 * KN;
+    float* f_fc = gf + 5 * KN;  float* f_hfcp = gf + 6 * KN;
     double* d_ux = gd;        double* d_uy = gd + KN;   double* d_uz = gd + 2 * KN;
     double* d_r = gd + 3 * KN;  double* d_rinv = gd + 4 * KN;
     double* d_fc = gd + 5 * KN; double* d_hfcp = gd + 6 * KN;
@@ -442,6 +446,8 @@ __global__ void k_geometry(int N, int S, int kcap, int slots, double R1, double 
     const int npad = st_npad[s];
     const int G = npad < 64 ? npad : 64;
     if (m >= M) {
+        f_ux[o] = f_uy[o] = f_uz[o] = 0.f; f_rhi[o] = 3.0f; gf_rlo[o] = 0.f;
+        f_rinv[o] = 0.f; f_fc[o] = 0.f; f_hfcp[o] = 0.f;
         d_ux[o] = d_uy[o] = d_uz[o] = 0.0; d_r[o] = 3.0; d_rinv[o] = 0.0;
         d_fc[o] = 0.0; d_hfcp[o] = 0.0;
         // a padded bond reads back its own (zero) slot and its own atom
@@ -476,6 +482,9 @@ __global__ void k_geometry(int N, int S, int kcap, int slots, double R1, double 
     d_ux[o] = ux; d_uy[o] = uy; d_uz[o] = uz; d_r[o] = r; d_rinv[o] = rinv;
     d_fc[o] = fc; d_hfcp[o] = hfcp;
     const float rhi = (float)r;
+    f_ux[o] = (float)ux; f_uy[o] = (float)uy; f_uz[o] = (float)uz;
+    f_rhi[o] = rhi; gf_rlo[o] = (float)(r - (double)rhi);
+    f_rinv[o] = (float)rinv; f_fc[o] = (float)fc; f_hfcp[o] = (float)hfcp;
     gpk[o] = make_float4((float)ux, (float)uy, (float)uz, rhi);
     gpk[KN + o] = make_float4((float)(r - (double)rhi), (float)rinv, (float)fc, (float)hfcp);
     if (!Lists) return;
@@ -787,6 +796,8 @@ int build_set(mt_set* set, const int64_t* atom_offset, const double* pos, const 
         HIPCHECK(hipMemcpyAsync(set->st_slot.p, set->h_slot.data(), sizeof(int) * (S + 1), hipMemcpyHostToDevice, st));
 
     const size_t KN = (size_t)kcap * N;
+    HIPCHECK(set->gf.reserve(sizeof(float) * 7 * KN));
+    HIPCHECK(set->gf_rlo.reserve(sizeof(float) * KN));
     HIPCHECK(set->gpk.reserve(sizeof(float4) * 2 * KN));
     HIPCHECK(set->gd.reserve(sizeof(double) * 7 * KN));
     HIPCHECK(set->gcs.reserve(sizeof(float) * kCosPairs * (size_t)N));
@@ -801,7 +812,8 @@ int build_set(mt_set* set, const int64_t* atom_offset, const double* pos, const 
         N, S, kcap, kcap, set->R1, set->R2, set->st_off.as<int>(), set->pos.as<double>(),
         meta.as<StructMeta>(), set->perm.as<int>(), inv.as<int>(), cnt.as<int>(), ent_j.as<int>(),
         ent_sh.as<int>(), set->lbo.as<int>(), set->xbase.as<int>(), set->st_npad.as<int>(),
-        set->gpk.as<float4>(), set->gd.as<double>(), set->rev.as<int>(), set->revc.as<int>(), set->jl.as<int>(), set->nbr_j.as<int>(),
+        set->gf.as<float>(), set->gf_rlo.as<float>(), set->gpk.as<float4>(),
+        set->gd.as<double>(), set->rev.as<int>(), set->revc.as<int>(), set->jl.as<int>(), set->nbr_j.as<int>(),
         set->nbr_sh.as<int>(), B.flags);
     HIPCHECK(hipGetLastError());
     const int rc = refresh_angle_tables(set, st);
@@ -824,7 +836,8 @@ int update_geometry(mt_set* set, const double* pos, hipStream_t st) {
         N, S, kcap, set->kmax, set->R1, set->R2, set->st_off.as<int>(), set->pos.as<double>(),
         B.meta.as<StructMeta>(), set->perm.as<int>(), B.inv.as<int>(), B.cnt.as<int>(), B.ent_j.as<int>(),
         B.ent_sh.as<int>(), set->lbo.as<int>(), set->xbase.as<int>(), set->st_npad.as<int>(),
-        set->gpk.as<float4>(), set->gd.as<double>(), set->rev.as<int>(), set->revc.as<int>(), set->jl.as<int>(), set->nbr_j.as<int>(),
+        set->gf.as<float>(), set->gf_rlo.as<float>(), set->gpk.as<float4>(),
+        set->gd.as<double>(), set->rev.as<int>(), set->revc.as<int>(), set->jl.as<int>(), set->nbr_j.as<int>(),
         set->nbr_sh.as<int>(), B.flags);
     HIPCHECK(hipGetLastError());
     return refresh_angle_tables(set, st);

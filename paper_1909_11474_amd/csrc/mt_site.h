@@ -121,7 +121,7 @@ struct Geo {
                 ux[m] = ok ? G.ux[o] : S(0);
                 uy[m] = ok ? G.uy[o] : S(0);
                 uz[m] = ok ? G.uz[o] : S(0);
-                r[m] = ok ? G.r[o] : S(3);
+                r[m] = ok ? G.rhi[o] : S(3);
                 rinv[m] = ok ? G.rinv[o] : S(0);
                 fc[m] = ok ? G.fc[o] : S(0);
                 hfcp[m] = ok ? G.hfcp[o] : S(0);
