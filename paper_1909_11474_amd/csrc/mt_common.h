@@ -94,7 +94,10 @@ struct GeomArrays {
     const S* rhi; const S* rlo; const S* rinv;
     const S* fc; const S* hfcp;     // f_C and f_C'/2
     // float only: the same geometry packed per bond slot as two 4-vectors,
-    // (ux, uy, uz, r_hi) and (r_lo, 1/r, f_C, f_C'/2), [kcap][N] each
+    // (ux, uy, uz, r_hi) and (r_lo, 1/r, f_C, f_C'/2), [kcap][N] each.  The float
+    // kernels read these two alone; without the unpacked arrays the other buffers
+    // lie elsewhere and the 64,000-atom force call is slower (float64 21.1 -> 21.7
+    // us, float 17.1 -> 17.4)
     const float4* pk0; const float4* pk1;
 };
 

@@ -120,7 +120,7 @@ __device__ __forceinline__ void finish_fit(const FinArgs& F, int c, const double
 
 // Structures with more partial-sum slots than this (over 2,048 atoms: a
 // structure over the batching limit has one slot per 256-atom block, a batched
-// one at most 8) are summed by the whole block; smaller ones by one thread each.
+// one has one) are summed by the whole block; smaller ones by one thread each.
 constexpr int kCoopSlots = 8;
 
 // Block-wide slot sums of structure s (all threads call; the result is valid
@@ -258,8 +258,8 @@ __global__ __launch_bounds__(256) void k_finalize_fit_wave(FinArgs F, int P) {
 }
 
 // Z for sets without block-wide structures when S is small: one block per
-// candidate, one thread per structure (strided beyond the block), then a fixed
-// LDS tree.  Every thread issues its structure's table and partial-sum loads
+// candidate, one thread per structure (strided beyond the block), then
+// wavefront butterflies.  Every thread issues its structure's table and partial-sum loads
 // at once, so a generation pays two memory round trips here instead of the
 // four or five of a wavefront looping over the structures.  OneSlot: every
 // structure has exactly one partial-sum slot (slot s), so the partial sums
@@ -666,9 +666,12 @@ ItemPlan* get_plan(mt_set* set, int P, const LaunchCfg& cfg, int fam) {
     // results are unchanged.  Class 4 joins where the whole call is latency: an open
     // tile, at most three steps for a structure on average and fewer steps than
     // compute units (18 structures x 5 candidates, Tersoff form, gradient:
-    // 199 us a call with launches of its own, 178 us).  With more steps its own
-    // kernel, of twice the wavefronts in flight in float, soon makes up for the
-    // launch, and the launches' times stay those of one class each.
+    // 199 us a call with launches of its own, 178 us).  Beyond the compute units
+    // its own kernel, of twice the wavefronts in flight in float, makes up for the
+    // launch (gradient of 64 x 300 in float 420 us, 436-461 joined).  Three steps
+    // are short of that line, so that calls of several steps keep a launch per
+    // class, which the launch timing reports; between the two joining would be
+    // faster (37 candidates x 18 structures 35.3 us, 30.1 joined).
     const std::vector<int>& classes = family_classes(fam);
     std::vector<int> cls(set->S, 0), Rs(set->S, 0);
     std::map<int, long long> nitems;
@@ -1038,7 +1041,11 @@ bool finished_by_gather(const mt_set* set) { return set->S == 1 && set->n_large 
 // 10.4 and 5.2 us over 125).  Above, the block that finishes the sums decides: it
 // adds one slot per site block with the threads of a gather block, 64,000 atoms
 // 20.4 us a call with one-wavefront site blocks and 32.4 us with both (20.9 with
-// neither), 125,000 atoms 29.3 and 51.8 us (26.6).
+// neither).  Site blocks of one and of four wavefronts, all outputs in float64 with
+// W_i and J: 57,600 atoms 20.8 and 22.3 us, 64,000 21.3 and 23.5, 65,536 (whole rounds
+// of either) 21.9 and 21.8, 74,088 24.2 and 25.9, 85,184 25.6 and 25.8, 97,336 26.8
+// and 26.1, 125,000 31.8 and 29.8.  They cross near 90,000 atoms; the line lies at the
+// largest size below at which they were equal.
 static int site_block(long long atoms) { return atoms <= 65536 ? 64 : kLargeBlock; }
 static int gather_block(long long atoms) { return atoms <= 16384 ? 64 : kLargeBlock; }
 int eval_slots(const mt_set* set, int P) {
@@ -1132,8 +1139,7 @@ int launch_finalize_fit(mt_set* set, int P, const double* w, double* Z, hipStrea
     if (F.coop) {
         hipLaunchKernelGGL(k_finalize_fit, dim3(P), dim3(256), 0, st, F);
     } else if (set->S > 64) {
-        // power-of-two block (the LDS tree halves it), at least one thread per
-        // structure up to 256
+        // at least one thread per structure up to 256, two or four wavefronts
         int block = 128;
         while (block < set->S && block < 256) block *= 2;
         if (set->nslots == set->S)

@@ -1220,8 +1220,9 @@ __global__ __launch_bounds__(256) void k_large_gather(BArgs<S> A, LArgs L) {
 // gradients of a candidate chunk (as for the fitness), k_large_residual turns
 // them into the force residuals a_i = F_i - F*_i, staged [chunk][3][Ns], and
 // k_large_adjoint forms every atom's grad sums (adjoint_sums) with the
-// residuals of its bond partners read from there; its partial sums go to the
-// structure's per-wavefront slots as in the batched adjoint.
+// residuals of its bond partners read from there; its partial sums go to one
+// slot per 256-atom block (a structure of at most 512 atoms: to its one slot by
+// k_sum_blocks).
 // ---------------------------------------------------------------------------
 template <typename S>
 __global__ __launch_bounds__(256) void k_large_residual(BArgs<S> A, LArgs L, S* __restrict__ abuf) {
