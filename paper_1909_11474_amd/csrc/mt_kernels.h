@@ -169,48 +169,44 @@ struct ItemCtx {
 __device__ __forceinline__ ItemCtx item_ctx(const SetDev& d, const Item& it) {
     // Item fields are uniform across the block; npad is 8, 16, 32, 64 or a
     // multiple of 64, so lane -> (replica, atom) needs no vector division.
+    // (Plain variables until the end: a struct written in the branches stays in
+    // scratch, and every use of a field is a load then.)
+    const int tid = threadIdx.x, R = it.R, npad = it.npad;
+    const bool one = npad <= 64;
+    const int sh = 31 - __clz(npad);
+    const int waves = npad >> 6;                           // wavefronts per replica above 64
+    const int wid = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int nw = blockDim.x >> 6;
+    // A structure's chunks of 64 atoms get cheaper in order (atoms are
+    // sorted by coordination), and wavefront w of a block runs on SIMD
+    // w mod 4: rows of four wavefronts take the (chunk, replica) pairs in
+    // turn from either end, so that no SIMD collects the costly chunks of
+    // several rows while the block waits for it at the exchange (M <= 12
+    // launch of 500 candidates x 101 packings: 765 us in plain order, 712 us).
+    const int row = wid & ~3, in_row = (nw - row) < 4 ? nw - row : 4;
+    const int rank = (row & 4) ? row + in_row - 1 - (wid - row) : wid;
+    const int chunk = rank / R;                            // scalar division
+    const bool in = chunk < waves;
     ItemCtx x;
     x.s = it.s;
     x.a0 = it.a0;
     x.Ns = it.ns;
-    x.npad = it.npad;
-    x.R = it.R;
-    const int tid = threadIdx.x;
-    if (x.npad <= 64) {
-        const int sh = 31 - __clz(x.npad);
-        x.q = tid >> sh;
-        x.la = tid & (x.npad - 1);
-        x.g = x.npad;
-        x.unit = 0;
-        x.wpr = 1;
-    } else {
-        const int wpr = x.npad >> 6;                       // wavefronts per replica
-        const int wid = __builtin_amdgcn_readfirstlane(tid >> 6);
-        const int nw = blockDim.x >> 6;
-        // A structure's chunks of 64 atoms get cheaper in order (atoms are
-        // sorted by coordination), and wavefront w of a block runs on SIMD
-        // w mod 4: rows of four wavefronts take the (chunk, replica) pairs in
-        // turn from either end, so that no SIMD collects the costly chunks of
-        // several rows while the block waits for it at the exchange (M <= 12
-        // launch of 500 candidates x 101 packings: 765 us in plain order, 712 us).
-        const int row = wid & ~3, in_row = (nw - row) < 4 ? nw - row : 4;
-        const int rank = (row & 4) ? row + in_row - 1 - (wid - row) : wid;
-        const int chunk = rank / x.R;                      // scalar division
-        x.unit = rank;
-        x.wpr = wpr;
-        x.q = chunk < wpr ? rank - chunk * x.R : x.R;
-        x.la = (chunk < wpr ? chunk << 6 : 0) + (tid & 63);
-        x.g = 64;
-    }
+    x.npad = npad;
+    x.R = R;
+    x.unit = one ? 0 : rank;
+    x.wpr = one ? 1 : waves;
+    x.g = one ? npad : 64;
+    x.q = one ? tid >> sh : in ? rank - chunk * R : R;
+    x.la = one ? tid & (npad - 1) : (in ? chunk << 6 : 0) + (tid & 63);
     x.active = (x.q < x.R) && (x.la < x.Ns);
     x.atom = x.a0 + (x.active ? x.la : 0);
     x.steps = (it.nc + x.R - 1) / x.R;
     x.slot = it.slot;
     x.xsz = it.xsz;
-    x.block_sync = x.npad > 64;
+    x.block_sync = npad > 64;
     // own exchange slot base: the first chunk's slots start at 0, and a chunk's
     // first atom is always a real atom
-    const int chunk0 = x.npad > 64 ? __builtin_amdgcn_readfirstlane(x.la & ~63) : 0;
+    const int chunk0 = one ? 0 : __builtin_amdgcn_readfirstlane(x.la & ~63);
     x.own = x.q < x.R ? (chunk0 ? d.xbase[x.a0 + chunk0] : 0) + (x.la - chunk0) + x.q * x.xsz : 0;
     // the wavefront's largest coordination is that of its first atom (sorted);
     // -1: no replica here (whole wavefronts past the last replica)
@@ -319,16 +315,21 @@ __device__ __forceinline__ void run_batched(const BArgs<S>& A, const Item& it, c
     constexpr int MM = M > 0 ? M : 1;
     int rv[MM];
 #pragma unroll
-    for (int m = 0; m < M; ++m)
-        rv[m] = x.active ? d.rev[(size_t)m * N + x.atom] + x.q * x.xsz : x.own + m * x.g;
+    for (int m = 0; m < M; ++m) {
+        rv[m] = d.rev[(size_t)m * N + x.atom] + x.q * x.xsz;
+        g.rows_apart();
+    }
+#pragma unroll
+    for (int m = 0; m < M; ++m) rv[m] = x.active ? rv[m] : x.own + m * x.g;
     const S* fr = fref_of<S>(d);
     S frx = S(0), fry = S(0), frz = S(0);
-    if (MODE == MODE_FIT && x.active) {
-        frx = fr[x.atom]; fry = fr[(size_t)N + x.atom]; frz = fr[(size_t)2 * N + x.atom];
+    if (MODE == MODE_FIT) {
+        const S a = fr[x.atom], b = fr[(size_t)N + x.atom], c = fr[(size_t)2 * N + x.atom];
+        frx = x.active ? a : S(0); fry = x.active ? b : S(0); frz = x.active ? c : S(0);
     }
-    const int orig = x.active ? d.perm[x.atom] : 0;
+    const int orig = d.perm[x.atom];
     S vx = S(0), vy = S(0), vz = S(0);
-    if (MODE == MODE_EVAL && A.vel && x.active) {
+    if (MODE == MODE_EVAL && A.vel) {
         vx = (S)A.vel[orig]; vy = (S)A.vel[(size_t)N + orig]; vz = (S)A.vel[(size_t)2 * N + orig];
     }
     __syncthreads();                                   // the records
@@ -386,8 +387,8 @@ __device__ __forceinline__ void run_batched(const BArgs<S>& A, const Item& it, c
             }
         }
         exchange_sync(sync);
-        // Lanes outside the structure have zero geometry and zero reference
-        // forces, so their energy, virial and residual are exactly zero.
+        // Lanes outside the structure have f_C = 0 and zero reference forces, so
+        // their energy, virial and residual are exactly zero.
         double v[8];
         v[0] = (double)U;
 #pragma unroll
@@ -507,6 +508,16 @@ struct WavesPerEU {
     static constexpr int value = (MC <= 4 && sizeof(S) == 4 && MODE == MODE_FIT) ? 4 : 1;
 };
 
+// The item, uniform across the block, in scalar registers: work lists do not change
+// while a kernel runs.
+__device__ __forceinline__ Item load_item(const Item* p) {
+    const auto* c = (const __attribute__((address_space(4))) Item*)p;
+    Item it;
+    it.s = c->s; it.c0 = c->c0; it.nc = c->nc; it.cost = 0;
+    it.a0 = c->a0; it.ns = c->ns; it.npad = c->npad; it.slot = c->slot; it.xsz = c->xsz; it.R = c->R;
+    return it;
+}
+
 template <typename S, int MODE, int MC, bool Full = false, bool Resid = false>
 __global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(WavesPerEU<S, MODE, MC>::value)))
 void k_batched(BArgs<S> A) {
@@ -515,7 +526,7 @@ void k_batched(BArgs<S> A) {
     const int b0 = A.bin_off ? A.bin_off[blockIdx.x] : (int)blockIdx.x;
     const int b1 = A.bin_off ? A.bin_off[blockIdx.x + 1] : b0 + 1;
     for (int i = b0; i < b1; ++i) {
-        const Item it = A.items[i];
+        const Item it = load_item(A.items + i);
         batched_item<S, MODE, MC, Full, Resid>(A, it, lds_raw + kRedBytes);
         __syncthreads();
     }
@@ -528,7 +539,7 @@ template <typename S, int MODE, int MC, bool Full = false>
 __global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(WavesPerEU<S, MODE, MC>::value)))
 void k_plain(BArgs<S> A) {
     extern __shared__ __align__(32) unsigned char lds_raw[];
-    batched_item<S, MODE, MC, Full>(A, A.items[0], lds_raw + kRedBytes);
+    batched_item<S, MODE, MC, Full>(A, load_item(A.items), lds_raw + kRedBytes);
 }
 
 // ---------------------------------------------------------------------------
@@ -836,7 +847,7 @@ __device__ __forceinline__ void run_adjoint(const BArgs<S>& A, const Item& it, c
     double* __restrict__ red = reinterpret_cast<double*>(lds - kRedBytes);
     int jl[MM];
 #pragma unroll
-    for (int m = 0; m < M; ++m) jl[m] = x.active ? d.jl[(size_t)m * N + x.atom] : x.la;
+    for (int m = 0; m < M; ++m) jl[m] = d.jl[(size_t)m * N + x.atom];
     __syncthreads();                                   // the records
     auto flush = [&](int step) __attribute__((always_inline)) {
         const int cl = x.q + step * x.R;
@@ -850,12 +861,9 @@ __device__ __forceinline__ void run_adjoint(const BArgs<S>& A, const Item& it, c
         const int c = it.c0 + clv;
         const Rec<S>& prec = pbuf[clv];
         // this atom's force residual, from the fitness call (lanes outside the
-        // structure: zero, and zero geometry)
-        S ax = S(0), ay = S(0), az = S(0);
-        if (x.active) {
-            const S* r = A.resid + (size_t)c * 3 * N;
-            ax = r[x.atom]; ay = r[(size_t)N + x.atom]; az = r[(size_t)2 * N + x.atom];
-        }
+        // structure: another atom's, and f_C = 0)
+        const S* r = A.resid + (size_t)c * 3 * N;
+        const S ax = r[x.atom], ay = r[(size_t)N + x.atom], az = r[(size_t)2 * N + x.atom];
         ab[x.la] = Vec4<S>{ax, ay, az, S(0)};
         exchange_sync(x.block_sync);
         if (x.block_sync && step > 0) flush(step - 1);
@@ -909,7 +917,7 @@ __global__ __launch_bounds__(512) void k_adjoint(BArgs<S> A) {
     const int b0 = A.bin_off ? A.bin_off[blockIdx.x] : (int)blockIdx.x;
     const int b1 = A.bin_off ? A.bin_off[blockIdx.x + 1] : b0 + 1;
     for (int i = b0; i < b1; ++i) {
-        const Item it = A.items[i];
+        const Item it = load_item(A.items + i);
         adjoint_item<S, MC, Full>(A, it, lds_raw + kRedBytes);
         __syncthreads();
     }
@@ -1263,14 +1271,15 @@ __device__ __forceinline__ void run_large_adjoint(const BArgs<S>& A, const LArgs
     g.load(d, atom, active, d.kcap);
     int jl[MM];
 #pragma unroll
-    for (int m = 0; m < M; ++m) jl[m] = (active && m < d.kcap) ? d.jl[(size_t)m * N + atom] : 0;
+    for (int m = 0; m < M; ++m) jl[m] = m < d.kcap ? d.jl[(size_t)m * N + atom] : 0;
     const int c = L.c0 + blockIdx.y;
     Rec<S> rec;
     decode_record<S, Full>(A.x + Form<Full>::nx * (size_t)c, rec);
     const S* a = abuf + (size_t)blockIdx.y * 3 * Ns;
-    const S ax = active ? a[la] : S(0), ay = active ? a[Ns + la] : S(0), az = active ? a[2 * Ns + la] : S(0);
+    const int own = atom - L.a0;
+    const S ax = a[own], ay = a[Ns + own], az = a[2 * Ns + own];
     S sums[NL];
-    // lanes past the structure have zero geometry: every sum is zero
+    // lanes past the structure have f_C = 0 on every bond: every sum is zero
     adjoint_sums<S, M, Full>(
         g, rec, ax, ay, az,
         [&](int m) {

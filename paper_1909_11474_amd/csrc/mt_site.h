@@ -56,12 +56,13 @@ struct Geo {
     // sum f_C u u^T and sum f_C u over the bonds
     S txx, tyy, tzz, tyz, tzx, txy, mx, my, mz;
 
-    __device__ __forceinline__ void load_moments(const SetDev& d, int atom, bool active, int rows) {
+    __device__ __forceinline__ void load_moments(const SetDev& d, int atom, int rows) {
         if constexpr (kMoments) {
 #pragma unroll
             for (int m = 0; m < M; ++m) {
-                const float4 a = active && m < rows ? d.gam[(size_t)m * d.N + atom] : make_float4(0.f, 0.f, 0.f, 0.f);
+                const float4 a = m < rows ? d.gam[(size_t)m * d.N + atom] : make_float4(0.f, 0.f, 0.f, 0.f);
                 ss[m] = a.x; sh[m] = a.y; sv[m] = a.z;
+                rows_apart();
             }
             txx = tyy = tzz = tyz = tzx = txy = mx = my = mz = S(0);
 #pragma unroll
@@ -72,6 +73,12 @@ struct Geo {
                 tyz += fy * uz[m]; tzx += fz * ux[m]; txy += fx * uy[m];
             }
         }
+    }
+
+    // Loads stay in the order of the rows in the variants that fill the registers:
+    // brought together, they spill values that the candidate loop then reloads.
+    static __device__ __forceinline__ void rows_apart() {
+        if constexpr (M > 6) __builtin_amdgcn_sched_barrier(0);
     }
 
     __device__ __forceinline__ S length(int m) const { return (S)r[m]; }
@@ -90,19 +97,27 @@ struct Geo {
     // unit vectors they carry up to ~2e-7 absolute error, which zeta passes on
     // to the energy through (cos - h)^2.
     // rows: neighbour rows the arrays hold (a variant wider than the set's
-    // capacity reads the rows past it as padding bonds)
+    // capacity reads the rows past it as padding bonds).  Lanes outside the
+    // structure (not active) read the atom that they are given, with f_C = 0 on
+    // every bond, so that they add nothing.  They take no branch of their own: at
+    // its end the compiler may spill registers while those lanes are still off, and
+    // a kernel of many spills then went on with whatever the spill slot held.
     __device__ __forceinline__ void load(const SetDev& d, int atom, bool active, int rows = M) {
         const int N = d.N;
         if constexpr (sizeof(S) == 4) {
+            float rhi[M > 0 ? M : 1], rlo[M > 0 ? M : 1];
 #pragma unroll
             for (int m = 0; m < M; ++m) {
                 const size_t o = (size_t)m * N + atom;
-                const bool ok = active && m < rows;
+                const bool ok = m < rows;
                 const float4 a = ok ? d.gf.pk0[o] : make_float4(0.f, 0.f, 0.f, 3.f);
                 const float4 b = ok ? d.gf.pk1[o] : make_float4(0.f, 0.f, 0.f, 0.f);
-                ux[m] = a.x; uy[m] = a.y; uz[m] = a.z; r[m] = (double)a.w + (double)b.x;
+                ux[m] = a.x; uy[m] = a.y; uz[m] = a.z; rhi[m] = a.w; rlo[m] = b.x;
                 rinv[m] = b.y; fc[m] = b.z; hfcp[m] = b.w;
+                rows_apart();
             }
+#pragma unroll
+            for (int m = 0; m < M; ++m) r[m] = (double)rhi[m] + (double)rlo[m];
             if constexpr (kCache && NP > 0) {
                 static_assert(M <= 6, "the pair table holds bonds 0-5");
                 int p = 0;
@@ -110,14 +125,14 @@ struct Geo {
                 for (int j = 0; j < M; ++j)
 #pragma unroll
                     for (int k = j + 1; k < M; ++k)
-                        cs[p++] = active && k < rows ? d.gcs[(size_t)(k * (k - 1) / 2 + j) * N + atom] : S(0);
+                        cs[p++] = k < rows ? d.gcs[(size_t)(k * (k - 1) / 2 + j) * N + atom] : S(0);
             }
         } else {
             const GeomArrays<double>& G = d.gd;
 #pragma unroll
             for (int m = 0; m < M; ++m) {
                 const size_t o = (size_t)m * N + atom;
-                const bool ok = active && m < rows;
+                const bool ok = m < rows;
                 ux[m] = ok ? G.ux[o] : S(0);
                 uy[m] = ok ? G.uy[o] : S(0);
                 uz[m] = ok ? G.uz[o] : S(0);
@@ -125,10 +140,16 @@ struct Geo {
                 rinv[m] = ok ? G.rinv[o] : S(0);
                 fc[m] = ok ? G.fc[o] : S(0);
                 hfcp[m] = ok ? G.hfcp[o] : S(0);
+                rows_apart();
             }
             cache_cos();
         }
-        load_moments(d, atom, active, rows);
+#pragma unroll
+        for (int m = 0; m < M; ++m) {
+            fc[m] = active ? fc[m] : S(0);
+            hfcp[m] = active ? hfcp[m] : S(0);
+        }
+        load_moments(d, atom, rows);
     }
 
     __device__ __forceinline__ void cache_cos() {
