@@ -310,7 +310,8 @@ __device__ __forceinline__ void run_batched(const BArgs<S>& A, const Item& it, c
     double* __restrict__ red = reinterpret_cast<double*>(lds - kRedBytes);
     const Rec<S>* __restrict__ pbuf = reinterpret_cast<const Rec<S>*>(lds);
     Vec4<S>* __restrict__ xb = reinterpret_cast<Vec4<S>*>(lds + lds_param_bytes<S>(it.nc));
-    Geo<S, M, Full> g;
+    constexpr bool Mom = MODE != MODE_EVAL;
+    Geo<S, M, Full, Mom> g;
     g.load(d, x.atom, x.active);
     constexpr int MM = M > 0 ? M : 1;
     int rv[MM];
@@ -356,7 +357,7 @@ __device__ __forceinline__ void run_batched(const BArgs<S>& A, const Item& it, c
         S w6[6];
 #pragma unroll
         for (int k = 0; k < 6; ++k) w6[k] = S(0);
-        site_eval_sink<S, M, true, (M > kPairwiseMax<S, Full>), Full>(
+        site_eval_sink<S, M, true, (M > kPairwiseMax<S, Full, Mom>), Full, true, Mom>(
             g, p, U, [&](int m, S gx, S gy, S gz) {
                 S* slot = &xb[x.own + m * x.g].x;     // the fourth component is never read
                 slot[0] = gx;
@@ -988,7 +989,7 @@ __device__ __forceinline__ void run_large_site(const BArgs<S>& A, const LArgs& L
                                                int rows = M) {
     const SetDev& d = A.set;
     const int N = d.N;
-    Geo<S, M, Full> g;
+    Geo<S, M, Full, false> g;
     g.load(d, atom, active, rows);
     constexpr int MM = M > 0 ? M : 1;
     const int c = L.c0 + blockIdx.y;
@@ -1018,7 +1019,7 @@ __device__ __forceinline__ void run_large_site(const BArgs<S>& A, const LArgs& L
     S Gx[MM], Gy[MM], Gz[MM];
     // about one wavefront per SIMD for a large structure: the bonds' float64
     // energy chains interleave
-    site_eval<S, M, E64, Full, false>(g, p, U, Gx, Gy, Gz);
+    site_eval<S, M, E64, Full, false, false>(g, p, U, Gx, Gy, Gz);
     using V4 = typename Stage4<S>::T;
     V4* gb = reinterpret_cast<V4*>(L.gbuf) + (size_t)blockIdx.y * nbs;
     if (active) {

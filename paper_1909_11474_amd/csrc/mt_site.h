@@ -36,11 +36,18 @@
 
 namespace mt {
 
-template <typename S, int M, bool Full = false>
+// Mom: the geometry serves many candidates (batched fitness and gradient), so the
+// float minimal form takes moments above kPairMax neighbours.  The evaluation and
+// two-pass kernels run one or a few candidates a block and are bound by latency:
+// the moments' registers (3 M + 9 more) spill there and cost more than the pair sums.
+// Evaluations in float, 500 close-packed atoms 26.0 us with pairs, 30.0 with moments;
+// six cells of 14 neighbours x 64 candidates 42 and 51 us; fitness of a 1,500-atom
+// packing x 400 138 and 146 us.
+template <typename S, int M, bool Full = false, bool Mom = true>
 struct Geo {
     static constexpr int NP = M * (M - 1) / 2;
     static constexpr bool kCache = NP <= 15;       // keep cos(theta) in registers for M <= 6
-    static constexpr bool kMoments = !Full && sizeof(S) == 4 && M > kPairMax;
+    static constexpr bool kMoments = Mom && !Full && sizeof(S) == 4 && M > kPairMax;
     S ux[M > 0 ? M : 1], uy[M > 0 ? M : 1], uz[M > 0 ? M : 1];
     double r[M > 0 ? M : 1];                      // float64 also in the float geometry: r - r0
     S rinv[M > 0 ? M : 1];
@@ -76,9 +83,11 @@ struct Geo {
     }
 
     // Loads stay in the order of the rows in the variants that fill the registers:
-    // brought together, they spill values that the candidate loop then reloads.
+    // brought together, they spill values that the candidate loop then reloads
+    // (without Mom the Tersoff form is faster as the compiler orders them: 500
+    // close-packed atoms x 64 candidates in float 37 us, 40 in the rows' order).
     static __device__ __forceinline__ void rows_apart() {
-        if constexpr (M > 6) __builtin_amdgcn_sched_barrier(0);
+        if constexpr (M > 6 && (Mom || !Full)) __builtin_amdgcn_sched_barrier(0);
     }
 
     __device__ __forceinline__ S length(int m) const { return (S)r[m]; }
@@ -235,8 +244,8 @@ __device__ __forceinline__ void opaque(T (&a)[N]) {
 // (where it does not take moments).  Above it one bond at a time: more pair
 // arithmetic, but four running sums instead of 4 M.  Float Tersoff form, 200
 // candidates x 22 packings: 134 us at 6, 142 at 8, 153 at 10, 181 at 12.
-template <typename S, bool Full>
-constexpr int kPairwiseMax = Full && sizeof(S) == 4 ? 6 : 8;
+template <typename S, bool Full, bool Mom = true>
+constexpr int kPairwiseMax = Mom && Full && sizeof(S) == 4 ? 6 : 8;
 
 // The site routine.  It hands each bond gradient G_j to sink(j, Gx, Gy, Gz);
 // PerBond selects the one-bond-at-a-time backward sweep (for large M without
@@ -254,12 +263,12 @@ struct ParkRegs {
     __device__ __forceinline__ void get(int j, S& x, S& y) const { x = a[j]; y = b[j]; }
 };
 
-template <typename S, int M, bool Energy64, bool PerBond, bool Full = false, bool SerialE64 = true,
+template <typename S, int M, bool Energy64, bool PerBond, bool Full = false, bool SerialE64 = true, bool Mom = true,
           typename Sink, typename Park>
-__device__ __forceinline__ void site_eval_sink(Geo<S, M, Full>& g, const Cand<S, Full>& p,
+__device__ __forceinline__ void site_eval_sink(Geo<S, M, Full, Mom>& g, const Cand<S, Full>& p,
                                                typename EnergyOf<S>::type& U, Sink&& sink, Park&& park) {
     constexpr int MM = M > 0 ? M : 1;
-    if constexpr (!Geo<S, M, Full>::kCache && M > 1) {
+    if constexpr (!Geo<S, M, Full, Mom>::kCache && M > 1) {
         // cos(theta) is not cached for larger M: keep the compiler from
         // hoisting the M (M - 1) / 2 values out of the candidate loop (they
         // would not fit in registers and go to scratch)
@@ -339,9 +348,9 @@ __device__ __forceinline__ void site_eval_sink(Geo<S, M, Full>& g, const Cand<S,
         ccj = (p.ccs * g.fc[j]) * (bfA * zn) * drcp_inf(zsafe * onep);
         // keep the scheduler from interleaving all M bonds' chains (about ten
         // live values each; float64 ones in the energy mode)
-        if constexpr (PerBond || Geo<S, M, Full>::kMoments || (kE64 && SerialE64)) __builtin_amdgcn_sched_barrier(0);
+        if constexpr (PerBond || Geo<S, M, Full, Mom>::kMoments || (kE64 && SerialE64)) __builtin_amdgcn_sched_barrier(0);
     };
-    if constexpr (Geo<S, M, Full>::kMoments) {
+    if constexpr (Geo<S, M, Full, Mom>::kMoments) {
         // The pair sums of every bond from the moments over all bonds:
         //   sum_k (c~_j f_C,k + c~_k f_C,j) t_jk u_k = c~_j (T u_j - h m) + f_C,j (T~ u_j - h m~),
         //   sum_k c~_k t_jk^2 = u_j . T~ u_j - 2 h u_j . m~ + h^2 s~,
@@ -480,12 +489,12 @@ __device__ __forceinline__ void site_eval_sink(Geo<S, M, Full>& g, const Cand<S,
 }
 
 // The site routine with the bond gradients returned in arrays.
-template <typename S, int M, bool Energy64 = false, bool Full = false, bool SerialE64 = true>
-__device__ __forceinline__ void site_eval(Geo<S, M, Full>& g, const Cand<S, Full>& p,
+template <typename S, int M, bool Energy64 = false, bool Full = false, bool SerialE64 = true, bool Mom = true>
+__device__ __forceinline__ void site_eval(Geo<S, M, Full, Mom>& g, const Cand<S, Full>& p,
                                           typename EnergyOf<S>::type& U,
                                           S* __restrict__ Gx, S* __restrict__ Gy,
                                           S* __restrict__ Gz) {
-    site_eval_sink<S, M, Energy64, (M > kPairwiseMax<S, Full>), Full, SerialE64>(
+    site_eval_sink<S, M, Energy64, (M > kPairwiseMax<S, Full, Mom>), Full, SerialE64, Mom>(
         g, p, U, [&](int j, S x, S y, S z) {
             Gx[j] = x;
             Gy[j] = y;

@@ -34,3 +34,13 @@ def test_small_classes_have_no_scratch():
     small = [n for n in s if re.search(r"k_batchedI(fLi0ELi6|fLi1ELi4)E|k_adjointIfLi4E", n)]
     assert len(small) == 6
     assert {n: s[n] for n in small if s[n]} == {}
+
+
+def test_float_evaluation_takes_no_moments():
+    """The float evaluation kernel of up to 16 neighbours holds no angular moments, whose
+    registers would go to scratch (1,080 bytes a lane or more with them, 832 without)."""
+    if not os.path.exists(B.LIB):
+        pytest.skip("library not built")
+    s = scratch_bytes()
+    n, = [n for n in s if n.startswith("_ZN2mt9k_batchedIfLi1ELi16ELb0E")]
+    assert 0 < s[n] < 1000
