@@ -85,9 +85,11 @@ struct Geo {
     // Loads stay in the order of the rows in the variants that fill the registers:
     // brought together, they spill values that the candidate loop then reloads
     // (without Mom the Tersoff form is faster as the compiler orders them: 500
-    // close-packed atoms x 64 candidates in float 37 us, 40 in the rows' order).
+    // close-packed atoms x 64 candidates in float 37 us, 40 in the rows' order; in
+    // float64 its gradient is not, at four neighbours either: 64 candidates x 100 cells 86
+    // us in the rows' order, 87).
     static __device__ __forceinline__ void rows_apart() {
-        if constexpr (M > 6 && (Mom || !Full)) __builtin_amdgcn_sched_barrier(0);
+        if constexpr (M > 6 ? Mom || !Full : sizeof(S) == 8 && Full && Mom) __builtin_amdgcn_sched_barrier(0);
     }
 
     __device__ __forceinline__ S length(int m) const { return (S)r[m]; }
