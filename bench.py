@@ -61,9 +61,9 @@ PMC_TRAFFIC = {
                 "paper_1909_11474_amd/csrc/mt_site.h",
                 "paper_1909_11474_amd/csrc/mt_kernels.h", "paper_1909_11474_amd/csrc/mt_k_fit32.hip",
                 "paper_1909_11474_amd/csrc/mt_eval.hip", "paper_1909_11474_amd/build.py"],
-    "sha256_16": "0f6ada335d7ba575",
-    "fetch_bytes": 21996.6 * 1024 * 2.00,
-    "write_bytes": 26224.6 * 1024 * 1.00,
+    "sha256_16": "4e730abbab36a28f",
+    "fetch_bytes": 25288.2 * 1024 * 2.00,
+    "write_bytes": 25296.7 * 1024 * 1.00,
 }
 
 

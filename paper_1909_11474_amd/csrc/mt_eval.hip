@@ -670,8 +670,9 @@ ItemPlan* get_plan(mt_set* set, int P, const LaunchCfg& cfg, int fam) {
     // its own kernel, of twice the wavefronts in flight in float, makes up for the
     // launch (gradient of 64 x 300 in float 420 us, 436-461 joined).  Three steps
     // are short of that line, so that calls of several steps keep a launch per
-    // class, which the launch timing reports; between the two joining would be
-    // faster (37 candidates x 18 structures 35.3 us, 30.1 joined).
+    // class, which the launch timing reports; between the two joining was faster
+    // when the kernels were slower (37 candidates x 18 structures 35.3 us, 30.1
+    // joined; 26.4 now, not joined).
     const std::vector<int>& classes = family_classes(fam);
     std::vector<int> cls(set->S, 0), Rs(set->S, 0);
     std::map<int, long long> nitems;
