@@ -30,9 +30,10 @@ def test_small_classes_have_no_scratch():
          if re.match(r"_ZN2mt9(k_batched|k_adjoint)I", n)}
     assert len(s) >= 30 and max(s.values()) > 100          # the larger classes do spill
     # k_batched<S, mode, class, ...>: float fitness of class 6, evaluation of class 4;
-    # k_adjoint<S, class, ...>: float class 4
-    small = [n for n in s if re.search(r"k_batchedI(fLi0ELi6|fLi1ELi4)E|k_adjointIfLi4E", n)]
-    assert len(small) == 6
+    # k_adjoint<S, class, ...>: float class 4 of the Tersoff form (the minimal form's is held
+    # to 128 registers for four wavefronts a SIMD, and spills for that)
+    small = [n for n in s if re.search(r"k_batchedI(fLi0ELi6|fLi1ELi4)E|k_adjointIfLi4ELb1E", n)]
+    assert len(small) == 5
     assert {n: s[n] for n in small if s[n]} == {}
 
 
